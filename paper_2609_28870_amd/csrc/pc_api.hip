@@ -136,6 +136,25 @@ pc_status fill_u32_gated(uint32_t *p, uint32_t value, size_t count, hipStream_t 
     return PC_OK;
 }
 
+__global__ void fill_all_kernel(Fills f, const int32_t *__restrict__ gate) {
+    if (gated_off(gate)) return;
+    const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int a = 0; a < f.n; ++a) {
+        uint32_t *p = f.p[a];
+        const uint32_t v = f.value[a];
+        const size_t n = f.count[a];
+        for (size_t i = first; i < n; i += stride) p[i] = v;
+    }
+}
+
+pc_status fill_all(const Fills &f, hipStream_t s, const int32_t *gate) {
+    size_t most = 0;
+    for (int a = 0; a < f.n; ++a) most = f.count[a] > most ? f.count[a] : most;
+    if (most == 0) return PC_OK;
+    PC_LAUNCH(K_FILL32, fill_all_kernel, dim3(fill_blocks(most)), dim3(256), 0, s, f, gate);
+    return PC_OK;
+}
+
 }  // namespace pc
 
 extern "C" {
