@@ -56,16 +56,16 @@ ALGO_BYTES = {
     "runs_fill": lambda B: 4,
 }
 # generic prev/next kernels: per element of the key streams they sort
-GENERIC_PN = ("sort_digit_hist", "sort_digit_scan", "sort_onesweep_pass", "link_partition", "perm_partition",
+GENERIC_PN = ("sort_digit_hist", "sort_high_bits", "sort_onesweep_pass", "link_partition", "perm_partition",
               "perm_local")
 
 
 def chain_bytes(name, n, n_slots, m, n_req):
     """Algorithmic bytes per launch of the chained prev/next's own kernels
     (n accesses, n_slots anchor slots, m unresolved accesses, n_req requests)."""
-    return {# two launches: the layout check (offsets in), the anchors (key in; slot key + record out)
-            "chain_anchor": (n_req * 16 + n_slots * (8 + 8 + 16)) // 2,
-            "chain_scan": n_slots * (4 + 4 + 4) // 3,     # three launches over the slot counts
+    return {# the layout check (offsets in) and the anchors (key in; slot key + record out)
+            "chain_anchor": n_req * 16 + n_slots * (8 + 8 + 16),
+            "chain_scan": n_slots * (4 + 4 + 4) // 2,     # two launches over the slot counts
             # slot record, masks, offset in; key in, (key, pos, flag) out
             "chain_compact": n_slots * (16 + 16 + 4) + m * (8 + 8 + 4 + 1),
             "chain_merge": m * (1 + 4 + 4 + 4 + 8),       # (flag, pos, prev, next) in; prev / next out
@@ -78,7 +78,7 @@ def log(*a):
 
 # HIP kernel behind each timed kernel id (for the committed counter summary)
 HIP_KERNEL = {"sort_onesweep_pass": "pc::sort_pass_kernel", "link_partition": "pc::link_partition_kernel",
-              "perm_partition": "pc::perm_partition_kernel", "hash_blocks": "pc::hash_fused_kernel",
+              "perm_partition": "pc::perm_partition_kernel", "hash_blocks": "pc::hash_kernel",
               "sd_local_finish": "pc::sd_local_kernel",
               "perm_local": "pc::perm_local_kernel", "mrc_hist": "pc::mrc_hist_kernel",
               "request_distance": "pc::req_dist_kernel",
@@ -438,8 +438,8 @@ def main():
 
     ms_step = wall * 1e3 / args.steps
     value = n_blocks / (ms_step / 1e3)
-    # the four high-key sort passes of each inner prev/next exit at once
-    # unless its first link asked for them; count only passes that moved data
+    # the launch for the high key bits of each inner prev/next exits at once
+    # unless its first link asked for it; count only launches that moved data
     chain = pc.chained_info(pipe.ws_pn) if pipe.chained else None
     if chain:
         log("chained prev/next:", chain)
@@ -453,8 +453,8 @@ def main():
         calls = 1
         highs = int(pc.high_key_passes_ran(pipe.ws_pn))
         n_slots = pn_elems = n_blocks
-    work_launches = {"sort_onesweep_pass": 4 * calls + 4 * highs, "link_partition": calls + highs,
-                     "sort_digit_hist": calls + highs}
+    work_launches = {"sort_onesweep_pass": 4 * calls, "link_partition": calls, "sort_digit_hist": calls,
+                     "sort_high_bits": highs}
     # bins: dist in, depth in unless it comes from the request layout, next in
     # when the next-use histogram is taken
     layout_depth = getattr(pipe, "layout_depth", False)
@@ -494,12 +494,12 @@ def main():
         mt["GBps_at_this_run"] = round(roof["traffic"] / (d["avg_working_launch_ms"] / 1e3) / 1e9, 1)
     roof["traffic_detail"] = mt
     stage_of = {"hash_blocks": "hash", "sort_digit_hist": "prev_next",
-                "sort_digit_scan": "prev_next", "sort_onesweep_pass": "prev_next",
+                "sort_high_bits": "prev_next", "sort_onesweep_pass": "prev_next",
                 "link_partition": "prev_next",
                 "perm_partition": "prev_next", "perm_local": "prev_next", "chain_anchor": "prev_next",
                 "chain_stair": "prev_next", "chain_scan": "prev_next", "chain_compact": "prev_next",
                 "chain_merge": "prev_next", "mrc_hist": "mrc", "mrc_map": "mrc",
-                "mrc_cost": "mrc", "request_distance": "request_distance",
+                "request_distance": "request_distance",
                 "session_requests": "session_profile" if args.profile else "session_distance",
                 "session_distance": "session_distance",
                 "reuse_profile_pack": "reuse_profile", "reuse_profile_walk": "reuse_profile",

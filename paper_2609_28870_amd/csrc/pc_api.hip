@@ -12,7 +12,7 @@ static const char *kernel_name(KernelId k) {
     case K_FILL32: return "fill_u32";
     case K_HASH: return "hash_blocks";
     case K_SORT_HIST: return "sort_digit_hist";
-    case K_SORT_SCAN: return "sort_digit_scan";
+    case K_SORT_HIGH: return "sort_high_bits";
     case K_SORT_PASS: return "sort_onesweep_pass";
     case K_LINK: return "link_partition";
     case K_PERM: return "perm_partition";
@@ -25,7 +25,6 @@ static const char *kernel_name(KernelId k) {
     case K_SD_PASS: return "sd_dominance_pass";
     case K_SD_LOCAL: return "sd_local_finish";
     case K_MRC_HIST: return "mrc_hist";
-    case K_MRC_COST: return "mrc_cost";
     case K_REQ_ORDER: return "request_order";
     case K_REQ_DIST: return "request_distance";
     case K_SESS_REQ: return "session_requests";
@@ -109,14 +108,6 @@ __global__ void fill_u32_kernel(uint32_t *__restrict__ p, uint32_t value, size_t
     for (; i < count; i += stride) p[i] = value;
 }
 
-__global__ void fill_u32_gated_kernel(uint32_t *__restrict__ p, uint32_t value, size_t count,
-                                      const int32_t *__restrict__ gate) {
-    if (*gate == 0) return;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = value;
-}
-
 static unsigned fill_blocks(size_t count) {
     size_t blocks = (count + 255) / 256;
     if (blocks > 65536) blocks = 65536;
@@ -129,29 +120,20 @@ pc_status fill_u32(uint32_t *p, uint32_t value, size_t count, hipStream_t s) {
     return PC_OK;
 }
 
-pc_status fill_u32_gated(uint32_t *p, uint32_t value, size_t count, hipStream_t s, const int32_t *gate) {
-    if (!gate) return fill_u32(p, value, count, s);
-    if (count == 0) return PC_OK;
-    PC_LAUNCH(K_FILL32, fill_u32_gated_kernel, dim3(fill_blocks(count)), dim3(256), 0, s, p, value, count, gate);
-    return PC_OK;
-}
-
 __global__ void fill_all_kernel(Fills f, const int32_t *__restrict__ gate) {
     if (gated_off(gate)) return;
-    const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int a = 0; a < f.n; ++a) {
-        uint32_t *p = f.p[a];
-        const uint32_t v = f.value[a];
-        const size_t n = f.count[a];
-        for (size_t i = first; i < n; i += stride) p[i] = v;
-    }
+    fill_segments(f);
+}
+
+unsigned fill_blocks(const Fills &f) {
+    size_t most = 0;
+    for (int a = 0; a < f.n; ++a) most = f.count[a] > most ? f.count[a] : most;
+    const unsigned b = fill_blocks(most);
+    return b ? b : 1;
 }
 
 pc_status fill_all(const Fills &f, hipStream_t s, const int32_t *gate) {
-    size_t most = 0;
-    for (int a = 0; a < f.n; ++a) most = f.count[a] > most ? f.count[a] : most;
-    if (most == 0) return PC_OK;
-    PC_LAUNCH(K_FILL32, fill_all_kernel, dim3(fill_blocks(most)), dim3(256), 0, s, f, gate);
+    PC_LAUNCH(K_FILL32, fill_all_kernel, dim3(fill_blocks(f)), dim3(256), 0, s, f, gate);
     return PC_OK;
 }
 

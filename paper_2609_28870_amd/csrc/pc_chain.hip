@@ -53,11 +53,11 @@ constexpr int HW_STATUS = 0;
 constexpr int HW_PATH = 1;       // 0 = chain path verified, 1 = generic over all keys
 constexpr int HW_UNRESOLVED = 2; // accesses that went through the compacted prev/next
 constexpr int HW_REASON = 3;     // why the generic path ran: 1 layout, 2 too many unresolved, 3 check, 4 nested error
-constexpr int HW_BAD = 4;        // device flag: invalid block layout
+constexpr int HW_BAD = 4;        // device flag: invalid block layout (HW_CHAIN is then 0)
 constexpr int HW_FAIL = 5;       // device flag: a merge check failed
 constexpr int HW_HIGH_ANCHOR = 6;     // the prev/next over the anchors also sorted by the high key bits
 constexpr int HW_HIGH_UNRESOLVED = 7; // the prev/next over the unresolved accesses did
-constexpr int HW_CHAIN = 8;      // gate: 1 while the chain path goes on
+constexpr int HW_CHAIN = 8;      // gate: 1 while the chain path goes on (0 from the start for an invalid layout)
 constexpr int HW_WORDS = 16;     // header words cleared by each call
 
 __device__ __forceinline__ int wave_id_uniform() {
@@ -80,33 +80,31 @@ __device__ __forceinline__ uint64_t lane_pos(const Slot &q, int lane, int deepes
     return deepest ? q.pos - (uint64_t)lane : q.pos + (uint64_t)lane;
 }
 
-// Every request: blk_off[r] <= blk_off[r+1], blk_off[0] = 0, blk_off[R] = n.
-__global__ void chain_layout_kernel(const uint64_t *__restrict__ off, uint32_t n_seqs, uint64_t n,
-                                    int32_t *__restrict__ hdr) {
-    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_seqs) return;
-    const uint64_t a = off[r], b = off[r + 1];
-    bool ok = a <= b && b <= n;
-    if (r == 0) ok = ok && a == 0;
-    if (r + 1 == n_seqs) ok = ok && b == n;
-    if (!ok) {
-        atomicOr(hdr + HW_BAD, 1);
-        atomicOr(hdr + HW_STATUS, DEV_ERR_BAD_LAYOUT);
-    }
-}
-
-// One wave per request: the request's anchors go to slots
+// One wave per request: checks the layout (blk_off[r] <= blk_off[r+1],
+// blk_off[0] = 0, blk_off[R] = n) and writes the request's anchors to slots
 // base(r) .. base(r) + ceil(len / S) - 1, base(r) = floor(blk_off[r] / S) + r,
 // in time order (ascending depth, or descending in the deepest-first
-// layout); the slots up to the next request's first one get filler keys.
+// layout); the slots up to the next request's first one get filler keys.  A
+// request with a bad range writes nothing and ends the chain path; the others
+// stay inside the slots whatever their neighbours' ranges are.
 __global__ __launch_bounds__(CH_THREADS) void chain_anchor_kernel(
-    const uint64_t *__restrict__ keys, const uint64_t *__restrict__ off, uint32_t n_seqs, uint64_t n_slots,
-    int deepest, uint64_t *__restrict__ akeys, uint4 *__restrict__ rec, const int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
+    const uint64_t *__restrict__ keys, const uint64_t *__restrict__ off, uint32_t n_seqs, uint64_t n, uint64_t n_slots,
+    int deepest, uint64_t *__restrict__ akeys, uint4 *__restrict__ rec, int32_t *__restrict__ hdr) {
     const int lane = threadIdx.x & (WAVE - 1);
     const uint64_t waves = (uint64_t)gridDim.x * (CH_THREADS / WAVE);
     for (uint64_t r = (uint64_t)blockIdx.x * (CH_THREADS / WAVE) + wave_id_uniform(); r < n_seqs; r += waves) {
         const uint64_t o0 = off[r], o1 = off[r + 1];
+        bool ok = o0 <= o1 && o1 <= n;
+        if (r == 0) ok = ok && o0 == 0;
+        if (r + 1 == n_seqs) ok = ok && o1 == n;
+        if (!ok) {
+            if (lane == 0) {
+                atomicOr(hdr + HW_BAD, 1);
+                atomicOr(hdr + HW_STATUS, DEV_ERR_BAD_LAYOUT);
+                atomicAnd(hdr + HW_CHAIN, 0);
+            }
+            continue;
+        }
         const uint64_t len = o1 - o0, base = o0 / CH_S + r, n_anchor = (len + CH_S - 1) / CH_S;
         const uint64_t next_base = (r + 1 < n_seqs) ? o1 / CH_S + r + 1 : n_slots;
         for (uint64_t i = lane; base + i < next_base; i += WAVE) {
@@ -155,7 +153,7 @@ __global__ __launch_bounds__(CH_THREADS) void chain_stair_kernel(
     const uint64_t *__restrict__ keys, uint64_t n_slots, const uint4 *__restrict__ rec,
     const uint32_t *__restrict__ aprev, int deepest, uint32_t *__restrict__ prev, uint32_t *__restrict__ next,
     int want_next, uint4 *__restrict__ open, uint2 *__restrict__ claimed, const int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
+    if (!hdr[HW_CHAIN]) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const uint64_t waves = (uint64_t)gridDim.x * (CH_THREADS / WAVE);
     const Slot none{0, 0, NONE};
@@ -197,64 +195,61 @@ __global__ __launch_bounds__(CH_THREADS) void chain_stair_kernel(
 }
 
 // Per slot: the lanes without a next link (valid and not claimed), into
-// open[j].zw, and the count of lanes open on either side.
-__global__ __launch_bounds__(256) void chain_count_kernel(uint64_t n_slots, const uint4 *__restrict__ rec,
-                                                          const uint2 *__restrict__ claimed, uint4 *__restrict__ open,
-                                                          uint32_t *__restrict__ cnt, const int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
-    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_slots) return;
-    const uint32_t lanes = rec[j].z;
-    const uint64_t valid = lanes >= (uint32_t)WAVE ? ~0ull : (1ull << lanes) - 1;
-    const uint2 c = claimed[j];
-    const uint64_t mx = valid & ~((uint64_t)c.x | ((uint64_t)c.y << 32));
-    const uint4 o = open[j];
-    const uint64_t mp = (uint64_t)o.x | ((uint64_t)o.y << 32);
-    open[j] = make_uint4(o.x, o.y, (uint32_t)mx, (uint32_t)(mx >> 32));
-    cnt[j] = (uint32_t)__popcll(mp | mx);
-}
-
-// Exclusive scan of cnt[0 .. m) into out[0 .. m], out[m] = total: tile sums,
-// one workgroup over the tile sums, then each tile again with its base.
-__global__ __launch_bounds__(SCAN_THREADS) void chain_scan_tiles_kernel(const uint32_t *__restrict__ cnt,
-                                                                        uint64_t m, uint32_t *__restrict__ tsum,
-                                                                        const int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
+// open[j].zw, and the count of lanes open on either side; and the sum of the
+// counts per tile of SCAN_TILE slots.
+__global__ __launch_bounds__(SCAN_THREADS) void chain_count_kernel(uint64_t n_slots, const uint4 *__restrict__ rec,
+                                                                   const uint2 *__restrict__ claimed,
+                                                                   uint4 *__restrict__ open,
+                                                                   uint32_t *__restrict__ cnt,
+                                                                   uint32_t *__restrict__ tsum,
+                                                                   const int32_t *__restrict__ hdr) {
+    if (!hdr[HW_CHAIN]) return;
     __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
-    const uint64_t t0 = (uint64_t)blockIdx.x * SCAN_TILE;
     uint32_t s = 0;
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
-        const uint64_t i = t0 + (uint64_t)k * SCAN_THREADS + threadIdx.x;
-        if (i < m) s += cnt[i];
+        const uint64_t j = (uint64_t)blockIdx.x * SCAN_TILE + (uint64_t)k * SCAN_THREADS + threadIdx.x;
+        if (j >= n_slots) continue;
+        const uint32_t lanes = rec[j].z;
+        const uint64_t valid = lanes >= (uint32_t)WAVE ? ~0ull : (1ull << lanes) - 1;
+        const uint2 c = claimed[j];
+        const uint64_t mx = valid & ~((uint64_t)c.x | ((uint64_t)c.y << 32));
+        const uint4 o = open[j];
+        const uint64_t mp = (uint64_t)o.x | ((uint64_t)o.y << 32);
+        open[j] = make_uint4(o.x, o.y, (uint32_t)mx, (uint32_t)(mx >> 32));
+        const uint32_t v = (uint32_t)__popcll(mp | mx);
+        cnt[j] = v;
+        s += v;
     }
     uint32_t total = 0;
     block_excl_scan(s, tmp, &total);
     if (threadIdx.x == 0) tsum[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void chain_scan_top_kernel(uint32_t *__restrict__ tsum, uint64_t tiles,
-                                                                      int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
-    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
-    uint32_t carry = 0;
-    for (uint64_t t0 = 0; t0 < tiles; t0 += SCAN_THREADS) {
-        const uint64_t i = t0 + threadIdx.x;
-        const uint32_t v = i < tiles ? tsum[i] : 0;
-        uint32_t total = 0;
-        const uint32_t e = block_excl_scan(v, tmp, &total);
-        if (i < tiles) tsum[i] = carry + e;
-        carry += total;
+// Exclusive scan of cnt[0 .. m) into out[0 .. m): every workgroup adds up the
+// tile sums itself (a few thousand words at most).  Workgroup 0 then decides
+// whether the chain path goes on: only if the anchors' prev/next reported no
+// error and the unresolved accesses fit the workspace (the layout is valid,
+// or this kernel would have been off); otherwise the reason is recorded.
+__global__ __launch_bounds__(SCAN_THREADS) void chain_scan_kernel(const uint32_t *__restrict__ cnt, uint64_t m,
+                                                                  const uint32_t *__restrict__ tsum,
+                                                                  uint32_t *__restrict__ out, int32_t *hdr,
+                                                                  const int32_t *__restrict__ anchor_hdr,
+                                                                  uint32_t m_cap) {
+    if (!hdr[HW_CHAIN]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0 && hdr[HW_BAD]) hdr[HW_REASON] = 1;
+        return;
     }
-    if (threadIdx.x == 0) hdr[HW_UNRESOLVED] = (int32_t)carry;
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void chain_scan_apply_kernel(const uint32_t *__restrict__ cnt, uint64_t m,
-                                                                        const uint32_t *__restrict__ tsum,
-                                                                        uint32_t *__restrict__ out,
-                                                                        const int32_t *__restrict__ hdr) {
-    if (hdr[HW_BAD]) return;
     __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
+    uint32_t mine = 0, all = 0;
+    for (uint32_t i = threadIdx.x; i < gridDim.x; i += SCAN_THREADS) {
+        const uint32_t v = tsum[i];
+        all += v;
+        mine += i < blockIdx.x ? v : 0u;
+    }
+    uint32_t base = 0, unresolved = 0;
+    block_excl_scan(mine, tmp, &base);
+    block_excl_scan(all, tmp, &unresolved);
     // each thread scans SCAN_ITEMS consecutive entries
     const uint64_t i0 = (uint64_t)blockIdx.x * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
     uint32_t v[SCAN_ITEMS], s = 0;
@@ -264,13 +259,18 @@ __global__ __launch_bounds__(SCAN_THREADS) void chain_scan_apply_kernel(const ui
         s += v[k];
     }
     uint32_t total = 0;
-    uint32_t run = tsum[blockIdx.x] + block_excl_scan(s, tmp, &total);
+    uint32_t run = base + block_excl_scan(s, tmp, &total);
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         if (i0 + k < m) out[i0 + k] = run;
         run += v[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[m] = (uint32_t)hdr[HW_UNRESOLVED];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const int32_t reason = anchor_hdr[0] ? 4 : unresolved > m_cap ? 2 : 0;
+        hdr[HW_UNRESOLVED] = (int32_t)unresolved;
+        hdr[HW_REASON] = reason;
+        if (reason) hdr[HW_CHAIN] = 0;
+    }
 }
 
 // The unresolved accesses, in time order, into (key, position, which sides
@@ -373,93 +373,31 @@ __global__ __launch_bounds__(CH_THREADS) void chain_merge_kernel(const uint32_t 
     if (bad) atomicOr(hdr + HW_FAIL, 1);
 }
 
-// an inner prev/next call's header: its status into ours (word 0), its
-// high-bit flag (word 1) into word `high_word` of ours; only when the inner
-// call ran (gate word of ours non-zero)
-__global__ void chain_status_kernel(const int32_t *__restrict__ nested, int32_t *__restrict__ hdr, int high_word,
-                                    int gate_word) {
-    if (threadIdx.x != 0 || !hdr[gate_word]) return;
-    if (nested[0]) atomicOr(hdr + HW_STATUS, nested[0]);
-    hdr[high_word] = nested[1];
-}
-
-// After the layout check: the chain path starts if the layout is valid.
-__global__ void chain_open_kernel(int32_t *__restrict__ hdr) {
-    if (threadIdx.x == 0) hdr[HW_CHAIN] = hdr[HW_BAD] ? 0 : 1;
-}
-
-// After the unresolved count: the chain path goes on if the layout is valid,
-// the anchors' prev/next reported no error and the unresolved accesses fit
-// the workspace; otherwise the reason is recorded.
-__global__ void chain_decide_kernel(int32_t *__restrict__ hdr, const int32_t *__restrict__ anchor_hdr,
-                                    uint32_t m_cap) {
-    if (threadIdx.x != 0) return;
-    int32_t reason = 0;
-    if (hdr[HW_BAD]) reason = 1;
-    else if (anchor_hdr[0]) reason = 4;
-    else if ((uint32_t)hdr[HW_UNRESOLVED] > m_cap) reason = 2;
-    hdr[HW_REASON] = reason;
-    hdr[HW_CHAIN] = reason == 0 ? 1 : 0;
-}
-
-// After the merge: the generic prev/next over all keys runs (HW_PATH = 1)
-// if the chain path stopped, the inner prev/next reported an error or the
-// merge check failed.
-__global__ void chain_verdict_kernel(int32_t *__restrict__ hdr, const int32_t *__restrict__ inner_hdr) {
-    if (threadIdx.x != 0) return;
-    int32_t reason = hdr[HW_REASON];
-    if (reason == 0 && inner_hdr[0]) reason = 4;
-    if (reason == 0 && hdr[HW_FAIL]) reason = 3;
-    hdr[HW_REASON] = reason;
-    hdr[HW_PATH] = reason != 0 ? 1 : 0;
-}
-
 struct ChainWs {
     int32_t *hdr;
-    void *generic;        // pc_prev_next_use workspace over all keys (also the unresolved stage's space)
-    size_t generic_bytes;
+    // control blocks of the three generic prev/next: over all keys, over the
+    // anchor slots, over the unresolved accesses
+    SortCtl all, anchors, rest;
+    void *generic;        // buffers over all keys (also the unresolved stage's space)
+    uint64_t m_cap;       // the most unresolved accesses they hold
     uint64_t *akeys;
     uint4 *rec;
     uint4 *open;
     uint2 *claimed;
     uint32_t *aprev, *anext, *cnt, *coff, *tsum;
-    void *aws;            // pc_prev_next_use workspace over the slots
-    size_t aws_bytes;
+    void *abufs;          // buffers over the slots
     size_t bytes;
 };
 
 static uint64_t chain_slots(uint64_t n, uint32_t n_seqs) { return n / CH_S + n_seqs + 1; }
 
-static ChainWs carve_chain(void *ws, uint64_t n, uint32_t n_seqs) {
-    Carver c{(char *)ws, 0};
-    ChainWs w;
-    const uint64_t ns = chain_slots(n, n_seqs);
-    w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
-    w.generic_bytes = pc_prev_next_use_ws(n);
-    w.generic = c.take<char>(w.generic_bytes);
-    w.akeys = c.take<uint64_t>(ns);
-    w.rec = c.take<uint4>(ns);
-    w.open = c.take<uint4>(ns);
-    w.claimed = c.take<uint2>(ns);
-    w.aprev = c.take<uint32_t>(ns);
-    w.anext = c.take<uint32_t>(ns);
-    w.cnt = c.take<uint32_t>(ns);
-    w.coff = c.take<uint32_t>(ns + 1);
-    w.tsum = c.take<uint32_t>((ns + SCAN_TILE - 1) / SCAN_TILE + 1);
-    w.aws_bytes = pc_prev_next_use_ws(ns);
-    w.aws = c.take<char>(w.aws_bytes);
-    w.bytes = c.off;
-    return w;
-}
-
-// The unresolved stage's arrays inside the generic workspace (unused until a
-// fallback); false if they do not fit.
+// The unresolved stage's arrays inside the generic buffers (unused until a
+// fallback).
 struct OpenWs {
     uint64_t *ckeys;
     uint32_t *cpos, *cprev, *cnext;
     uint8_t *cflag;
-    void *ws;
-    size_t ws_bytes;
+    void *bufs;
 };
 static size_t carve_open(void *base, uint64_t m, OpenWs *o) {
     Carver c{(char *)base, 0};
@@ -468,21 +406,52 @@ static size_t carve_open(void *base, uint64_t m, OpenWs *o) {
     o->cprev = c.take<uint32_t>(m);
     o->cnext = c.take<uint32_t>(m);
     o->cflag = c.take<uint8_t>(m);
-    o->ws_bytes = pc_prev_next_use_ws(m);
-    o->ws = c.take<char>(o->ws_bytes);
+    o->bufs = c.take<char>(sort_bufs_bytes(m));
     return c.off;
 }
 
-// the most unresolved accesses the generic workspace holds (at most n)
-static uint64_t open_capacity(const ChainWs &w, uint64_t n) {
+// the most unresolved accesses the generic buffers over n keys hold (at most n)
+static uint64_t open_capacity(uint64_t n) {
     OpenWs o;
+    const size_t bytes = sort_bufs_bytes(n);
     uint64_t lo = 0, hi = n;
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo + 1) / 2;
-        if (carve_open(nullptr, mid, &o) <= w.generic_bytes) lo = mid;
+        if (carve_open(nullptr, mid, &o) <= bytes) lo = mid;
         else hi = mid - 1;
     }
     return lo;
+}
+
+static SortCtl take_sort_ctl(Carver &c, uint64_t n) {
+    size_t bytes;
+    sort_ctl(nullptr, n, &bytes);
+    char *at = c.take<char>(bytes);
+    return sort_ctl(at, n, &bytes);
+}
+
+static ChainWs carve_chain(void *ws, uint64_t n, uint32_t n_seqs) {
+    Carver c{(char *)ws, 0};
+    ChainWs w;
+    const uint64_t ns = chain_slots(n, n_seqs);
+    w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
+    w.all = take_sort_ctl(c, n);
+    w.anchors = take_sort_ctl(c, ns);
+    w.m_cap = open_capacity(n);
+    w.rest = take_sort_ctl(c, w.m_cap);
+    w.generic = c.take<char>(sort_bufs_bytes(n));
+    w.akeys = c.take<uint64_t>(ns);
+    w.rec = c.take<uint4>(ns);
+    w.open = c.take<uint4>(ns);
+    w.claimed = c.take<uint2>(ns);
+    w.aprev = c.take<uint32_t>(ns);
+    w.anext = c.take<uint32_t>(ns);
+    w.cnt = c.take<uint32_t>(ns);
+    w.coff = c.take<uint32_t>(ns);
+    w.tsum = c.take<uint32_t>((ns + SCAN_TILE - 1) / SCAN_TILE + 1);
+    w.abufs = c.take<char>(sort_bufs_bytes(ns));
+    w.bytes = c.off;
+    return w;
 }
 
 static unsigned wave_grid(uint64_t items, int cus) {
@@ -509,43 +478,42 @@ pc_status pc_prev_next_chained(const uint64_t *keys, uint64_t n, const uint64_t 
     if (ws_bytes < pc_prev_next_chained_ws(n, n_seqs)) return PC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const ChainWs w = carve_chain(ws, n, n_seqs);
-    pc_status st = fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, HW_WORDS, s);
-    if (st != PC_OK || n == 0) return st;
+    pc_status st;
+    if (n == 0) return fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, HW_WORDS, s);
     const int deepest = (flags & PC_HASH_DEEPEST_FIRST) ? 1 : 0;
     const int want_next = (flags & PC_PREV_ONLY) ? 0 : 1;
     const int cus = device_cus();
+    const SortReport all_report{w.hdr, HW_HIGH_ANCHOR};
 
-    // the generic prev/next over all keys, gated on `gate` (nullptr: always)
-    auto generic = [&](const int32_t *gate) -> pc_status {
-        pc_status g = prev_next_core(keys, n, nullptr, prev, next, key_hist, w.generic, s, gate, gate != nullptr);
-        if (g != PC_OK) return g;
-        PC_LAUNCH(K_FILL32, chain_status_kernel, dim3(1), dim3(64), 0, s, (const int32_t *)w.generic, w.hdr,
-                  HW_HIGH_ANCHOR, HW_PATH);
-        return PC_OK;
-    };
     if (n_seqs == 0) {   // n > 0 accesses in no request: an invalid layout
-        if ((st = fill_u32(reinterpret_cast<uint32_t *>(w.hdr + HW_STATUS), (uint32_t)DEV_ERR_BAD_LAYOUT, 1, s)) !=
-                PC_OK ||
-            (st = fill_u32(reinterpret_cast<uint32_t *>(w.hdr + HW_PATH), 1u, 1, s)) != PC_OK ||
-            (st = fill_u32(reinterpret_cast<uint32_t *>(w.hdr + HW_REASON), 1u, 1, s)) != PC_OK)
-            return st;
-        return generic(nullptr);
+        Fills f;
+        f.add(w.hdr, (uint32_t)DEV_ERR_BAD_LAYOUT, 1);
+        f.add(w.hdr + HW_PATH, 1u, 1);
+        f.add(w.hdr + HW_UNRESOLVED, 0u, 1);
+        f.add(w.hdr + HW_REASON, 1u, 1);
+        f.add(w.hdr + HW_REASON + 1, 0u, HW_WORDS - HW_REASON - 1);
+        if ((st = fill_all(f, s)) != PC_OK) return st;
+        return prev_next_core(keys, n, nullptr, prev, next, key_hist, w.all, w.generic, s, nullptr, all_report);
     }
 
     // Every decision below is taken on the device: later launches are gated
     // on header words, so the call never waits for the GPU.
     const uint64_t ns = chain_slots(n, n_seqs);
     const int32_t *chain = w.hdr + HW_CHAIN;
-    PC_LAUNCH(K_CHAIN_ANCHOR, chain_layout_kernel, dim3((unsigned)((n_seqs + 255) / 256)), dim3(256), 0, s,
-              blk_off, n_seqs, n, w.hdr);
-    PC_LAUNCH(K_CHAIN_ANCHOR, chain_open_kernel, dim3(1), dim3(64), 0, s, w.hdr);
+    {
+        Fills f;
+        f.add(w.hdr, 0u, HW_CHAIN);
+        f.add(w.hdr + HW_CHAIN, 1u, 1);
+        f.add(w.hdr + HW_CHAIN + 1, 0u, HW_WORDS - HW_CHAIN - 1);
+        f.add(w.claimed, 0u, 2 * ns);
+        sort_ctl_clear(f, w.all);
+        if ((st = fill_all(f, s)) != PC_OK) return st;
+    }
     PC_LAUNCH(K_CHAIN_ANCHOR, chain_anchor_kernel, dim3(wave_grid(n_seqs, cus)), dim3(CH_THREADS), 0, s, keys,
-              blk_off, n_seqs, ns, deepest, w.akeys, w.rec, (const int32_t *)w.hdr);
-    if ((st = prev_next_core(w.akeys, ns, nullptr, w.aprev, w.anext, nullptr, w.aws, s, chain, false)) != PC_OK)
+              blk_off, n_seqs, n, ns, deepest, w.akeys, w.rec, w.hdr);
+    if ((st = prev_next_core(w.akeys, ns, nullptr, w.aprev, w.anext, nullptr, w.anchors, w.abufs, s, chain,
+                             SortReport{w.hdr, HW_HIGH_ANCHOR})) != PC_OK)
         return st;
-    PC_LAUNCH(K_FILL32, chain_status_kernel, dim3(1), dim3(64), 0, s, (const int32_t *)w.aws, w.hdr, HW_HIGH_ANCHOR,
-              HW_CHAIN);
-    if ((st = fill_u32_gated(reinterpret_cast<uint32_t *>(w.claimed), 0u, 2 * ns, s, chain)) != PC_OK) return st;
     const int batch = stair_batch(n);
     const dim3 stair_grid(wave_grid((ns + batch - 1) / batch, cus));
     if (batch == 16)
@@ -560,39 +528,40 @@ pc_status pc_prev_next_chained(const uint64_t *keys, uint64_t n, const uint64_t 
         PC_LAUNCH(K_CHAIN_STAIR, chain_stair_kernel<2>, stair_grid, dim3(CH_THREADS), 0, s, keys, ns,
                   (const uint4 *)w.rec, w.aprev, deepest, prev, next, want_next, w.open, w.claimed,
                   (const int32_t *)w.hdr);
-    PC_LAUNCH(K_CHAIN_SCAN, chain_count_kernel, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, s, ns,
-              (const uint4 *)w.rec, (const uint2 *)w.claimed, w.open, w.cnt, (const int32_t *)w.hdr);
     const uint64_t tiles = (ns + SCAN_TILE - 1) / SCAN_TILE;
-    PC_LAUNCH(K_CHAIN_SCAN, chain_scan_tiles_kernel, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, w.cnt, ns,
-              w.tsum, (const int32_t *)w.hdr);
-    PC_LAUNCH(K_CHAIN_SCAN, chain_scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, w.tsum, tiles, w.hdr);
-    PC_LAUNCH(K_CHAIN_SCAN, chain_scan_apply_kernel, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, w.cnt, ns,
-              w.tsum, w.coff, (const int32_t *)w.hdr);
+    PC_LAUNCH(K_CHAIN_SCAN, chain_count_kernel, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s, ns,
+              (const uint4 *)w.rec, (const uint2 *)w.claimed, w.open, w.cnt, w.tsum, (const int32_t *)w.hdr);
 
     // the unresolved accesses: compacted, their own prev/next (over the
     // count the scan wrote, sized for the most that fit), merged back
-    const uint64_t m_cap = open_capacity(w, n);
+    const uint64_t m_cap = w.m_cap;
     OpenWs o;
     carve_open(w.generic, m_cap, &o);
-    PC_LAUNCH(K_CHAIN_SCAN, chain_decide_kernel, dim3(1), dim3(64), 0, s, w.hdr, (const int32_t *)w.aws,
+    PC_LAUNCH(K_CHAIN_SCAN, chain_scan_kernel, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s,
+              (const uint32_t *)w.cnt, ns, (const uint32_t *)w.tsum, w.coff, w.hdr, (const int32_t *)w.anchors.hdr,
               (uint32_t)m_cap);
     PC_LAUNCH(K_CHAIN_COMPACT, chain_compact_kernel, dim3(wave_grid((ns + WAVE - 1) / WAVE, cus)),
               dim3(CH_THREADS), 0, s, keys, ns, (const uint4 *)w.rec, (const uint4 *)w.open, w.coff, deepest,
               o.ckeys, o.cpos, o.cflag, (const int32_t *)w.hdr);
     const uint32_t *m_dev = reinterpret_cast<const uint32_t *>(w.hdr + HW_UNRESOLVED);
-    if ((st = prev_next_core(o.ckeys, m_cap, m_dev, o.cprev, o.cnext, nullptr, o.ws, s, chain, false)) != PC_OK)
+    if ((st = prev_next_core(o.ckeys, m_cap, m_dev, o.cprev, o.cnext, nullptr, w.rest, o.bufs, s, chain,
+                             SortReport{w.hdr, HW_HIGH_UNRESOLVED})) != PC_OK)
         return st;
-    PC_LAUNCH(K_FILL32, chain_status_kernel, dim3(1), dim3(64), 0, s, (const int32_t *)o.ws, w.hdr,
-              HW_HIGH_UNRESOLVED, HW_CHAIN);
     uint64_t mg = (m_cap + CH_THREADS - 1) / CH_THREADS;
     if (mg > (uint64_t)cus * 16) mg = (uint64_t)cus * 16;
     PC_LAUNCH(K_CHAIN_MERGE, chain_merge_kernel, dim3((unsigned)(mg ? mg : 1)), dim3(CH_THREADS), 0, s, o.cpos,
               o.cflag, o.cprev, o.cnext, prev, next, want_next, w.hdr);
-
-    // the check's verdict; the generic path over all keys runs only if it
-    // (or an earlier step) says so
-    PC_LAUNCH(K_CHAIN_MERGE, chain_verdict_kernel, dim3(1), dim3(64), 0, s, w.hdr, (const int32_t *)o.ws);
-    return generic(w.hdr + HW_PATH);
+    // The generic prev/next over all keys runs (HW_PATH = 1) if the chain path
+    // stopped, the inner prev/next reported an error or a check failed.
+    RareGate rare;
+    rare.good = chain;
+    rare.error = w.rest.hdr;
+    rare.error_reason = 4;
+    rare.fail = w.hdr + HW_FAIL;
+    rare.fail_reason = 3;
+    rare.reason = w.hdr + HW_REASON;
+    rare.on = w.hdr + HW_PATH;
+    return prev_next_rare(keys, n, prev, next, key_hist, w.all, w.generic, s, rare, all_report);
 }
 
 }  // extern "C"

@@ -42,7 +42,7 @@ enum KernelId {
     K_FILL32 = 0,
     K_HASH,
     K_SORT_HIST,
-    K_SORT_SCAN,
+    K_SORT_HIGH,
     K_SORT_PASS,
     K_LINK,
     K_PERM,
@@ -55,7 +55,6 @@ enum KernelId {
     K_SD_PASS,
     K_SD_LOCAL,
     K_MRC_HIST,
-    K_MRC_COST,
     K_REQ_ORDER,
     K_REQ_DIST,
     K_SESS_REQ,
@@ -119,25 +118,63 @@ struct Fills {
     }
 };
 pc_status fill_all(const Fills &f, hipStream_t s, const int32_t *gate = nullptr);
+unsigned fill_blocks(const Fills &f);   // 256-thread blocks of a launch that fills them
 
 // Gates: a launch given a device word runs only when the word is non-zero
 // (nullptr: always), so a path chosen on the device needs no read-back.
-pc_status fill_u32_gated(uint32_t *p, uint32_t value, size_t count, hipStream_t s, const int32_t *gate);
 
-// pc_stack_distance with every launch gated; workspace as
-// pc_stack_distance_ws(n)
-pc_status stack_distance_gated(const uint32_t *prev, const uint32_t *next, uint64_t n, uint32_t *dist, void *ws,
-                               hipStream_t s, const int32_t *gate);
+// pc_stack_distance gated, for a call whose gate is seldom on (one launch for
+// small n); workspace as pc_stack_distance_ws(n), control words cleared by an
+// earlier launch, errors or'ed into *status
+constexpr int SD_CTL_WORDS = 64;
+pc_status stack_distance_rare(const uint32_t *prev, const uint32_t *next, uint64_t n, uint32_t *dist, void *ws,
+                              uint32_t *ctl, hipStream_t s, const int32_t *gate, int32_t *status);
 
-// pc_prev_next_use over min(n, *n_dev) keys (n_dev: a count the GPU wrote;
-// nullptr: n), grids and workspace sized for n (pc_prev_next_use_ws(n)),
-// every launch gated; `rare`: a call whose gate is seldom on takes small
-// persistent grids (cheap when off, slower when on)
+// Prev/next over min(n, *n_dev) keys (n_dev: a count the GPU wrote; nullptr:
+// n), n > 0, grids and buffers sized for n, every launch gated.  `k` is the
+// call's control block (status in header word 0, "the high key bits were
+// sorted too" in word 1), `bufs` its buffers (sort_bufs_bytes(n)).  When the
+// call runs, the last launch adds the status to report.hdr[0] and copies word
+// 1 to report.hdr[high_word] (if report.hdr is given).
+struct SortCtl {
+    int32_t *hdr;
+    uint32_t *start, *hist, *words, *link2, *cursor[4];
+    size_t zero_words;   // from hist on
+};
+struct SortReport {
+    int32_t *hdr = nullptr;
+    int high_word = 0;
+};
+SortCtl sort_ctl(void *at, uint64_t n, size_t *bytes);
+void sort_ctl_clear(Fills &f, const SortCtl &k);
+size_t sort_bufs_bytes(uint64_t n);
 pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev, uint32_t *prev, uint32_t *next,
-                         const uint32_t *key_hist, void *ws, hipStream_t s, const int32_t *gate, bool rare);
+                         const uint32_t *key_hist, const SortCtl &k, void *bufs, hipStream_t s, const int32_t *gate,
+                         const SortReport &report);
+// The same for a path that is seldom taken (two launches for small n): it runs if the
+// path it stands behind stopped (*good is 0, *reason says why), or if that one
+// reported an error or a failed check; then *reason is set and *on becomes 1
+// (0 before).  The control block must have been cleared (sort_ctl_clear) by an
+// earlier launch.
+struct RareGate {
+    const int32_t *good = nullptr, *error = nullptr, *fail = nullptr;
+    int32_t error_reason = 0, fail_reason = 0;
+    int32_t *reason = nullptr, *on = nullptr;
+};
+pc_status prev_next_rare(const uint64_t *keys, uint64_t n, uint32_t *prev, uint32_t *next, const uint32_t *key_hist,
+                         const SortCtl &k, void *bufs, hipStream_t s, const RareGate &rare, const SortReport &report);
 
 // ------------------------------------------------------------ device helpers
 __device__ __forceinline__ bool gated_off(const int32_t *gate) { return gate && *gate == 0; }
+__device__ __forceinline__ void fill_segments(const Fills &f) {
+    const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int a = 0; a < f.n; ++a) {
+        uint32_t *p = f.p[a];
+        const uint32_t v = f.value[a];
+        const size_t n = f.count[a];
+        for (size_t i = first; i < n; i += stride) p[i] = v;
+    }
+}
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
     const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src, WAVE);
     const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(v >> 32), src, WAVE);
@@ -178,6 +215,41 @@ __device__ __forceinline__ uint64_t ld_status64(const uint64_t *p) {
 }
 __device__ __forceinline__ void st_status64(uint64_t *p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every device-scope atomic this wave has issued has been performed (they act
+// where all XCDs see them, so a ticket taken afterwards publishes them without
+// the cache write-back of a fence).
+__device__ __forceinline__ void atomics_performed() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The end of one phase of a persistent kernel: this workgroup's `mine` chunks
+// are written; waits until `all` chunks of the phase are (*done counts them).
+// Every wave waits for its own stores, then one wave writes the L2 back and,
+// after the wait, drops what the caches hold of other XCDs' data (a fence in
+// every wave of every workgroup took 100 us and more a phase).  The polls are
+// far apart, for they queue up with the counts at one address.  Only
+// workgroups that run hold chunks, so the wait ends; it is bounded all the
+// same.
+constexpr uint32_t PHASE_SPIN_LIMIT = 1u << 24;
+__device__ __forceinline__ void finish_phase(uint32_t *done, uint32_t mine, uint32_t all, int32_t *err) {
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x < WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (threadIdx.x == 0) {
+            if (mine) atomicAdd(done, mine);
+            uint32_t spins = 0;
+            while (ld_status(done) < all) {
+                if (++spins > PHASE_SPIN_LIMIT) {
+                    atomicOr(err, DEV_ERR_LOOKBACK_TIMEOUT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(32);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave with DPP: four row

@@ -17,8 +17,8 @@
 // 64-bit atomics.  Up to 1024 edges sit in LDS at once; more are taken 1024
 // at a time, one launch each, a launch counting only the accesses that fall
 // between its edges.  Integer atomics make the result independent of
-// scheduling order.  A last tiny kernel forms alpha*count + beta*depthsum
-// exactly as 128-bit integers.
+// scheduling order.  The last workgroup to finish forms alpha*count +
+// beta*depthsum exactly as 128-bit integers.
 //
 // pc_mrc_weighted_layout takes the depths from the request layout instead
 // of an array: depth(t) = t - (start of t's request).  A map kernel writes a
@@ -92,8 +92,9 @@ __global__ __launch_bounds__(MRC_THREADS) void mrc_hist_kernel(
     const uint32_t *__restrict__ dist, const uint32_t *__restrict__ depth,
     const uint32_t *__restrict__ gstart, const uint8_t *__restrict__ startbits,
     const uint32_t *__restrict__ next, uint64_t n, const uint64_t *__restrict__ caps, uint32_t n_caps,
-    uint32_t k0, uint32_t Kc, uint64_t *__restrict__ count, uint64_t *__restrict__ depthsum,
-    uint64_t *__restrict__ nexthist, int desc, int32_t *__restrict__ err) {
+    uint32_t k0, uint32_t Kc, uint64_t *count, uint64_t *depthsum, uint64_t *__restrict__ nexthist, int desc,
+    int32_t *__restrict__ err, uint32_t *__restrict__ ticket, uint64_t alpha, uint64_t beta,
+    uint64_t *__restrict__ cost_lo, uint64_t *__restrict__ cost_hi) {
     extern __shared__ uint64_t smem[];
     const uint32_t K = Kc;
     uint64_t *s_ds = smem;                    // K+2
@@ -220,6 +221,23 @@ __global__ __launch_bounds__(MRC_THREADS) void mrc_hist_kernel(
         if (next && s_nh[i])
             atomicAdd(reinterpret_cast<unsigned long long *>(&nexthist[k0 + i]), (unsigned long long)s_nh[i]);
     }
+    // the last workgroup of the last launch: cost = alpha*count +
+    // beta*depthsum as a 128-bit integer (hi:lo), mod 2^128
+    if (!last) return;
+    __shared__ uint32_t s_last;
+    atomics_performed();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    for (uint32_t i = threadIdx.x; i <= n_caps; i += blockDim.x) {
+        const uint64_t c = ld_status64(&count[i]), d = ld_status64(&depthsum[i]);
+        const uint64_t a_lo = alpha * c, a_hi = __umul64hi(alpha, c);
+        const uint64_t b_lo = beta * d, b_hi = __umul64hi(beta, d);
+        const uint64_t s = a_lo + b_lo;
+        cost_lo[i] = s;
+        cost_hi[i] = a_hi + b_hi + (s < a_lo ? 1ull : 0ull);
+    }
 }
 
 // The layout map, one thread per request: bit t of startbits set when a
@@ -256,21 +274,6 @@ __global__ __launch_bounds__(256) void mrc_map_kernel(const uint64_t *__restrict
         }
     }
 }
-
-// cost = alpha*count + beta*depthsum as a 128-bit integer (hi:lo), mod 2^128
-__global__ void mrc_cost_kernel(const uint64_t *__restrict__ count, const uint64_t *__restrict__ depthsum,
-                                uint32_t bins, uint64_t alpha, uint64_t beta, uint64_t *__restrict__ lo,
-                                uint64_t *__restrict__ hi) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= bins) return;
-    const uint64_t c = count[i], d = depthsum[i];
-    const uint64_t a_lo = alpha * c, a_hi = __umul64hi(alpha, c);
-    const uint64_t b_lo = beta * d, b_hi = __umul64hi(beta, d);
-    const uint64_t s = a_lo + b_lo;
-    lo[i] = s;
-    hi[i] = a_hi + b_hi + (s < a_lo ? 1ull : 0ull);
-}
-
 
 // workspace of pc_mrc_weighted_layout: the header, gstart (one word per 64
 // positions) and the start bitmap (one bit per position, whole 64-bit words)
@@ -310,24 +313,27 @@ static pc_status mrc_run(const uint32_t *dist, const uint32_t *depth, const uint
     int32_t *hdr = reinterpret_cast<int32_t *>(ws);
     const uint32_t bins = n_caps + 1;
     pc_status st;
-    if ((st = fill_u32(reinterpret_cast<uint32_t *>(hdr), 0u, 1, s)) != PC_OK) return st;
-    if ((st = fill_u32(reinterpret_cast<uint32_t *>(count), 0u, 2 * (size_t)bins, s)) != PC_OK) return st;
-    if ((st = fill_u32(reinterpret_cast<uint32_t *>(depthsum), 0u, 2 * (size_t)bins, s)) != PC_OK) return st;
-    if (nextuse_hist && (st = fill_u32(reinterpret_cast<uint32_t *>(nextuse_hist), 0u, 2 * (size_t)bins, s)) != PC_OK)
-        return st;
-
     const int cus = device_cus();
     const bool layout = blk_off != nullptr;
     const MrcLayoutWs lw = mrc_layout_carve(ws, n);
-    if (layout && n > 0) {
-        if (n_seqs == 0) return fill_u32(reinterpret_cast<uint32_t *>(hdr), (uint32_t)DEV_ERR_BAD_LAYOUT, 1, s);
-        if ((st = fill_u32(lw.startbits, 0u, 2 * ((n + 63) / 64), s)) != PC_OK) return st;
+    // one launch clears the status, the ticket (header word 1), the outputs and
+    // the layout's bitmap
+    const bool empty_layout = layout && n > 0 && n_seqs == 0;
+    Fills f;
+    f.add(hdr, empty_layout ? (uint32_t)DEV_ERR_BAD_LAYOUT : 0u, 1);
+    f.add(hdr + 1, 0u, 1);
+    f.add(count, 0u, 2 * (size_t)bins);
+    f.add(depthsum, 0u, 2 * (size_t)bins);
+    if (nextuse_hist) f.add(nextuse_hist, 0u, 2 * (size_t)bins);
+    if (layout && n > 0) f.add(lw.startbits, 0u, 2 * ((n + 63) / 64));
+    if ((st = fill_all(f, s)) != PC_OK || empty_layout) return st;
+    if (layout && n > 0)
         PC_LAUNCH(K_MRC_MAP, mrc_map_kernel, dim3((unsigned)(((uint64_t)n_seqs + 255) / 256)), dim3(256), 0, s,
                   blk_off, n_seqs, n, desc, lw.gstart, lw.startbits, hdr);
-    }
     const uint32_t *gs = layout ? lw.gstart : nullptr;
     const uint8_t *sb = layout ? reinterpret_cast<const uint8_t *>(lw.startbits) : nullptr;
     const uint64_t per = layout ? mrc_per<true>() : mrc_per<false>();
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(hdr + 1);
     uint64_t grid = (n + MRC_THREADS * per - 1) / (MRC_THREADS * per);
     // up to 64 workgroups per CU: eight resident (32 registers of loads per
     // lane keep eight waves per SIMD) and the rest queued behind them, which
@@ -340,19 +346,21 @@ static pc_status mrc_run(const uint32_t *dist, const uint32_t *depth, const uint
         const bool chunked = n_caps > MRC_EDGES;
         if (!chunked && !layout)
             PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, false>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
-                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr);
+                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
+                      ticket, alpha, beta, cost_lo, cost_hi);
         else if (!chunked)
             PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, true>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
-                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr);
+                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
+                      ticket, alpha, beta, cost_lo, cost_hi);
         else if (!layout)
             PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, false>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
-                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr);
+                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
+                      ticket, alpha, beta, cost_lo, cost_hi);
         else
             PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, true>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
-                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr);
+                      s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
+                      ticket, alpha, beta, cost_lo, cost_hi);
     }
-    PC_LAUNCH(K_MRC_COST, mrc_cost_kernel, dim3((bins + 255) / 256), dim3(256), 0, s, count, depthsum, bins, alpha,
-              beta, cost_lo, cost_hi);
     return PC_OK;
 }
 

@@ -26,12 +26,12 @@
 // merged prefix sums follow from the two blocks' own.
 //
 // Passes: count heads and cold accesses per 4096-position tile, keeping
-// three bits per position (head, cold, last of a run); scan; read the number
-// of runs back (the call synchronises once); compact the runs from those
-// bits (head's prev, head position, end position, cold count before the
-// head); merge levels; write D from the run list.  prev is streamed once.  With
-// more runs than 1/16 of the accesses plus 1024 the call runs
-// pc_stack_distance instead.
+// three bits per position (head, cold, last of a run); scan, and decide on the
+// device; compact the runs from those bits (head's prev, head position, end
+// position, cold count before the head); merge the runs of each block of 2048
+// in LDS, then eight blocks a launch; write D from the run list.  prev is
+// streamed once.  With more runs than 1/16 of the accesses plus 1024 the
+// dominance count of pc_stack_distance runs instead.
 #include "pc_internal.h"
 
 namespace pc {
@@ -125,8 +125,12 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_count_kernel(const uint32_t 
     if (threadIdx.x == 0) counts[blockIdx.x] = make_uint2(th, tc);
 }
 
-// Exclusive scan of the per-tile (heads, cold) pairs: tile sums, one
-// workgroup over them (writing the totals to the header), tiles again.
+// Exclusive scan of the per-tile (heads, cold) pairs: sums of RSCAN_TILE
+// tiles (only when there are more than that), then every workgroup adds the
+// sums before its own and scans its tiles.  Workgroup 0 writes the header,
+// the path included: over runs, or the dominance count over accesses when
+// there are more runs than the workspace holds (rmax); and clears the control
+// words of the latter.
 __global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_tiles_kernel(const uint2 *__restrict__ c, uint64_t m,
                                                                         uint2 *__restrict__ tsum) {
     __shared__ uint32_t tmp[RSCAN_THREADS / WAVE];
@@ -146,30 +150,27 @@ __global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_tiles_kernel(const ui
     if (threadIdx.x == 0) tsum[blockIdx.x] = make_uint2(ta, tb);
 }
 
-__global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_top_kernel(uint2 *__restrict__ tsum, uint64_t tiles,
-                                                                      int32_t *__restrict__ hdr) {
+__global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_kernel(const uint2 *__restrict__ c, uint64_t m,
+                                                                  const uint2 *__restrict__ tsum,
+                                                                  uint2 *__restrict__ out, uint64_t rmax,
+                                                                  int32_t *__restrict__ hdr, uint32_t *__restrict__ ctl,
+                                                                  uint32_t ctl_words) {
     __shared__ uint32_t tmp[RSCAN_THREADS / WAVE];
-    uint32_t ca = 0, cb = 0;
-    for (uint64_t t0 = 0; t0 < tiles; t0 += RSCAN_THREADS) {
-        const uint64_t i = t0 + threadIdx.x;
-        const uint2 v = i < tiles ? tsum[i] : make_uint2(0u, 0u);
-        uint32_t ta = 0, tb = 0;
-        const uint32_t ea = block_excl_scan(v.x, tmp, &ta);
-        const uint32_t eb = block_excl_scan(v.y, tmp, &tb);
-        if (i < tiles) tsum[i] = make_uint2(ca + ea, cb + eb);
-        ca += ta;
-        cb += tb;
+    uint32_t ma = 0, mb = 0, aa = 0, ab = 0;   // before this workgroup, and in all
+    if (gridDim.x > 1) {
+        for (uint32_t i = threadIdx.x; i < gridDim.x; i += RSCAN_THREADS) {
+            const uint2 v = tsum[i];
+            aa += v.x;
+            ab += v.y;
+            ma += i < blockIdx.x ? v.x : 0u;
+            mb += i < blockIdx.x ? v.y : 0u;
+        }
     }
-    if (threadIdx.x == 0) {
-        hdr[RW_RUNS] = (int32_t)ca;
-        hdr[RW_COLD] = (int32_t)cb;
-    }
-}
-
-__global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_apply_kernel(const uint2 *__restrict__ c, uint64_t m,
-                                                                        const uint2 *__restrict__ tsum,
-                                                                        uint2 *__restrict__ out) {
-    __shared__ uint32_t tmp[RSCAN_THREADS / WAVE];
+    uint32_t ba = 0, bb = 0, runs = 0, cold = 0;
+    block_excl_scan(ma, tmp, &ba);
+    block_excl_scan(mb, tmp, &bb);
+    block_excl_scan(aa, tmp, &runs);
+    block_excl_scan(ab, tmp, &cold);
     const uint64_t i0 = (uint64_t)blockIdx.x * RSCAN_TILE + (uint64_t)threadIdx.x * 4;
     uint2 v[4];
     uint32_t a = 0, b = 0;
@@ -180,14 +181,28 @@ __global__ __launch_bounds__(RSCAN_THREADS) void runs_scan_apply_kernel(const ui
         b += v[k].y;
     }
     uint32_t ta = 0, tb = 0;
-    uint32_t ra = tsum[blockIdx.x].x + block_excl_scan(a, tmp, &ta);
-    uint32_t rb = tsum[blockIdx.x].y + block_excl_scan(b, tmp, &tb);
+    uint32_t ra = ba + block_excl_scan(a, tmp, &ta);
+    uint32_t rb = bb + block_excl_scan(b, tmp, &tb);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         if (i0 + k < m) out[i0 + k] = make_uint2(ra, rb);
         ra += v[k].x;
         rb += v[k].y;
     }
+    if (blockIdx.x != 0) return;
+    if (gridDim.x == 1) {
+        runs = ta;
+        cold = tb;
+    }
+    if (threadIdx.x == 0) {
+        const bool over = runs > rmax;
+        hdr[RW_STATUS] = 0;
+        hdr[RW_PATH] = over ? 1 : 0;
+        hdr[RW_RUNS] = (int32_t)runs;
+        hdr[RW_COLD] = (int32_t)cold;
+        hdr[RW_RUNS_OK] = over ? 0 : 1;
+    }
+    for (uint32_t i = threadIdx.x; i < ctl_words; i += RSCAN_THREADS) ctl[i] = 0;
 }
 
 // Per run s (in time order): p[s] = prev(head), h[s] = head position,
@@ -228,24 +243,76 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_compact_kernel(const uint32_
     }
 }
 
-// Level 0: keys p, weights len = e - h + 1 as one-element prefix sums.
-__global__ __launch_bounds__(256) void runs_init_kernel(const uint32_t *__restrict__ rp, const uint32_t *__restrict__ rh,
-                                                        const uint32_t *__restrict__ re,
-                                                        uint32_t *__restrict__ key, uint32_t *__restrict__ pre,
-                                                        uint32_t *__restrict__ idx, uint32_t *__restrict__ acc,
-                                                        const int32_t *__restrict__ hdr) {
+// The first levels of the merge: each workgroup sorts BLOCK_RUNS consecutive
+// runs by p in LDS, bottom up, with the inclusive prefix sums of their lengths
+// and each run's sum over the earlier runs of the block with a smaller p.
+constexpr int BLOCK_THREADS = 1024;
+constexpr int BLOCK_ITEMS = 2;
+constexpr int BLOCK_RUNS = BLOCK_THREADS * BLOCK_ITEMS;
+constexpr int BLOCK_LEVELS = 11;
+static_assert(BLOCK_RUNS == 1 << BLOCK_LEVELS, "a block is a whole number of levels");
+__global__ __launch_bounds__(BLOCK_THREADS) void runs_block_kernel(
+    const uint32_t *__restrict__ rp, const uint32_t *__restrict__ rh, const uint32_t *__restrict__ re,
+    uint32_t *__restrict__ key, uint32_t *__restrict__ pre, uint32_t *__restrict__ idx, uint32_t *__restrict__ acc,
+    const int32_t *__restrict__ hdr) {
     if (!hdr[RW_RUNS_OK]) return;
+    __shared__ uint32_t s_key[2][BLOCK_RUNS], s_pre[2][BLOCK_RUNS], s_acc[BLOCK_RUNS];
+    __shared__ uint16_t s_idx[2][BLOCK_RUNS];
     const uint64_t r = runs_of(hdr);
-    for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < r; s += (uint64_t)gridDim.x * blockDim.x) {
-        key[s] = rp[s];
-        pre[s] = re[s] - rh[s] + 1;
-        idx[s] = (uint32_t)s;
-        acc[s] = 0;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * BLOCK_RUNS; b0 < r; b0 += (uint64_t)gridDim.x * BLOCK_RUNS) {
+        const int m = r - b0 < (uint64_t)BLOCK_RUNS ? (int)(r - b0) : BLOCK_RUNS;
+        for (int i = threadIdx.x; i < m; i += BLOCK_THREADS) {
+            s_key[0][i] = rp[b0 + i];
+            s_pre[0][i] = re[b0 + i] - rh[b0 + i] + 1;
+            s_idx[0][i] = (uint16_t)i;
+            s_acc[i] = 0;
+        }
+        int cur = 0;
+        for (int lvl = 0; (1 << lvl) < m; ++lvl) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < BLOCK_ITEMS; ++q) {
+                const int i = (int)threadIdx.x + q * BLOCK_THREADS;
+                if (i >= m) continue;
+                const int blk = i >> lvl, sb = (blk ^ 1) << lvl;
+                int lo = sb < m ? sb : m, hi = sb + (1 << lvl) < m ? sb + (1 << lvl) : m;
+                const int first = lo;
+                const uint32_t k = s_key[cur][i];
+                while (lo < hi) {   // first sibling key >= k (keys are distinct)
+                    const int mid = (lo + hi) >> 1;
+                    if (s_key[cur][mid] < k) lo = mid + 1;
+                    else hi = mid;
+                }
+                const int rank = lo - first;
+                const uint32_t below = rank ? s_pre[cur][lo - 1] : 0u;   // sibling weights with smaller keys
+                const int id = s_idx[cur][i];
+                if (blk & 1) s_acc[id] += below;                          // the sibling holds the earlier runs
+                const int at = ((blk >> 1) << (lvl + 1)) + (i - (blk << lvl)) + rank;
+                s_key[cur ^ 1][at] = k;
+                s_pre[cur ^ 1][at] = s_pre[cur][i] + below;
+                s_idx[cur ^ 1][at] = (uint16_t)id;
+            }
+            cur ^= 1;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < m; i += BLOCK_THREADS) {
+            key[b0 + i] = s_key[cur][i];
+            pre[b0 + i] = s_pre[cur][i];
+            idx[b0 + i] = (uint32_t)b0 + s_idx[cur][i];
+            acc[b0 + i] = s_acc[i];
+        }
+        __syncthreads();   // the block has left the LDS before the next one comes in
     }
 }
 
-// One merge level: blocks of 2^lvl elements sorted by key with inclusive
-// prefix sums of the weights become blocks of 2^(lvl+1).
+// Three more levels a launch: groups of MERGE_WAYS blocks of 2^lvl runs sorted
+// by p become blocks of 2^(lvl+3).  A run finds its rank in each of its seven
+// sibling blocks (the binary searches advance together, so a step costs one
+// memory latency for all of them): the earlier siblings' sums below it are
+// added to its count, all siblings' ranks and sums place it in the merged
+// block.
+constexpr int MERGE_BITS = 3;
+constexpr int MERGE_WAYS = 1 << MERGE_BITS;
 __global__ __launch_bounds__(256) void runs_merge_kernel(const uint32_t *__restrict__ key, const uint32_t *__restrict__ pre,
                                                          const uint32_t *__restrict__ idx, int lvl,
                                                          uint32_t *__restrict__ key2, uint32_t *__restrict__ pre2,
@@ -255,46 +322,61 @@ __global__ __launch_bounds__(256) void runs_merge_kernel(const uint32_t *__restr
     const uint64_t r = runs_of(hdr);
     if ((1ull << lvl) >= r) return;   // the merge took fewer levels
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < r; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t blk = i >> lvl;
-        const uint64_t sb = (blk ^ 1) << lvl;
-        uint64_t se = sb + (1ull << lvl);
-        if (se > r) se = r;
+        const uint64_t blk = i >> lvl, g0 = (blk >> MERGE_BITS) << (lvl + MERGE_BITS);
+        const int mine = (int)(blk & (MERGE_WAYS - 1));
         const uint32_t k = key[i];
-        uint64_t lo = sb, hi = sb < r ? se : sb;   // first sibling key >= k (keys are distinct)
-        while (lo < hi) {
-            const uint64_t mid = (lo + hi) >> 1;
-            if (key[mid] < k) lo = mid + 1;
-            else hi = mid;
+        // (positions fit 32 bits: r < 2^28)
+        uint32_t lo[MERGE_WAYS], hi[MERGE_WAYS];
+#pragma unroll
+        for (int x = 0; x < MERGE_WAYS; ++x) {
+            const uint64_t a = g0 + ((uint64_t)x << lvl), e = a + (1ull << lvl);
+            lo[x] = (uint32_t)(a < r ? a : r);
+            hi[x] = x == mine ? lo[x] : (uint32_t)(e < r ? e : r);   // its own block: no search
         }
-        const uint64_t rank = lo - sb;
-        const uint32_t below = rank ? pre[lo - 1] : 0u;   // sibling weights with smaller keys
-        if (blk & 1) acc[idx[i]] += below;                 // the sibling holds the earlier runs
-        const uint64_t q = ((blk >> 1) << (lvl + 1)) + (i - (blk << lvl)) + rank;
+        for (int step = 0; step <= lvl; ++step) {
+            uint32_t v[MERGE_WAYS];
+#pragma unroll
+            for (int x = 0; x < MERGE_WAYS; ++x) v[x] = lo[x] < hi[x] ? key[(lo[x] + hi[x]) >> 1] : 0u;
+#pragma unroll
+            for (int x = 0; x < MERGE_WAYS; ++x) {
+                const uint32_t mid = (lo[x] + hi[x]) >> 1;
+                if (lo[x] < hi[x]) {
+                    if (v[x] < k) lo[x] = mid + 1;
+                    else hi[x] = mid;
+                }
+            }
+        }
+        uint32_t earlier = 0, below = 0;
+        uint64_t rank = 0;
+#pragma unroll
+        for (int x = 0; x < MERGE_WAYS; ++x) {
+            const uint64_t a = g0 + ((uint64_t)x << lvl);
+            const uint32_t first = (uint32_t)(a < r ? a : r);
+            const uint32_t w = lo[x] > first ? pre[lo[x] - 1] : 0u;   // (zero for its own block)
+            rank += lo[x] - first;
+            below += w;
+            if (x < mine) earlier += w;
+        }
+        const uint32_t id = idx[i];
+        if (earlier) acc[id] += earlier;
+        const uint64_t q = g0 + (i - (blk << lvl)) + rank;
         key2[q] = k;
         pre2[q] = pre[i] + below;
-        idx2[q] = idx[i];
+        idx2[q] = id;
     }
-}
-
-// Distance of every run, in place of its cold count: z + acc - p - 1.
-__global__ __launch_bounds__(256) void runs_dist_kernel(const uint32_t *__restrict__ rp,
-                                                        const uint32_t *__restrict__ acc,
-                                                        uint32_t *__restrict__ rz, const int32_t *__restrict__ hdr) {
-    if (!hdr[RW_RUNS_OK]) return;
-    const uint64_t r = runs_of(hdr);
-    for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < r; s += (uint64_t)gridDim.x * blockDim.x)
-        rz[s] = rz[s] + acc[s] - rp[s] - 1;
 }
 
 // D of every position from the run list alone: a warm position lies in
 // exactly one run [h, e], every other position is cold.  The runs that can
 // touch a tile are the one in progress at its start and those starting in
 // it; a thread finds the run at its first position by binary search and
-// walks on.
+// walks on.  A run's distance is z + acc - p - 1.
 __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, const uint2 *__restrict__ off,
                                                                 uint64_t tiles, const uint32_t *__restrict__ rh,
                                                                 const uint32_t *__restrict__ re,
-                                                                const uint32_t *__restrict__ rd,
+                                                                const uint32_t *__restrict__ rp,
+                                                                const uint32_t *__restrict__ rz,
+                                                                const uint32_t *__restrict__ acc,
                                                                 uint32_t *__restrict__ dist,
                                                                 const int32_t *__restrict__ hdr) {
     if (!hdr[RW_RUNS_OK]) return;
@@ -319,7 +401,7 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, cons
         // registers: loads only where a run starts
         bool in_run = s >= lo;
         uint64_t end = in_run ? re[s] : 0;
-        uint32_t dv = in_run ? rd[s] : NONE;
+        uint32_t dv = in_run ? rz[s] + acc[s] - rp[s] - 1 : NONE;
         uint64_t next_head = s + 1 < hi ? rh[s + 1] : ~0ull;
         const bool vec = (reinterpret_cast<uintptr_t>(dist) & 15) == 0;
     #pragma unroll
@@ -333,7 +415,7 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, cons
                     ++s;
                     in_run = true;
                     end = re[s];
-                    dv = rd[s];
+                    dv = rz[s] + acc[s] - rp[s] - 1;
                     next_head = s + 1 < hi ? rh[s + 1] : ~0ull;
                 }
                 d[k] = (in_run && end >= t) ? dv : NONE;
@@ -349,23 +431,11 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, cons
     }
 }
 
-__global__ void runs_status_kernel(const int32_t *__restrict__ nested, int32_t *__restrict__ hdr) {
-    if (threadIdx.x == 0 && hdr[RW_PATH] && nested[0]) atomicOr(hdr + RW_STATUS, nested[0]);
-}
-
-// the path, decided from the number of runs: over runs, or the dominance
-// count over accesses when there are more runs than the workspace holds
-__global__ void runs_decide_kernel(int32_t *__restrict__ hdr, uint64_t rmax) {
-    if (threadIdx.x != 0) return;
-    const bool over = runs_of(hdr) > rmax;
-    hdr[RW_PATH] = over ? 1 : 0;
-    hdr[RW_RUNS_OK] = over ? 0 : 1;
-}
-
 static uint64_t runs_max(uint64_t n) { return n / 16 + 1024; }
 
 struct RunsWs {
     int32_t *hdr;
+    uint32_t *ctl;   // control words of the fallback
     void *sd;   // pc_stack_distance workspace (the fallback); the arrays below live inside it
     size_t sd_bytes;
     uint2 *counts, *tsum, *off, *marks;
@@ -377,6 +447,7 @@ static RunsWs carve_runs(void *ws, uint64_t n) {
     Carver c{(char *)ws, 0};
     RunsWs w;
     w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
+    w.ctl = c.take<uint32_t>(SD_CTL_WORDS);
     w.sd_bytes = pc_stack_distance_ws(n);
     const size_t sd_at = c.off;
     const uint64_t tiles = (n + RUN_TILE - 1) / RUN_TILE;
@@ -416,44 +487,42 @@ pc_status pc_stack_distance_runs(const uint32_t *prev, const uint32_t *next, uin
     if (ws_bytes < pc_stack_distance_runs_ws(n)) return PC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const RunsWs w = carve_runs(ws, n);
-    pc_status st = fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, 8, s);
-    if (st != PC_OK || n == 0) return st;
+    if (n == 0) return fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, 8, s);
+    pc_status st;
     const uint64_t tiles = (n + RUN_TILE - 1) / RUN_TILE;
     const uint64_t stiles = (tiles + RSCAN_TILE - 1) / RSCAN_TILE;
+    const uint64_t rm = runs_max(n);
     PC_LAUNCH(K_RUNS_COUNT, runs_count_kernel, dim3((unsigned)tiles), dim3(RUN_THREADS), 0, s, prev, n, w.counts,
               w.marks);
-    PC_LAUNCH(K_RUNS_SCAN, runs_scan_tiles_kernel, dim3((unsigned)stiles), dim3(RSCAN_THREADS), 0, s,
-              (const uint2 *)w.counts, tiles, w.tsum);
-    PC_LAUNCH(K_RUNS_SCAN, runs_scan_top_kernel, dim3(1), dim3(RSCAN_THREADS), 0, s, w.tsum, stiles, w.hdr);
-    PC_LAUNCH(K_RUNS_SCAN, runs_scan_apply_kernel, dim3((unsigned)stiles), dim3(RSCAN_THREADS), 0, s,
-              (const uint2 *)w.counts, tiles, (const uint2 *)w.tsum, w.off);
+    if (stiles > 1)
+        PC_LAUNCH(K_RUNS_SCAN, runs_scan_tiles_kernel, dim3((unsigned)stiles), dim3(RSCAN_THREADS), 0, s,
+                  (const uint2 *)w.counts, tiles, w.tsum);
     // the path is decided on the device, so nothing here waits for the GPU:
     // every later launch is gated on the decision, and the launches of the
     // path not taken return at once (grids capped per compute unit)
-    const uint64_t rm = runs_max(n);
-    PC_LAUNCH(K_RUNS_SCAN, runs_decide_kernel, dim3(1), dim3(64), 0, s, w.hdr, rm);
-    if ((st = stack_distance_gated(prev, next, n, dist, w.sd, s, w.hdr + RW_PATH)) != PC_OK) return st;
-    PC_LAUNCH(K_FILL32, runs_status_kernel, dim3(1), dim3(64), 0, s, (const int32_t *)w.sd, w.hdr);
+    PC_LAUNCH(K_RUNS_SCAN, runs_scan_kernel, dim3((unsigned)stiles), dim3(RSCAN_THREADS), 0, s,
+              (const uint2 *)w.counts, tiles, (const uint2 *)w.tsum, w.off, rm, w.hdr, w.ctl, (uint32_t)SD_CTL_WORDS);
+    if ((st = stack_distance_rare(prev, next, n, dist, w.sd, w.ctl, s, w.hdr + RW_PATH, w.hdr + RW_STATUS)) != PC_OK)
+        return st;
     const int32_t *ok = w.hdr;
     PC_LAUNCH(K_RUNS_COMPACT, runs_compact_kernel, dim3(capped(tiles, 16)), dim3(RUN_THREADS), 0, s, prev, n,
               (const uint2 *)w.off, (const uint2 *)w.marks, w.rp, w.rh, w.re, w.rz, tiles, ok);
+    PC_LAUNCH(K_RUNS_MERGE, runs_block_kernel, dim3(capped((rm + BLOCK_RUNS - 1) / BLOCK_RUNS, 4)),
+              dim3(BLOCK_THREADS), 0, s, (const uint32_t *)w.rp, (const uint32_t *)w.rh, (const uint32_t *)w.re,
+              w.key[0], w.pre[0], w.idx[0], w.acc, ok);
+    // one launch per three levels the largest run count needs; the levels past
+    // the actual count return at once
     const unsigned rg = capped((rm + 255) / 256, 16);
-    PC_LAUNCH(K_RUNS_MERGE, runs_init_kernel, dim3(rg), dim3(256), 0, s, (const uint32_t *)w.rp,
-              (const uint32_t *)w.rh, (const uint32_t *)w.re, w.key[0], w.pre[0], w.idx[0], w.acc, ok);
-    // one launch per level the largest run count needs; the levels past the
-    // actual count return at once
     int cur = 0;
-    for (int lvl = 0; (1ull << lvl) < rm; ++lvl) {
+    for (int lvl = BLOCK_LEVELS; (1ull << lvl) < rm; lvl += MERGE_BITS) {
         PC_LAUNCH(K_RUNS_MERGE, runs_merge_kernel, dim3(rg), dim3(256), 0, s, (const uint32_t *)w.key[cur],
                   (const uint32_t *)w.pre[cur], (const uint32_t *)w.idx[cur], lvl, w.key[cur ^ 1], w.pre[cur ^ 1],
                   w.idx[cur ^ 1], w.acc, ok);
         cur ^= 1;
     }
-    PC_LAUNCH(K_RUNS_MERGE, runs_dist_kernel, dim3(rg), dim3(256), 0, s, (const uint32_t *)w.rp,
-              (const uint32_t *)w.acc, w.rz, ok);
     PC_LAUNCH(K_RUNS_FILL, runs_fill_kernel, dim3(capped(tiles, 16)), dim3(RUN_THREADS), 0, s, n,
-              (const uint2 *)w.off, tiles, (const uint32_t *)w.rh, (const uint32_t *)w.re, (const uint32_t *)w.rz,
-              dist, ok);
+              (const uint2 *)w.off, tiles, (const uint32_t *)w.rh, (const uint32_t *)w.re, (const uint32_t *)w.rp,
+              (const uint32_t *)w.rz, (const uint32_t *)w.acc, dist, ok);
     return PC_OK;
 }
 

@@ -11,12 +11,13 @@
 // equal keys contiguous except where different keys share those bits; the
 // link step resolves such short "mixed" runs by scanning them, and when a
 // run is too long to scan it flags the four passes over the high bits and a
-// second link (then the full 64-bit sort makes equal keys adjacent).
+// second link, one persistent launch (then the full 64-bit sort makes equal
+// keys adjacent).
 //   * the four 8-bit digit histograms of a group of passes come from the
 //     caller (the hash kernel counts them while it writes the keys) or from
-//     one counting pass (LDS-privatised, then global atomics); one workgroup
-//     scans them into digit bases;
-//   * each of the eight sort passes is a single "onesweep" kernel: a
+//     one counting pass (LDS-privatised, then global atomics), whose last
+//     workgroup scans them into digit bases;
+//   * each of the four sort passes is a single "onesweep" kernel: a
 //     workgroup takes the next tile from an atomic counter (so every tile it
 //     waits on is already running), ranks its 8192 elements by digit with
 //     wave ballots (stable: lanes in order, waves in order), publishes its
@@ -47,50 +48,79 @@ constexpr uint64_t FLAG_AGG = 1ull << 32;
 constexpr uint64_t FLAG_INC = 1ull << 33;
 constexpr uint32_t SPIN_LIMIT = 1u << 22;
 
-// Histograms of the four byte digits p0 .. p0+3 (one group of passes) in one
-// read of the keys; the group over the high bytes runs only when asked.
+// Words of the control block (zeroed before each call): tile counters of the
+// passes, tickets, and for the persistent kernel a chunk counter and a count
+// of finished chunks per phase.
+enum CtlWord {
+    CTL_TILE = 0,          // + pass: next tile of a sort pass
+    CTL_TICKET = 8,        // blocks of the histogram kernel that are through
+    CTL_PHASE = 16,        // + 2 * phase: next chunk, finished chunks
+    CTL_WORDS = 48
+};
 constexpr int HIST_DIGITS = SORT_PASSES / 2;
-__global__ __launch_bounds__(256) void sort_hist_kernel(const uint64_t *__restrict__ keys, uint64_t n, int p0,
-                                                        uint32_t *__restrict__ hist,
-                                                        const int32_t *__restrict__ only_if,
-                                                        const uint32_t *__restrict__ n_dev,
-                                                        const int32_t *__restrict__ gate) {
-    if ((only_if && *only_if == 0) || gated_off(gate)) return;
-    n = dev_count(n, n_dev);
-    __shared__ uint32_t h[HIST_DIGITS][RADIX];
-    for (int i = threadIdx.x; i < HIST_DIGITS * RADIX; i += blockDim.x) (&h[0][0])[i] = 0;
+
+// Histogram of HIST_DIGITS byte digits from p0 on over keys[lo, hi), LDS to
+// global (all threads of the workgroup; h: HIST_DIGITS * RADIX words of LDS)
+__device__ __forceinline__ void digit_hist(const uint64_t *keys, uint64_t lo, uint64_t hi, uint64_t stride, int p0,
+                                           uint32_t *h, uint32_t *hist) {
+    for (int i = threadIdx.x; i < HIST_DIGITS * RADIX; i += blockDim.x) h[i] = 0;
     __syncthreads();
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    for (uint64_t i = lo + threadIdx.x; i < hi; i += stride) {
         const uint32_t k = (uint32_t)(keys[i] >> (8 * p0));
 #pragma unroll
-        for (int p = 0; p < HIST_DIGITS; ++p) atomicAdd(&h[p][(k >> (8 * p)) & 0xFF], 1u);
+        for (int p = 0; p < HIST_DIGITS; ++p) atomicAdd(&h[p * RADIX + ((k >> (8 * p)) & 0xFF)], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < HIST_DIGITS * RADIX; i += blockDim.x) {
-        const uint32_t v = (&h[0][0])[i];
-        if (v) atomicAdd(&hist[p0 * RADIX + i], v);
+    for (int i = threadIdx.x; i < HIST_DIGITS * RADIX; i += blockDim.x)
+        if (h[i]) atomicAdd(&hist[p0 * RADIX + i], h[i]);
+}
+
+// Exclusive scan of each of HIST_DIGITS 256-bin rows -> digit bases (one
+// workgroup of at least 256 threads); a row that does not sum to n (a
+// histogram handed in by the caller) is reported
+__device__ __forceinline__ void digit_starts(const uint32_t *rows, uint32_t *start, uint64_t n, uint32_t *tmp,
+                                             int32_t *err) {
+    for (int p = 0; p < HIST_DIGITS; ++p) {
+        uint32_t total;
+        const bool in = (int)threadIdx.x < RADIX;
+        const uint32_t v = in ? ld_status(&rows[p * RADIX + threadIdx.x]) : 0u;
+        const uint32_t e = block_excl_scan(v, tmp, &total);
+        if (in) start[p * RADIX + threadIdx.x] = e;
+        if (threadIdx.x == 0 && (uint64_t)total != n) atomicOr(err, DEV_ERR_BAD_HIST);
     }
 }
 
-// exclusive scan of each pass's 256-bin histogram -> digit bases; hist
-// holds the group's rows (p0 .. p0+3) at rows 0..3; a row that does not sum
-// to n (a histogram handed in by the caller) is reported
-__global__ __launch_bounds__(RADIX) void sort_scan_kernel(const uint32_t *__restrict__ hist, int p0,
-                                                          uint32_t *__restrict__ start, uint64_t n,
-                                                          int32_t *__restrict__ err,
-                                                          const int32_t *__restrict__ only_if,
-                                                          const uint32_t *__restrict__ n_dev,
-                                                          const int32_t *__restrict__ gate) {
-    if ((only_if && *only_if == 0) || gated_off(gate)) return;
+// First launch of a call: clears the control block, the histograms, the
+// partition cursors and the look-back status, and, with the low bytes'
+// histograms handed in, turns them into digit starts.
+__global__ __launch_bounds__(256) void sort_init_kernel(Fills f, const uint32_t *__restrict__ key_hist,
+                                                        uint32_t *__restrict__ start, uint64_t n,
+                                                        int32_t *__restrict__ err, const uint32_t *__restrict__ n_dev,
+                                                        const int32_t *__restrict__ gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t tmp[256 / WAVE];
+    fill_segments(f);
+    if (key_hist && blockIdx.x == 0) digit_starts(key_hist, start, dev_count(n, n_dev), tmp, err);
+}
+
+// Histograms of the four low byte digits in one read of the keys; the last
+// block to finish turns them into digit starts.
+__global__ __launch_bounds__(256) void sort_hist_kernel(const uint64_t *__restrict__ keys, uint64_t n,
+                                                        uint32_t *hist, uint32_t *__restrict__ start,
+                                                        uint32_t *__restrict__ ctl, int32_t *__restrict__ err,
+                                                        const uint32_t *__restrict__ n_dev,
+                                                        const int32_t *__restrict__ gate) {
+    if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
-    __shared__ uint32_t tmp[RADIX / WAVE];
-    for (int p = 0; p < HIST_DIGITS; ++p) {
-        uint32_t total;
-        const uint32_t e = block_excl_scan(hist[p * RADIX + threadIdx.x], tmp, &total);
-        start[(p0 + p) * RADIX + threadIdx.x] = e;
-        if (threadIdx.x == 0 && (uint64_t)total != n) atomicOr(err, DEV_ERR_BAD_HIST);
-    }
+    __shared__ uint32_t h[HIST_DIGITS * RADIX];
+    __shared__ uint32_t tmp[256 / WAVE];
+    __shared__ uint32_t ticket;
+    digit_hist(keys, (uint64_t)blockIdx.x * blockDim.x, n, (uint64_t)gridDim.x * blockDim.x, 0, h, hist);
+    atomics_performed();
+    __syncthreads();
+    if (threadIdx.x == 0) ticket = atomicAdd(&ctl[CTL_TICKET], 1u);
+    __syncthreads();
+    if (ticket == gridDim.x - 1) digit_starts(hist, start, n, tmp, err);
 }
 
 // Large tiles make each digit's run in the output long (about 32 elements
@@ -110,12 +140,14 @@ struct SortLds {
 // One tile of a pass: the workgroup takes the next tile from the counter
 // (tiles are handed out in order, so every tile a look-back waits on belongs
 // to a workgroup already running it); false when none is left.
-__device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *__restrict__ keys_in,
-                                          const uint32_t *__restrict__ vals_in, uint64_t *__restrict__ keys_out,
-                                          uint32_t *__restrict__ vals_out, uint64_t n, int shift,
-                                          const uint32_t *__restrict__ start, uint64_t *__restrict__ status,
-                                          uint32_t *__restrict__ counter, uint32_t epoch, int32_t *__restrict__ err) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, const uint32_t *vals_in,
+                                          uint64_t *keys_out, uint32_t *vals_out, uint64_t n, int shift,
+                                          const uint32_t *start, uint64_t *status, uint32_t *counter, uint32_t epoch,
+                                          int32_t *err) {
+    // (an opaque copy: in a loop over tiles what is derived from it is worked
+    // out per tile instead of being held, and spilled, across the loop)
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
     const int lane = tid & (WAVE - 1);
     const int w = tid / WAVE;
     if (tid == 0) L.tile = atomicAdd(counter, 1u);
@@ -238,10 +270,9 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_pass_kernel(
     const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in,
     uint64_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out, uint64_t n, int shift,
     const uint32_t *__restrict__ start, uint64_t *__restrict__ status, uint32_t *__restrict__ counter,
-    uint32_t epoch, int32_t *__restrict__ err, const int32_t *__restrict__ only_if,
-    const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
-    // passes over the high key bits run only when the link step needs them
-    if ((only_if && *only_if == 0) || gated_off(gate)) return;
+    uint32_t epoch, int32_t *__restrict__ err, const uint32_t *__restrict__ n_dev,
+    const int32_t *__restrict__ gate) {
+    if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
     // Workgroups past the tile count take no tile (the counter then hands
     // out exactly the tiles there are) and leave at once: a grid sized for a
@@ -249,25 +280,6 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_pass_kernel(
     if ((uint64_t)blockIdx.x * SORT_TILE >= n) return;
     __shared__ SortLds L;
     sort_tile(L, keys_in, vals_in, keys_out, vals_out, n, shift, start, status, counter, epoch, err);
-}
-
-// The same pass from a small persistent grid (each workgroup takes tiles
-// until none are left), for launches that seldom do work: gated off, such a
-// launch costs a few hundred workgroups instead of one per tile.  When it
-// does run it is slower (11.0 against 7.5 ms for four passes over 2.1e9
-// keys), since one tile per workgroup overlaps one tile's tail with the next
-// one's loads.
-__global__ __launch_bounds__(SORT_THREADS, 4) void sort_pass_persistent_kernel(
-    const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in,
-    uint64_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out, uint64_t n, int shift,
-    const uint32_t *__restrict__ start, uint64_t *__restrict__ status, uint32_t *__restrict__ counter,
-    uint32_t epoch, int32_t *__restrict__ err, const int32_t *__restrict__ only_if,
-    const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
-    if ((only_if && *only_if == 0) || gated_off(gate)) return;
-    n = dev_count(n, n_dev);
-    __shared__ SortLds L;
-    while (sort_tile(L, keys_in, vals_in, keys_out, vals_out, n, shift, start, status, counter, epoch, err))
-        __syncthreads();   // the tile has left the LDS before the next one comes in
 }
 
 // ---- links, and the way back to time order -------------------------------
@@ -446,9 +458,9 @@ struct PermLds {
 
 template <bool FROM_SORT, int PERM_THREADS, int ITEMS, int RADIX_N, bool PER_TILE>
 __device__ __forceinline__ void perm_partition_body(
-    PermLds<PERM_THREADS * ITEMS, PERM_THREADS, RADIX_N> &L, const uint64_t *__restrict__ sk, const uint32_t *__restrict__ in_t,
-    const uint64_t *__restrict__ in_pn, uint64_t n, int s, uint64_t per_wg, uint32_t *__restrict__ cursor,
-    uint32_t *__restrict__ out_t, uint64_t *__restrict__ out_pn, bool full, int32_t *__restrict__ overflow) {
+    PermLds<PERM_THREADS * ITEMS, PERM_THREADS, RADIX_N> &L, const uint64_t *sk, const uint32_t *in_t,
+    const uint64_t *in_pn, uint64_t n, int s, uint64_t chunk, uint64_t per_wg, uint32_t *cursor, uint32_t *out_t,
+    uint64_t *out_pn, bool full, int32_t *overflow) {
     uint32_t *s_stage = reinterpret_cast<uint32_t *>(L.stage), *s_cnt = L.cnt, *s_lstart = L.lstart,
              *s_cur = L.cur, *s_bucket = reinterpret_cast<uint32_t *>(L.stage), *s_tmp = L.tmp;
     static_assert(RADIX_N % PERM_THREADS == 0 || PERM_THREADS % RADIX_N == 0, "whole digits per thread");
@@ -461,9 +473,10 @@ __device__ __forceinline__ void perm_partition_body(
     const bool owner = (int)threadIdx.x * DPT < RADIX_N;
     // positions fit 32 bits (n < 2^32 - 1); offsets from a tile's base are
     // compared against what is left, so nothing wraps near the end
-    if ((uint64_t)blockIdx.x * per_wg >= n) return;
-    const int tid0 = threadIdx.x;   // the tile loop below takes its own copy
-    const uint32_t lo = (uint32_t)((uint64_t)blockIdx.x * per_wg);
+    if (chunk * per_wg >= n) return;
+    int tid0 = threadIdx.x;   // the tile loop below takes its own copy
+    __asm__ volatile("" : "+v"(tid0));
+    const uint32_t lo = (uint32_t)(chunk * per_wg);
     const uint32_t hi = (uint64_t)lo + per_wg < n ? (uint32_t)(lo + per_wg) : (uint32_t)n;
 
     // ---- (per chunk) count the chunk's digits and reserve one run per digit
@@ -496,7 +509,7 @@ __device__ __forceinline__ void perm_partition_body(
     for (int q = 0; q < DPT && owner; ++q) {
         const int d = tid0 * DPT + q;
         const uint32_t c = s_cnt[d];
-        if (c) s_cur[d] = atomicAdd(&cursor[s_bucket[d]], c);
+        if (c) s_cur[d] = (s_bucket[d] << s) + atomicAdd(&cursor[s_bucket[d]], c);
     }
     __syncthreads();
     }
@@ -655,7 +668,10 @@ __device__ __forceinline__ void perm_partition_body(
         for (int q = 0; q < DPT && owner; ++q) {
             s_lstart[tid * DPT + q] = run;
             run += c[q];
-            if (PER_TILE && c[q]) s_cur[tid * DPT + q] = atomicAdd(&cursor[s_bucket[tid * DPT + q]], c[q]);
+            if (PER_TILE && c[q]) {
+                const uint32_t b = s_bucket[tid * DPT + q];
+                s_cur[tid * DPT + q] = (b << s) + atomicAdd(&cursor[b], c[q]);
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -695,21 +711,19 @@ __device__ __forceinline__ void perm_partition_body(
 }
 
 // The link variant holds more state per element (keys and neighbours): four
-// 256-thread workgroups per CU; the plain partition runs two of 512.  The first link
-// (over keys sorted by their low 32 bits) raises *flag when a mixed run is too
-// long to scan; the second one runs only then (only_if = flag), over fully
-// sorted keys.
+// 256-thread workgroups per CU; the plain partition runs two of 512.  The link
+// over keys sorted by their low 32 bits raises *flag when a mixed run is too
+// long to scan.
 __global__ __launch_bounds__(LINK_THREADS, 4) void link_partition_kernel(
     const uint64_t *__restrict__ sk, const uint32_t *__restrict__ in_t, uint64_t n, int s, int cus,
     uint32_t *__restrict__ cursor, uint32_t *__restrict__ out_t, uint64_t *__restrict__ out_pn,
-    const int32_t *__restrict__ only_if, int32_t *__restrict__ flag, const uint32_t *__restrict__ n_dev,
-    const int32_t *__restrict__ gate) {
-    if ((only_if && *only_if == 0) || gated_off(gate)) return;
+    int32_t *__restrict__ flag, const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
+    if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
     const uint64_t per_wg = chunk_elems(n, cus, LINK_CHUNK_MAX, LINK_TILE);
     __shared__ PermLds<LINK_TILE, LINK_THREADS, LINK_RADIX> L;
-    perm_partition_body<true, LINK_THREADS, LINK_ITEMS, LINK_RADIX, false>(L, sk, in_t, nullptr, n, s, per_wg, cursor, out_t, out_pn, only_if != nullptr,
-                              flag);
+    perm_partition_body<true, LINK_THREADS, LINK_ITEMS, LINK_RADIX, false>(L, sk, in_t, nullptr, n, s, blockIdx.x,
+                                                                           per_wg, cursor, out_t, out_pn, false, flag);
 }
 
 __global__ __launch_bounds__(PART_THREADS, 4) void perm_partition_kernel(
@@ -720,14 +734,8 @@ __global__ __launch_bounds__(PART_THREADS, 4) void perm_partition_kernel(
     n = dev_count(n, n_dev);
     const uint64_t per_wg = chunk_elems(n, cus, PERM_CHUNK_MAX, PERM_TILE);
     __shared__ PermLds<PERM_TILE, PART_THREADS, PERM_RADIX> L;
-    perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(L, nullptr, in_t, in_pn, n, s, per_wg, cursor, out_t, out_pn, true, nullptr);
-}
-
-// cursor[b] = b << s: each bucket's output run starts at its first t
-__global__ void perm_cursor_kernel(uint32_t *__restrict__ cursor, uint64_t nb, int s, const int32_t *__restrict__ gate) {
-    if (gated_off(gate)) return;
-    const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nb) cursor[b] = (uint32_t)(b << s);
+    perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(L, nullptr, in_t, in_pn, n, s, blockIdx.x,
+                                                                           per_wg, cursor, out_t, out_pn, true, nullptr);
 }
 
 // every 16384-range of t holds exactly its own triples: place the (prev,
@@ -738,12 +746,17 @@ __global__ __launch_bounds__(LOCAL_THREADS) void perm_local_kernel(const uint32_
                                                                    const uint64_t *__restrict__ in_pn,
                                                                    uint64_t n, uint32_t *__restrict__ prev,
                                                                    uint32_t *__restrict__ next,
+                                                                   const int32_t *__restrict__ hdr, SortReport report,
                                                                    const uint32_t *__restrict__ n_dev,
                                                                    const int32_t *__restrict__ gate) {
     constexpr uint32_t SPAN = 1u << PERM_LOCAL_BITS;
     constexpr int PER = SPAN / LOCAL_THREADS;
     __shared__ uint64_t s_pn[SPAN];
     if (gated_off(gate)) return;
+    if (report.hdr && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (hdr[0]) atomicOr(report.hdr, hdr[0]);
+        report.hdr[report.high_word] = hdr[1];
+    }
     n = dev_count(n, n_dev);
     // one range per workgroup, or several from a capped grid
     for (uint64_t r0 = (uint64_t)blockIdx.x * SPAN; r0 < n; r0 += (uint64_t)gridDim.x * SPAN) {
@@ -771,16 +784,6 @@ __global__ __launch_bounds__(LOCAL_THREADS) void perm_local_kernel(const uint32_
         __syncthreads();   // the range has left the LDS before the next one comes in
     }
 }
-
-struct SortWs {
-    int32_t *hdr;
-    uint32_t *hist, *start, *counters;
-    uint64_t *k1, *k2;   // sort ping-pong; afterwards (prev, next) pairs
-    uint32_t *v1, *v2;   // sort ping-pong; afterwards times t
-    uint64_t *status;
-    uint32_t *cursor;
-    size_t bytes;
-};
 
 // Partition plan for the way back to time order.  The last step uses
 // 16384-ranges of t.  The link splits into at most 256 buckets, later passes
@@ -823,120 +826,311 @@ static PermPlan plan_perm(uint64_t n) {
     return p;
 }
 
-static SortWs carve_sort(void *ws, uint64_t n) {
-    Carver c{(char *)ws, 0};
-    SortWs w;
-    const uint64_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
-    w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
-    w.hist = c.take<uint32_t>(SORT_PASSES * RADIX);
-    w.start = c.take<uint32_t>(SORT_PASSES * RADIX);
-    w.counters = c.take<uint32_t>(SORT_PASSES);
-    w.k1 = c.take<uint64_t>(n);
-    w.k2 = c.take<uint64_t>(n);
-    w.v1 = c.take<uint32_t>(n);
-    w.v2 = c.take<uint32_t>(n);
-    w.status = c.take<uint64_t>(tiles * RADIX);
-    w.cursor = c.take<uint32_t>(plan_perm(n).max_buckets + 1);
-    w.bytes = c.off;
-    return w;
+// The control block: histograms, counters and partition cursors (one array per
+// partition: both links, then the later passes), contiguous so that one fill
+// clears them, and the digit starts.
+static SortCtl take_ctl(Carver &c, uint64_t n) {
+    SortCtl k;
+    const PermPlan pp = plan_perm(n);
+    k.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
+    k.start = c.take<uint32_t>(SORT_PASSES * RADIX);
+    const size_t z0 = c.off;
+    k.hist = c.take<uint32_t>(SORT_PASSES * RADIX);
+    k.words = c.take<uint32_t>(CTL_WORDS);
+    k.link2 = c.take<uint32_t>(LINK_RADIX);
+    for (int i = 0; i < pp.passes; ++i) k.cursor[i] = c.take<uint32_t>(pp.buckets[i]);
+    k.zero_words = (c.off - z0) / sizeof(uint32_t);
+    return k;
+}
+SortCtl sort_ctl(void *at, uint64_t n, size_t *bytes) {
+    Carver c{(char *)at, 0};
+    const SortCtl k = take_ctl(c, n);
+    *bytes = c.off;
+    return k;
+}
+void sort_ctl_clear(Fills &f, const SortCtl &k) {
+    f.add(k.hdr, 0u, 2);
+    f.add(k.hist, 0u, k.zero_words);
 }
 
+struct SortBufs {
+    uint64_t *k1, *k2;   // sort ping-pong; afterwards (prev, next) pairs
+    uint32_t *v1, *v2;   // sort ping-pong; afterwards times t
+    uint64_t *status;
+};
+static SortBufs take_bufs(Carver &c, uint64_t n) {
+    SortBufs b;
+    b.k1 = c.take<uint64_t>(n);
+    b.k2 = c.take<uint64_t>(n);
+    b.v1 = c.take<uint32_t>(n);
+    b.v2 = c.take<uint32_t>(n);
+    b.status = c.take<uint64_t>((n + SORT_TILE - 1) / SORT_TILE * RADIX);
+    return b;
+}
+size_t sort_bufs_bytes(uint64_t n) {
+    Carver c{nullptr, 0};
+    take_bufs(c, n);
+    return c.off;
+}
+
+// ---- the whole of prev/next, or its tail, in one launch ------------------
+// A path that a call seldom takes (the passes over the high key bits; the
+// generic path behind the chained one) must still be enqueued, since the
+// choice is made on the device, and a launch that its gate turns off costs
+// about 4.5 us in the stream: eight launches for the high bits and twenty for
+// the generic path.  Here they are one persistent kernel of phases (for the
+// generic path, where that is the better one: prev_next_rare).  A phase
+// hands out its chunks from a counter and counts the finished ones; a
+// workgroup goes on to the next phase once all are finished.  Only running
+// workgroups hold chunks, so the wait ends whatever part of the grid is
+// resident.
+enum SortPhase { PH_HIST, PH_PASS, PH_LINK = PH_PASS + 4, PH_HIST2, PH_PASS2, PH_LINK2 = PH_PASS2 + 4, PH_PERM, PH_COUNT = PH_PERM + 3 };
+static_assert(CTL_PHASE + 2 * PH_COUNT <= CTL_WORDS, "the control words hold every phase");
+
+struct SortJob {
+    const uint64_t *keys;
+    uint64_t n;
+    const uint32_t *n_dev;
+    const uint32_t *key_hist;
+    SortCtl k;
+    SortBufs b;
+    PermPlan plan;
+    int cus;
+    bool whole;   // from the first pass to the last partition; else only the high bits and the second link
+    RareGate rare;
+};
+
+union PersistentLds {
+    SortLds sort;
+    PermLds<LINK_TILE, SORT_THREADS, LINK_RADIX> link;
+    PermLds<PERM_TILE, PART_THREADS, PERM_RADIX> perm;
+    uint32_t hist[HIST_DIGITS * RADIX];
+};
+static_assert(SORT_THREADS == PART_THREADS, "one workgroup size for all phases");
+
+// the next chunk of a phase, for the whole workgroup
+__device__ __forceinline__ uint32_t next_chunk(uint32_t *ctl, int phase, uint32_t *s_word) {
+    __syncthreads();
+    if (threadIdx.x == 0) *s_word = atomicAdd(&ctl[CTL_PHASE + 2 * phase], 1u);
+    __syncthreads();
+    return *s_word;
+}
+__device__ __forceinline__ uint32_t *phase_done(uint32_t *ctl, int phase) { return &ctl[CTL_PHASE + 2 * phase + 1]; }
+
+// histograms of four byte digits from p0 on, then their starts; `clear`: the
+// look-back status is cleared on the way, `given`: the histograms are known
+__device__ __forceinline__ void persistent_hist(const SortJob &j, uint64_t n, int p0, int phase, bool clear,
+                                                const uint32_t *given, PersistentLds &L, uint32_t *s_tmp,
+                                                uint32_t *s_word) {
+    // a chunk is whole tiles: two per workgroup, up to eight (a chunk ends with
+    // a flush of its histogram to device memory)
+    const uint64_t tiles = (n + SORT_TILE - 1) / SORT_TILE, even = tiles / (2 * gridDim.x);
+    const uint64_t per = even < 1 ? 1 : even > 8 ? 8 : even, CHUNK = per * SORT_TILE, WORDS = per * RADIX;
+    const uint64_t words = tiles * RADIX;
+    const uint32_t chunks = (uint32_t)((tiles + per - 1) / per);
+    uint32_t mine = 0;
+    for (uint32_t c; (c = next_chunk(j.k.words, phase, s_word)) < chunks; ++mine) {
+        const uint64_t lo = (uint64_t)c * CHUNK, hi = lo + CHUNK < n ? lo + CHUNK : n;
+        if (clear)
+            for (uint64_t i = c * WORDS + threadIdx.x; i < (c + 1) * WORDS && i < words; i += SORT_THREADS)
+                j.b.status[i] = 0;
+        if (!given) digit_hist(j.keys, lo, hi, blockDim.x, p0, L.hist, j.k.hist);
+    }
+    finish_phase(phase_done(j.k.words, phase), mine, chunks, j.k.hdr);
+    // every workgroup works the starts out and writes the same words
+    digit_starts(given ? given : j.k.hist + p0 * RADIX, j.k.start + p0 * RADIX, n, s_tmp, j.k.hdr);
+    __threadfence_block();
+    __syncthreads();
+}
+
+// the verdict of the path that a rare one stands behind
+__device__ __forceinline__ int32_t rare_reason(const RareGate &r) {
+    if (*r.good == 0) return *r.reason;
+    return *r.error ? r.error_reason : *r.fail ? r.fail_reason : 0;
+}
+__global__ void rare_gate_kernel(RareGate r) {
+    const int32_t why = rare_reason(r);
+    if (why == 0) return;
+    *r.reason = why;
+    *r.on = 1;
+}
+
+__global__ __launch_bounds__(SORT_THREADS, 4) void sort_persistent_kernel(SortJob j, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    if (j.whole) {
+        const int32_t why = rare_reason(j.rare);
+        if (why == 0) return;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *j.rare.reason = why;
+            *j.rare.on = 1;
+        }
+    } else if (j.k.hdr[1] == 0) {
+        return;
+    }
+    const uint64_t n = dev_count(j.n, j.n_dev);
+    __shared__ PersistentLds L;
+    __shared__ uint32_t s_tmp[SORT_THREADS / WAVE], s_word;
+    uint32_t *ctl = j.k.words;
+    const uint32_t tiles = (uint32_t)((n + SORT_TILE - 1) / SORT_TILE);
+    auto pass = [&](int p) {
+        const uint64_t *kin = p == 0 ? j.keys : (p & 1) ? j.b.k1 : j.b.k2;
+        const uint32_t *vin = p == 0 ? nullptr : (p & 1) ? j.b.v1 : j.b.v2;
+        uint64_t *kout = (p & 1) ? j.b.k2 : j.b.k1;
+        uint32_t *vout = (p & 1) ? j.b.v2 : j.b.v1;
+        const int phase = p < SORT_PASSES / 2 ? PH_PASS + p : PH_PASS2 + p - SORT_PASSES / 2;
+        uint32_t mine = 0;
+        __syncthreads();
+        while (sort_tile(L.sort, kin, vin, kout, vout, n, 8 * p, j.k.start + p * RADIX, j.b.status,
+                         ctl + CTL_TILE + p, (uint32_t)(p + 1), j.k.hdr)) {
+            ++mine;
+            __syncthreads();   // the tile has left the LDS before the next one comes in
+        }
+        finish_phase(phase_done(ctl, phase), mine, tiles, j.k.hdr);
+    };
+    auto link = [&](int phase, uint32_t *cursor, bool full) {
+        const uint64_t per = chunk_elems(n, j.cus, LINK_CHUNK_MAX, LINK_TILE);
+        const uint32_t chunks = (uint32_t)((n + per - 1) / per);
+        uint32_t mine = 0;
+        for (uint32_t c; (c = next_chunk(ctl, phase, &s_word)) < chunks; ++mine)
+            perm_partition_body<true, SORT_THREADS, LINK_TILE / SORT_THREADS, LINK_RADIX, false>(
+                L.link, j.b.k2, j.b.v2, nullptr, n, j.plan.s[0], c, per, cursor, j.b.v1, j.b.k1, full,
+                full ? nullptr : j.k.hdr + 1);
+        finish_phase(phase_done(ctl, phase), mine, chunks, j.k.hdr);
+    };
+    if (j.whole) {
+        persistent_hist(j, n, 0, PH_HIST, true, j.key_hist, L, s_tmp, &s_word);
+#pragma unroll 1
+        for (int p = 0; p < SORT_PASSES / 2; ++p) pass(p);
+        link(PH_LINK, j.k.cursor[0], false);
+    }
+    // (the flag is only ever raised, before the phase that precedes this ends)
+    if (__hip_atomic_load(j.k.hdr + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        persistent_hist(j, n, SORT_PASSES / 2, PH_HIST2, false, nullptr, L, s_tmp, &s_word);
+        // the passes go on from the low-sorted keys (k2, v2); the first link's
+        // triples in (k1, v1) are overwritten and made again
+#pragma unroll 1
+        for (int p = SORT_PASSES / 2; p < SORT_PASSES; ++p) pass(p);
+        link(PH_LINK2, j.k.link2, true);
+    }
+    if (j.whole) {
+#pragma unroll 1
+        for (int i = 1; i < j.plan.passes; ++i) {
+            const uint64_t per = chunk_elems(n, j.cus, PERM_CHUNK_MAX, PERM_TILE);
+            const uint32_t chunks = (uint32_t)((n + per - 1) / per);
+            // (selected, not indexed: the job stays out of scratch memory)
+            const bool odd = i & 1;
+            const int shift = i == 1 ? j.plan.s[1] : i == 2 ? j.plan.s[2] : j.plan.s[3];
+            uint32_t *cursor = i == 1 ? j.k.cursor[1] : i == 2 ? j.k.cursor[2] : j.k.cursor[3];
+            uint32_t mine = 0;
+            for (uint32_t c; (c = next_chunk(ctl, PH_PERM + i - 1, &s_word)) < chunks; ++mine)
+                perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(
+                    L.perm, nullptr, odd ? j.b.v1 : j.b.v2, odd ? j.b.k1 : j.b.k2, n, shift, c, per, cursor,
+                    odd ? j.b.v2 : j.b.v1, odd ? j.b.k2 : j.b.k1, true, nullptr);
+            finish_phase(phase_done(ctl, PH_PERM + i - 1), mine, chunks, j.k.hdr);
+        }
+    }
+}
+
+static pc_status perm_local(const SortJob &j, uint32_t *prev, uint32_t *next, hipStream_t s, const int32_t *gate,
+                            const SortReport &report) {
+    const int cur = (j.plan.passes - 1) & 1;
+    const uint64_t span = 1ull << PERM_LOCAL_BITS;
+    const uint64_t ranges = (j.n + span - 1) / span;
+    PC_LAUNCH(K_PERM_LOCAL, perm_local_kernel, dim3(j.whole ? capped(ranges, 1) : (unsigned)ranges),
+              dim3(LOCAL_THREADS), 0, s, cur ? j.b.v2 : j.b.v1, cur ? j.b.k2 : j.b.k1, j.n, prev, next,
+              (const int32_t *)j.k.hdr, report, j.n_dev, gate);
+    return PC_OK;
+}
 
 pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev, uint32_t *prev, uint32_t *next,
-                         const uint32_t *key_hist, void *ws, hipStream_t s, const int32_t *gate, bool rare) {
-    SortWs w = carve_sort(ws, n);
-    pc_status st = fill_u32_gated(reinterpret_cast<uint32_t *>(w.hdr), 0u, 1, s, gate);
-    if (st != PC_OK || n == 0) return st;
-
+                         const uint32_t *key_hist, const SortCtl &k, void *bufs, hipStream_t s, const int32_t *gate,
+                         const SortReport &report) {
+    Carver c{(char *)bufs, 0};
+    const SortBufs b = take_bufs(c, n);
+    if (n == 0) return PC_OK;
     const uint64_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
-    if ((st = fill_u32_gated(w.hist, 0u, SORT_PASSES * RADIX, s, gate)) != PC_OK) return st;
-    if ((st = fill_u32_gated(w.counters, 0u, SORT_PASSES, s, gate)) != PC_OK) return st;
-    if ((st = fill_u32_gated(reinterpret_cast<uint32_t *>(w.status), 0u, tiles * RADIX * 2, s, gate)) != PC_OK)
-        return st;
-
     const int cus = device_cus();
+    // The plan is made for the bound n: with fewer elements its later buckets
+    // stay empty.
+    const PermPlan pp = plan_perm(n);
+    if (pp.buckets[0] > (uint64_t)LINK_RADIX) return PC_ERR_TOO_LARGE;   // the plan never splits wider
+    Fills f;
+    sort_ctl_clear(f, k);
+    f.add(b.status, 0u, tiles * RADIX * 2);
+    PC_LAUNCH(K_FILL32, sort_init_kernel, dim3(fill_blocks(f)), dim3(256), 0, s, f, key_hist, k.start, n, k.hdr, n_dev,
+              gate);
     uint64_t hg = (n + 4095) / 4096;
     if (hg > (uint64_t)cus * 4) hg = (uint64_t)cus * 4;
-    // flag (header word 1): the first link met a mixed run too long to scan,
-    // so the high-byte passes and a second link run
-    int32_t *need_high = w.hdr + 1;
-    if ((st = fill_u32_gated(reinterpret_cast<uint32_t *>(need_high), 0u, 1, s, gate)) != PC_OK) return st;
     // the low bytes' histograms: handed in by the hash, or counted here
     if (!key_hist)
-        PC_LAUNCH(K_SORT_HIST, sort_hist_kernel, dim3((unsigned)hg), dim3(256), 0, s, keys, n, 0, w.hist,
-                  (const int32_t *)nullptr, n_dev, gate);
-    PC_LAUNCH(K_SORT_SCAN, sort_scan_kernel, dim3(1), dim3(RADIX), 0, s, key_hist ? key_hist : w.hist, 0, w.start, n,
-              w.hdr, (const int32_t *)nullptr, n_dev, gate);
-
+        PC_LAUNCH(K_SORT_HIST, sort_hist_kernel, dim3((unsigned)hg), dim3(256), 0, s, keys, n, k.hist, k.start,
+                  k.words, k.hdr, n_dev, gate);
+    const uint64_t *kin = keys;
+    const uint32_t *vin = nullptr;
+    for (int p = 0; p < SORT_PASSES / 2; ++p) {
+        uint64_t *kout = (p & 1) ? b.k2 : b.k1;
+        uint32_t *vout = (p & 1) ? b.v2 : b.v1;
+        PC_LAUNCH(K_SORT_PASS, sort_pass_kernel, dim3((unsigned)tiles), dim3(SORT_THREADS), 0, s, kin, vin, kout,
+                  vout, n, 8 * p, k.start + p * RADIX, b.status, k.words + CTL_TILE + p, (uint32_t)(p + 1), k.hdr,
+                  n_dev, gate);
+        kin = kout;
+        vin = vout;
+    }
     // Links + partition back to time order.  The sort leaves (key, t) in
     // (k2, v2) after four passes and again after eight; the triples ping-pong
     // between the first sort buffers ((prev, next) pairs in k1, t in v1) and,
     // once the sorted keys have been consumed, the second ones (k2, v2).
-    // The plan is made for the bound n: with fewer elements its later
-    // buckets stay empty.
-    const PermPlan pp = plan_perm(n);
-    if (pp.buckets[0] > (uint64_t)LINK_RADIX) return PC_ERR_TOO_LARGE;   // the plan never splits wider
-    uint32_t *bt[2] = {w.v1, w.v2};
-    uint64_t *bpn[2] = {w.k1, w.k2};
     const unsigned ptiles = (unsigned)max_chunks(n, cus, PERM_CHUNK_MAX, PERM_TILE);
     const unsigned ltiles = (unsigned)max_chunks(n, cus, LINK_CHUNK_MAX, LINK_TILE);
-    const unsigned cg0 = (unsigned)((pp.buckets[0] + 255) / 256);
-
-    const uint64_t *kin = keys;
-    const uint32_t *vin = nullptr;
-    for (int p = 0; p < SORT_PASSES; ++p) {
-        if (p == SORT_PASSES / 2) {
-            // first link, over keys sorted by their low 32 bits
-            PC_LAUNCH(K_FILL32, perm_cursor_kernel, dim3(cg0), dim3(256), 0, s, w.cursor, pp.buckets[0], pp.s[0],
-                      gate);
-            PC_LAUNCH(K_LINK, link_partition_kernel, dim3(ltiles), dim3(LINK_THREADS), 0, s, kin, vin, n, pp.s[0],
-                      cus, w.cursor, bt[0], bpn[0], (const int32_t *)nullptr, need_high, n_dev, gate);
-            PC_LAUNCH(K_SORT_HIST, sort_hist_kernel, dim3((unsigned)hg), dim3(256), 0, s, keys, n, SORT_PASSES / 2,
-                      w.hist, (const int32_t *)need_high, n_dev, gate);
-            PC_LAUNCH(K_SORT_SCAN, sort_scan_kernel, dim3(1), dim3(RADIX), 0, s, w.hist + SORT_PASSES / 2 * RADIX,
-                      SORT_PASSES / 2, w.start, n, w.hdr, (const int32_t *)need_high, n_dev, gate);
-        }
-        uint64_t *kout = (p & 1) ? w.k2 : w.k1;
-        uint32_t *vout = (p & 1) ? w.v2 : w.v1;
-        // the passes over the high bits, and every pass of a call that
-        // seldom runs, take the persistent grid
-        const int32_t *high = p >= SORT_PASSES / 2 ? (const int32_t *)need_high : nullptr;
-        if (high || rare)
-            PC_LAUNCH(K_SORT_PASS, sort_pass_persistent_kernel, dim3(capped(tiles, 2)), dim3(SORT_THREADS), 0, s,
-                      kin, vin, kout, vout, n, 8 * p, w.start + p * RADIX, w.status, w.counters + p,
-                      (uint32_t)(p + 1), w.hdr, high, n_dev, gate);
-        else
-            PC_LAUNCH(K_SORT_PASS, sort_pass_kernel, dim3((unsigned)tiles), dim3(SORT_THREADS), 0, s, kin, vin,
-                      kout, vout, n, 8 * p, w.start + p * RADIX, w.status, w.counters + p, (uint32_t)(p + 1),
-                      w.hdr, high, n_dev, gate);
-        kin = kout;
-        vin = vout;
-    }
-    // second link, over fully sorted keys, only if the first one gave up
-    PC_LAUNCH(K_FILL32, perm_cursor_kernel, dim3(cg0), dim3(256), 0, s, w.cursor, pp.buckets[0], pp.s[0], gate);
     PC_LAUNCH(K_LINK, link_partition_kernel, dim3(ltiles), dim3(LINK_THREADS), 0, s, kin, vin, n, pp.s[0], cus,
-              w.cursor, bt[0], bpn[0], (const int32_t *)need_high, (int32_t *)nullptr, n_dev, gate);
-    int cur = 0;
+              k.cursor[0], b.v1, b.k1, k.hdr + 1, n_dev, gate);
+    // the passes over the high bits and a second link, if the first one met a
+    // mixed run too long to scan (header word 1)
+    const SortJob j{keys, n, n_dev, key_hist, k, b, pp, cus, false, RareGate{}};
+    PC_LAUNCH(K_SORT_HIGH, sort_persistent_kernel, dim3(capped(tiles, 2)), dim3(SORT_THREADS), 0, s, j, gate);
+    uint32_t *bt[2] = {b.v1, b.v2};
+    uint64_t *bpn[2] = {b.k1, b.k2};
     for (int i = 1; i < pp.passes; ++i) {
-        const unsigned cg = (unsigned)((pp.buckets[i] + 255) / 256);
-        PC_LAUNCH(K_FILL32, perm_cursor_kernel, dim3(cg), dim3(256), 0, s, w.cursor, pp.buckets[i], pp.s[i], gate);
-        const int nxt = cur ^ 1;
-        PC_LAUNCH(K_PERM, perm_partition_kernel, dim3(ptiles), dim3(PART_THREADS), 0, s, bt[cur], bpn[cur], n,
-                  pp.s[i], cus, w.cursor, bt[nxt], bpn[nxt], n_dev, gate);
-        cur = nxt;
+        const int from = (i - 1) & 1;
+        PC_LAUNCH(K_PERM, perm_partition_kernel, dim3(ptiles), dim3(PART_THREADS), 0, s, bt[from], bpn[from], n,
+                  pp.s[i], cus, k.cursor[i], bt[from ^ 1], bpn[from ^ 1], n_dev, gate);
     }
-    const uint64_t span = 1ull << PERM_LOCAL_BITS;
-    const uint64_t ranges = (n + span - 1) / span;
-    PC_LAUNCH(K_PERM_LOCAL, perm_local_kernel, dim3(rare ? capped(ranges, 1) : (unsigned)ranges), dim3(LOCAL_THREADS),
-              0, s, bt[cur], bpn[cur], n, prev, next, n_dev, gate);
-    return PC_OK;
+    return perm_local(j, prev, next, s, gate, report);
+}
+
+// As one persistent launch, or as the launches of prev_next_core behind the
+// verdict.  On, a chained call over random keys took 0.23 ms persistent at
+// 1.0e5 keys, 0.33 as launches; 0.63 and 0.37 at 3.0e6; 2.61 and 2.02 at
+// 3.0e7; 13.3 and 12.2 at 2.0e8: the ends of the phases weigh most where a
+// phase is a few tiles per CU.  Off, which is the rule, the launches cost 27 us
+// more than the one at 2.8e7 keys (of a step of 1.76 ms), and with their
+// grids' size 0.37 ms of 20.4 at 8.0e8, so the largest calls keep the one.
+constexpr uint64_t RARE_LAUNCHES_MIN = 1ull << 20, RARE_LAUNCHES_MAX = 1ull << 26;
+pc_status prev_next_rare(const uint64_t *keys, uint64_t n, uint32_t *prev, uint32_t *next, const uint32_t *key_hist,
+                         const SortCtl &k, void *bufs, hipStream_t s, const RareGate &rare, const SortReport &report) {
+    if (n >= RARE_LAUNCHES_MIN && n < RARE_LAUNCHES_MAX) {
+        PC_LAUNCH(K_FILL32, rare_gate_kernel, dim3(1), dim3(1), 0, s, rare);
+        return prev_next_core(keys, n, nullptr, prev, next, key_hist, k, bufs, s, rare.on, report);
+    }
+    Carver c{(char *)bufs, 0};
+    const PermPlan pp = plan_perm(n);
+    if (pp.buckets[0] > (uint64_t)LINK_RADIX) return PC_ERR_TOO_LARGE;
+    const SortJob j{keys, n, nullptr, key_hist, k, take_bufs(c, n), pp, device_cus(), true, rare};
+    const uint64_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
+    PC_LAUNCH(K_SORT_HIGH, sort_persistent_kernel, dim3(capped(tiles, 2)), dim3(SORT_THREADS), 0, s, j,
+              (const int32_t *)nullptr);
+    return perm_local(j, prev, next, s, rare.on, report);
 }
 
 }  // namespace pc
 
 extern "C" {
 
-size_t pc_prev_next_use_ws(uint64_t n) { return pc::carve_sort(nullptr, n).bytes; }
+size_t pc_prev_next_use_ws(uint64_t n) {
+    size_t ctl;
+    pc::sort_ctl(nullptr, n, &ctl);
+    return ctl + pc::sort_bufs_bytes(n);
+}
 
 pc_status pc_prev_next_use(const uint64_t *keys, uint64_t n, uint32_t *prev, uint32_t *next,
                            const uint32_t *key_hist, void *ws, size_t ws_bytes, void *stream) {
@@ -944,7 +1138,12 @@ pc_status pc_prev_next_use(const uint64_t *keys, uint64_t n, uint32_t *prev, uin
     if (n > 0 && (!keys || !prev || !next)) return PC_ERR_INVALID;
     if (!ws) return PC_ERR_WORKSPACE;
     if (ws_bytes < pc_prev_next_use_ws(n)) return PC_ERR_WORKSPACE;
-    return pc::prev_next_core(keys, n, nullptr, prev, next, key_hist, ws, (hipStream_t)stream, nullptr, false);
+    hipStream_t s = (hipStream_t)stream;
+    size_t ctl;
+    const pc::SortCtl k = pc::sort_ctl(ws, n, &ctl);
+    if (n == 0) return pc::fill_u32(reinterpret_cast<uint32_t *>(k.hdr), 0u, 1, s);
+    return pc::prev_next_core(keys, n, nullptr, prev, next, key_hist, k, (char *)ws + ctl, s, nullptr,
+                              pc::SortReport{});
 }
 
 }  // extern "C"

@@ -21,8 +21,8 @@
 //
 // Buckets are ranges of t, so their sizes are known in advance from the
 // per-4096 prefix of cold counts: #non-cold t < X = X - Z(X).
-//   * sd_cold_count + a three-step scan -> Z at every multiple of 4096
-//   * per level (1-3 levels of 8-bit digits above bit 12), over tiles of 1024
+//   * sd_cold_count + a two-step scan -> Z at every multiple of 4096
+//   * per level (1-3 levels of 8-bit digits above bit 12), over tiles of 2048
 //     elements: sd_count (per-tile digit counts), a segmented scan of those
 //     counts over the tiles of each bucket (sd_seg: reduce, carry, scan --
 //     no waiting on other workgroups), then sd_dominance_pass: one ballot
@@ -55,111 +55,101 @@ constexpr int LOC_PARTS = LOC_THREADS / 64;                    // column-prefix 
 constexpr int SCAN_THREADS = 1024;
 
 // number of non-cold accesses t < X (X a multiple of 4096, or X = n)
-__device__ __forceinline__ uint64_t cnt_lt(uint64_t X, const uint32_t *__restrict__ Zc) {
+__device__ __forceinline__ uint64_t cnt_lt(uint64_t X, const uint32_t *Zc) {
     return X - Zc[(X + LOCAL_SPAN - 1) >> LOCAL_BITS];
 }
 
-__global__ __launch_bounds__(256) void sd_cold_count_kernel(const uint32_t *__restrict__ prev,
-                                                            uint64_t n, uint32_t *__restrict__ cnt,
-                                                            const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t tmp[4];
-    constexpr int PER = LOCAL_SPAN / 256;   // 16 consecutive values per thread
-    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
-    for (uint64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
-    const uint64_t base = chunk * LOCAL_SPAN + (uint64_t)threadIdx.x * PER;
+// The steps below are functions of one chunk of their work, so that the
+// kernels (one launch per step) and the persistent kernel (all of them in one
+// launch, for callers that seldom need them) share them.
+
+// cold accesses of one 4096-range of t
+template <int THREADS>
+__device__ __forceinline__ void cold_count(const uint32_t *prev, uint64_t n, uint64_t chunk, uint32_t *cnt,
+                                           uint32_t *tmp) {
+    // 16-byte vectors, all in flight at once
+    constexpr int PER = LOCAL_SPAN / 4 / THREADS;
+    const uint64_t base = chunk * LOCAL_SPAN;
     uint32_t c = 0;
-    if (base + PER <= n && (reinterpret_cast<uintptr_t>(prev) & 15) == 0) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(prev + base);   // four 16-byte loads in flight
-        uint4 v[PER / 4];
+    if (base + LOCAL_SPAN <= n && (reinterpret_cast<uintptr_t>(prev) & 15) == 0) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(prev + base);
+        uint4 v[PER];
 #pragma unroll
-        for (int q = 0; q < PER / 4; ++q) v[q] = p[q];
+        for (int q = 0; q < PER; ++q) v[q] = p[threadIdx.x + q * THREADS];
 #pragma unroll
-        for (int q = 0; q < PER / 4; ++q)
+        for (int q = 0; q < PER; ++q)
             c += (v[q].x == NONE) + (v[q].y == NONE) + (v[q].z == NONE) + (v[q].w == NONE);
     } else {
-        for (int j = 0; j < PER; ++j) c += (base + j < n && prev[base + j] == NONE) ? 1u : 0u;
+        for (uint32_t j = threadIdx.x; j < LOCAL_SPAN; j += THREADS)
+            c += (base + j < n && prev[base + j] == NONE) ? 1u : 0u;
     }
     uint32_t total;
     block_excl_scan(c, tmp, &total);
     if (threadIdx.x == 0) cnt[chunk] = total;
-    }
 }
 
-// exclusive scan of m values (one workgroup); out[m] = total
-__global__ __launch_bounds__(SCAN_THREADS) void sd_scan_kernel(const uint32_t *__restrict__ in,
-                                                               uint64_t m,
-                                                               uint32_t *__restrict__ out,
-                                                               const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
-    const uint64_t seg = (m + SCAN_THREADS - 1) / SCAN_THREADS;
-    const uint64_t lo = threadIdx.x * seg;
-    const uint64_t hi = lo + seg < m ? lo + seg : m;
-    uint32_t s = 0;
-    for (uint64_t i = lo; i < hi; ++i) s += in[i];
-    uint32_t total;
-    uint32_t run = block_excl_scan(s, tmp, &total);
-    for (uint64_t i = lo; i < hi; ++i) {
-        const uint32_t x = in[i];
-        out[i] = run;
-        run += x;
-    }
-    if (threadIdx.x == 0) out[m] = total;
-}
-
-// Exclusive scan of m values over many workgroups (the per-4096 cold counts
-// number n / 4096): block sums, one workgroup scans the sums, every block
-// scans itself on top of its offset.  out[m] = total.
-constexpr int SCAN_BLOCK = SCAN_THREADS * 4;
-__global__ __launch_bounds__(SCAN_THREADS) void sd_scan_reduce_kernel(const uint32_t *__restrict__ in, uint64_t m,
-                                                                      uint32_t *__restrict__ part,
-                                                                      const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
-    const uint64_t i0 = (uint64_t)blockIdx.x * SCAN_BLOCK + (uint64_t)threadIdx.x * 4;
+// Exclusive scan of m values, SCAN_BLOCK per workgroup: block sums first (not
+// needed for a single block), then every block adds the sums before its own.
+// out[m] = total.
+constexpr int SCAN_BLOCK = 4096;
+__device__ __forceinline__ void scan_reduce(const uint32_t *in, uint64_t m, uint64_t block, uint32_t *part,
+                                            uint32_t *tmp) {
     uint32_t x = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) x += i0 + q < m ? in[i0 + q] : 0u;
+    for (uint32_t j = threadIdx.x; j < SCAN_BLOCK; j += blockDim.x) {
+        const uint64_t i = block * SCAN_BLOCK + j;
+        x += i < m ? in[i] : 0u;
+    }
     uint32_t total;
     block_excl_scan(x, tmp, &total);
-    if (threadIdx.x == 0) part[blockIdx.x] = total;
+    if (threadIdx.x == 0) part[block] = total;
 }
-
-__global__ __launch_bounds__(SCAN_THREADS) void sd_scan_apply_kernel(const uint32_t *__restrict__ in, uint64_t m,
-                                                                     const uint32_t *__restrict__ part_ex,
-                                                                     uint64_t nblocks, uint32_t *__restrict__ out,
-                                                                     const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
-    const uint64_t i0 = (uint64_t)blockIdx.x * SCAN_BLOCK + (uint64_t)threadIdx.x * 4;
-    uint32_t v[4], x = 0;
+template <int THREADS>
+__device__ __forceinline__ void scan_apply(const uint32_t *in, uint64_t m, uint64_t block, const uint32_t *part,
+                                           uint32_t *out, uint32_t *tmp) {
+    constexpr int PER = SCAN_BLOCK / THREADS;
+    uint32_t before = 0, base;
+    for (uint64_t j = threadIdx.x; j < block; j += THREADS) before += part[j];
+    block_excl_scan(before, tmp, &base);
+    const uint64_t i0 = block * SCAN_BLOCK + (uint64_t)threadIdx.x * PER;
+    uint32_t v[PER], x = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PER; ++q) {
         v[q] = i0 + q < m ? in[i0 + q] : 0u;
         x += v[q];
     }
     uint32_t total;
-    uint32_t run = part_ex[blockIdx.x] + block_excl_scan(x, tmp, &total);
+    uint32_t run = base + block_excl_scan(x, tmp, &total);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < PER; ++q) {
         if (i0 + q < m) out[i0 + q] = run;
         run += v[q];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[m] = part_ex[nblocks];
+    if (threadIdx.x == 0 && (block + 1) * SCAN_BLOCK >= m) out[m] = base + total;
 }
 
-// tiles per bucket of a dominance pass (bucket = t >> S)
-__global__ void sd_tile_count_kernel(const uint32_t *__restrict__ Zc, uint64_t n, int S,
-                                     uint64_t nbuckets, uint32_t *__restrict__ tcount, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbuckets) return;
+// non-cold accesses of bucket b (t >> S == b), in tiles
+__device__ __forceinline__ uint32_t bucket_tiles(const uint32_t *Zc, uint64_t n, int S, uint64_t b) {
     uint64_t lo = b << S, hi = (b + 1) << S;
     lo = lo < n ? lo : n;
     hi = hi < n ? hi : n;
     const uint64_t size = cnt_lt(hi, Zc) - cnt_lt(lo, Zc);
-    tcount[b] = (uint32_t)((size + DOM_TILE - 1) / DOM_TILE);
+    return (uint32_t)((size + DOM_TILE - 1) / DOM_TILE);
+}
+
+// One bucket of a level: its first tile (the tiles of the buckets before it;
+// there are at most a few thousand) and its tiles' entries in tile_bucket, so
+// that the level's steps need one load instead of a search.
+__device__ __forceinline__ void map_tiles(const uint32_t *Zc, uint64_t n, int S, uint64_t nbuckets, uint64_t b,
+                                          uint32_t *tfirst, uint32_t *tile_bucket, uint32_t *tmp) {
+    uint32_t before = 0, first;
+    for (uint64_t j = threadIdx.x; j < b; j += blockDim.x) before += bucket_tiles(Zc, n, S, j);
+    block_excl_scan(before, tmp, &first);
+    const uint32_t mine = bucket_tiles(Zc, n, S, b);
+    if (threadIdx.x == 0) {
+        tfirst[b] = first;
+        if (b + 1 == nbuckets) tfirst[nbuckets] = first + mine;
+    }
+    for (uint32_t j = threadIdx.x; j < mine; j += blockDim.x) tile_bucket[first + j] = (uint32_t)b;
 }
 
 // ---- one MSD level of the dominance count (8-bit digits of t) -----------
@@ -171,25 +161,10 @@ struct TileLoc {
     bool valid;
 };
 
-// tile -> bucket of a level (largest b with tfirst[b] <= tile), computed
-// once per level so the level's kernels need one load instead of a search
-__global__ void sd_tile_bucket_kernel(const uint32_t *__restrict__ tfirst, uint64_t nbuckets, uint64_t max_tiles,
-                                      uint32_t *__restrict__ tile_bucket, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    const uint64_t tile = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tile >= max_tiles || tile >= tfirst[nbuckets]) return;
-    uint64_t lo = 0, hi = nbuckets;
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (tfirst[mid] <= tile) lo = mid; else hi = mid;
-    }
-    tile_bucket[tile] = (uint32_t)lo;
-}
-
 template <bool FIRST>
-__device__ __forceinline__ TileLoc locate_tile(uint64_t tile, uint64_t n, const uint32_t *__restrict__ Zc,
-                                               int S, const uint32_t *__restrict__ tfirst, uint64_t nbuckets,
-                                               const uint32_t *__restrict__ tile_bucket) {
+__device__ __forceinline__ TileLoc locate_tile(uint64_t tile, uint64_t n, const uint32_t *Zc,
+                                               int S, const uint32_t *tfirst, uint64_t nbuckets,
+                                               const uint32_t *tile_bucket) {
     TileLoc L{0, 0, 0, 0, true};
     if (FIRST) {
         const uint64_t tiles = (n + DOM_TILE - 1) / DOM_TILE;
@@ -212,8 +187,8 @@ __device__ __forceinline__ TileLoc locate_tile(uint64_t tile, uint64_t n, const 
 }
 
 template <bool FIRST>
-__device__ __forceinline__ void load_tile(const TileLoc &L, const uint32_t *__restrict__ in_t,
-                                          const uint32_t *__restrict__ in_acc, int w, int lane,
+__device__ __forceinline__ void load_tile(const TileLoc &L, const uint32_t *in_t,
+                                          const uint32_t *in_acc, int w, int lane,
                                           uint32_t (&t)[DOM_CHUNKS_PER_WAVE], uint32_t (&acc)[DOM_CHUNKS_PER_WAVE],
                                           bool (&ok)[DOM_CHUNKS_PER_WAVE], bool want_acc) {
 #pragma unroll
@@ -241,14 +216,11 @@ __device__ __forceinline__ void load_tile(const TileLoc &L, const uint32_t *__re
 // cover the chain of dependent loads (tile -> bucket -> range -> elements).
 constexpr int COUNT_TPW = 4;
 template <bool FIRST>
-__global__ __launch_bounds__(DOM_THREADS) void sd_count_kernel(
-    const uint32_t *__restrict__ in_t, uint64_t n, const uint32_t *__restrict__ Zc, int s, int k,
-    const uint32_t *__restrict__ tfirst, uint64_t nbuckets, const uint32_t *__restrict__ tile_bucket,
-    uint16_t *__restrict__ cnt, uint8_t *__restrict__ seg, uint64_t groups, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t s_cnt[COUNT_TPW][DOM_RADIX];
+__device__ __forceinline__ bool count_tiles(const uint32_t *in_t, uint64_t n, const uint32_t *Zc, int s, int k,
+                                            const uint32_t *tfirst, uint64_t nbuckets, const uint32_t *tile_bucket,
+                                            uint16_t *cnt, uint8_t *seg, uint64_t grp,
+                                            uint32_t (*s_cnt)[DOM_RADIX]) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
     __syncthreads();   // the previous group's counts are written out
     const uint64_t tile0 = grp * COUNT_TPW;
     // an invalid tile (past the level's last) has an empty range: it loads
@@ -257,7 +229,7 @@ __global__ __launch_bounds__(DOM_THREADS) void sd_count_kernel(
 #pragma unroll
     for (int q = 0; q < COUNT_TPW; ++q)
         L[q] = locate_tile<FIRST>(tile0 + q, n, Zc, s + k, tfirst, nbuckets, tile_bucket);
-    if (!L[0].valid) break;   // every later group is past the level's last tile too
+    if (!L[0].valid) return false;   // every later group is past the level's last tile too
     for (int i = tid; i < COUNT_TPW * DOM_RADIX; i += DOM_THREADS) (&s_cnt[0][0])[i] = 0;
     uint32_t t[COUNT_TPW][DOM_CHUNKS_PER_WAVE], acc[DOM_CHUNKS_PER_WAVE];
     bool ok[COUNT_TPW][DOM_CHUNKS_PER_WAVE];
@@ -288,30 +260,31 @@ __global__ __launch_bounds__(DOM_THREADS) void sd_count_kernel(
         if (tid < DOM_RADIX) cnt[tile * DOM_RADIX + tid] = (uint16_t)s_cnt[q][tid];
         if (tid == 0) seg[tile] = FIRST ? (tile == 0) : (tile == L[q].first_tile);
     }
-    }
+    return true;
 }
 
 // Segmented exclusive scan over tiles, per digit (a bucket's first tile
-// restarts the sum), in three steps over groups of SEG_GROUP tiles.
-constexpr int SEG_GROUP = 256;
+// restarts the sum), in three steps over groups of tiles.  A group's tiles are
+// walked one after the other by one workgroup, so groups are small while there
+// are few tiles (16 tiles up to 16,384; at 489 tiles the steps took 58 us each
+// with groups of 256, two workgroups) and large enough afterwards that the
+// carry handles them 1024 at a time.
 constexpr int SEG_BATCH = 16;
+constexpr uint64_t SEG_GROUP_MAX = 256;
+static uint64_t seg_group(uint64_t tiles) {
+    uint64_t g = (tiles + 1023) / 1024;
+    g = (g + SEG_BATCH - 1) / SEG_BATCH * SEG_BATCH;
+    return g < (uint64_t)SEG_BATCH ? (uint64_t)SEG_BATCH : g < SEG_GROUP_MAX ? g : SEG_GROUP_MAX;
+}
 
 __device__ __forceinline__ uint64_t total_tiles(const uint32_t *tfirst_end, uint64_t fixed) {
     return tfirst_end ? (uint64_t)*tfirst_end : fixed;
 }
 
-// A: per group, the sum after its last bucket start, and whether it has one
-__global__ __launch_bounds__(DOM_RADIX) void sd_seg_reduce_kernel(const uint16_t *__restrict__ cnt,
-                                                                  const uint8_t *__restrict__ seg,
-                                                                  const uint32_t *tfirst_end, uint64_t fixed,
-                                                                  uint32_t *__restrict__ gsum,
-                                                                  uint8_t *__restrict__ ghas, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    const uint64_t rows = total_tiles(tfirst_end, fixed);
-    const uint64_t r0 = (uint64_t)blockIdx.x * SEG_GROUP;
-    if (r0 >= rows) return;
-    const uint64_t r1 = r0 + SEG_GROUP < rows ? r0 + SEG_GROUP : rows;
-    const int d = threadIdx.x;
+// A: per group (rows [r0, r1) of digit d), the sum after its last bucket start,
+// and whether it has one
+__device__ __forceinline__ void seg_reduce(const uint16_t *cnt, const uint8_t *seg, uint64_t r0, uint64_t r1, int d,
+                                           uint64_t grp, uint32_t *gsum, uint8_t *ghas) {
     uint32_t tail = 0;
     bool has = false;
     for (uint64_t r = r0; r < r1; r += SEG_BATCH) {
@@ -329,29 +302,21 @@ __global__ __launch_bounds__(DOM_RADIX) void sd_seg_reduce_kernel(const uint16_t
             tail += c[q];
         }
     }
-    gsum[blockIdx.x * DOM_RADIX + d] = tail;
-    if (d == 0) ghas[blockIdx.x] = has;
+    gsum[grp * DOM_RADIX + d] = tail;
+    if (d == 0) ghas[grp] = has;
 }
 
 // B: carry into every group: per digit (one workgroup each), a segmented
 // scan over the groups where a group holding a bucket start restarts the
 // sum.  Inside a wave: the plain prefix sum minus the sum before the last
 // start at or below the lane (found with a ballot); across the waves of a
-// 1024-group chunk and across chunks: a short serial carry.
-constexpr int CARRY_THREADS = 1024;
-__global__ __launch_bounds__(CARRY_THREADS) void sd_seg_carry_kernel(const uint32_t *__restrict__ gsum,
-                                                                     const uint8_t *__restrict__ ghas,
-                                                                     const uint32_t *tfirst_end, uint64_t fixed,
-                                                                     uint32_t *__restrict__ gin, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t s_val[CARRY_THREADS / WAVE];
-    __shared__ uint32_t s_has[CARRY_THREADS / WAVE];
-    const uint64_t rows = total_tiles(tfirst_end, fixed);
-    const uint64_t groups = (rows + SEG_GROUP - 1) / SEG_GROUP;
-    const int d = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
+// workgroup's chunk of groups and across chunks: a short serial carry.
+constexpr int CARRY_WAVES_MAX = 16;
+__device__ __forceinline__ void seg_carry(const uint32_t *gsum, const uint8_t *ghas, uint64_t groups, int d,
+                                          uint32_t *gin, uint32_t *s_val, uint32_t *s_has) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE, nw = (int)blockDim.x / WAVE;
     uint32_t carry = 0;   // carry into the current chunk
-    for (uint64_t g0 = 0; g0 < groups; g0 += CARRY_THREADS) {
+    for (uint64_t g0 = 0; g0 < groups; g0 += blockDim.x) {
         const uint64_t g = g0 + tid;
         const bool in = g < groups;
         const bool f = in && ghas[g];
@@ -370,7 +335,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void sd_seg_carry_kernel(const uint3
         uint32_t cin = carry;   // carry into this wave
         for (int x = 0; x < w; ++x) cin = s_has[x] ? s_val[x] : cin + s_val[x];
         uint32_t chunk_out = cin;
-        for (int x = w; x < CARRY_THREADS / WAVE; ++x) chunk_out = s_has[x] ? s_val[x] : chunk_out + s_val[x];
+        for (int x = w; x < nw; ++x) chunk_out = s_has[x] ? s_val[x] : chunk_out + s_val[x];
         const uint32_t incl = last >= 0 ? seg : cin + seg;   // carry after group g
         const uint32_t prev = (uint32_t)__shfl_up((int)incl, 1, WAVE);
         if (in) gin[g * DOM_RADIX + d] = lane == 0 ? cin : prev;
@@ -380,18 +345,9 @@ __global__ __launch_bounds__(CARRY_THREADS) void sd_seg_carry_kernel(const uint3
 }
 
 // C: per group, the exclusive prefix of every tile
-__global__ __launch_bounds__(DOM_RADIX) void sd_seg_scan_kernel(const uint16_t *__restrict__ cnt,
-                                                                const uint8_t *__restrict__ seg,
-                                                                const uint32_t *tfirst_end, uint64_t fixed,
-                                                                const uint32_t *__restrict__ gin,
-                                                                uint32_t *__restrict__ pre, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    const uint64_t rows = total_tiles(tfirst_end, fixed);
-    const uint64_t r0 = (uint64_t)blockIdx.x * SEG_GROUP;
-    if (r0 >= rows) return;
-    const uint64_t r1 = r0 + SEG_GROUP < rows ? r0 + SEG_GROUP : rows;
-    const int d = threadIdx.x;
-    uint32_t run = gin[blockIdx.x * DOM_RADIX + d];
+__device__ __forceinline__ void seg_scan(const uint16_t *cnt, const uint8_t *seg, uint64_t r0, uint64_t r1, int d,
+                                         uint64_t grp, const uint32_t *gin, uint32_t *pre) {
+    uint32_t run = gin[grp * DOM_RADIX + d];
     for (uint64_t r = r0; r < r1; r += SEG_BATCH) {
         uint32_t c[SEG_BATCH];
         bool f[SEG_BATCH];
@@ -417,37 +373,43 @@ __global__ __launch_bounds__(DOM_RADIX) void sd_seg_scan_kernel(const uint16_t *
 // tiles (the scanned counts), earlier chunks of the tile (2-D prefix over
 // (chunk, digit) in LDS) and earlier lanes of its chunk (ballot masks) --
 // and the tile is written out digit-partitioned through LDS.
-template <bool FIRST>
-__global__ __launch_bounds__(DOM_THREADS) void sd_dominance_kernel(
-    const uint32_t *__restrict__ in_t, const uint32_t *__restrict__ in_acc,
-    uint32_t *__restrict__ out_t, uint32_t *__restrict__ out_acc, uint64_t n,
-    const uint32_t *__restrict__ Zc, int s, int k, const uint32_t *__restrict__ tfirst,
-    uint64_t nbuckets, const uint32_t *__restrict__ tile_bucket, const uint32_t *__restrict__ pre,
-    int32_t *__restrict__ err, uint64_t ntiles, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    // chunk histograms -> column prefix; once every position is known, the
-    // staged tile (t, then acc) in the same space: 36 KB of LDS in all, so
-    // four workgroups share a CU
-    __shared__ uint16_t s_h[DOM_CHUNKS][DOM_RADIX];
-    __shared__ uint16_t s_pl[DOM_CHUNKS][DOM_RADIX];    // 2-D prefix (earlier chunks, smaller digit)
-    static_assert(sizeof(s_h) >= 2 * DOM_TILE * sizeof(uint32_t), "the stage fits the histograms");
-    uint32_t *s_st = reinterpret_cast<uint32_t *>(&s_h[0][0]);   // staged t
-    uint32_t *s_sa = s_st + DOM_TILE;                           // staged acc
+// LDS of the level: chunk histograms -> column prefix (h); once every position
+// is known, the staged tile (t, then acc) in the same space: 36 KB in all, so
+// four workgroups share a CU.
+struct DomLds {
+    uint16_t h[DOM_CHUNKS][DOM_RADIX];
+    uint16_t pl[DOM_CHUNKS][DOM_RADIX];    // 2-D prefix (earlier chunks, smaller digit)
     // per-digit tile starts and smaller-digit counts; before that, the two
     // half sums of the column prefix
-    __shared__ uint32_t s_part[2][DOM_RADIX];
-    uint32_t *s_lstart = s_part[0], *s_gl = s_part[1];
-    __shared__ uint32_t s_base[DOM_RADIX];
-    __shared__ uint32_t s_tmp[DOM_WAVES];
+    uint32_t part[2][DOM_RADIX];
+    uint32_t base[DOM_RADIX];
+    uint32_t tmp[DOM_WAVES];
+};
+static_assert(sizeof(DomLds::h) >= 2 * DOM_TILE * sizeof(uint32_t), "the stage fits the histograms");
 
-    const int tid = threadIdx.x;
+template <bool FIRST>
+__device__ __forceinline__ bool dominance_tile(DomLds &D, const uint32_t *in_t, const uint32_t *in_acc,
+                                               uint32_t *out_t, uint32_t *out_acc, uint64_t n, const uint32_t *Zc,
+                                               int s, int k, const uint32_t *tfirst, uint64_t nbuckets,
+                                               const uint32_t *tile_bucket, const uint32_t *pre, int32_t *err,
+                                               uint64_t tile) {
+    uint16_t(*s_h)[DOM_RADIX] = D.h;
+    uint16_t(*s_pl)[DOM_RADIX] = D.pl;
+    uint32_t(*s_part)[DOM_RADIX] = D.part;
+    uint32_t *s_base = D.base, *s_tmp = D.tmp;
+    uint32_t *s_st = reinterpret_cast<uint32_t *>(&s_h[0][0]);   // staged t
+    uint32_t *s_sa = s_st + DOM_TILE;                           // staged acc
+    uint32_t *s_lstart = s_part[0], *s_gl = s_part[1];
+    // (an opaque copy: in a loop over tiles what is derived from it is worked
+    // out per tile instead of being held across the loop)
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
     const int lane = tid & (WAVE - 1);
     const int w = tid / WAVE;
     const uint32_t dmask = (1u << k) - 1u;
-    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     __syncthreads();   // the previous tile has left the LDS
     const TileLoc L = locate_tile<FIRST>(tile, n, Zc, s + k, tfirst, nbuckets, tile_bucket);
-    if (!L.valid) break;   // every later tile is past the level's last too
+    if (!L.valid) return false;   // every later tile is past the level's last too
     // same digit, earlier tiles of the bucket (threads below RADIX own a digit)
     const uint32_t G = tid < DOM_RADIX ? pre[tile * DOM_RADIX + tid] : 0u;
     {
@@ -554,31 +516,34 @@ __global__ __launch_bounds__(DOM_THREADS) void sd_dominance_kernel(
             atomicOr(err, DEV_ERR_BAD_LAYOUT);
         }
     }
-    }
+    return true;
 }
 
 // Last 12 bits, one workgroup per 4096-range of t, then D in t order.  The
 // level-A counts go straight into a slot per t (acc included), so only the
 // six low bits of t are staged for level B, and the prev values needed at the
 // end are loaded up front; LDS stays under 40 KB (four workgroups per CU).
-__global__ __launch_bounds__(LOC_THREADS, 6) void sd_local_kernel(
-    const uint32_t *__restrict__ in_t, const uint32_t *__restrict__ in_acc,
-    const uint32_t *__restrict__ prev, uint64_t n, const uint32_t *__restrict__ Zc,
-    uint32_t *__restrict__ dist, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ uint32_t slot[LOCAL_SPAN];           // by t: acc + counts; first the column-prefix sums
-    __shared__ uint16_t s_h[LOC_CHUNKS][64];        // chunk histograms -> column prefix
-    __shared__ uint16_t s_pl[LOC_CHUNKS][64];       // 2-D prefix (earlier chunks, smaller digit)
-    __shared__ uint8_t s_low[LOCAL_SPAN];           // bits 0..5 of t, grouped by bits 6..11
-    __shared__ uint32_t s_lstart[65];
-    __shared__ uint32_t s_tmp[LOC_WAVES];
+struct LocalLds {
+    uint32_t slot[LOCAL_SPAN];           // by t: acc + counts; first the column-prefix sums
+    uint16_t h[LOC_CHUNKS][64];          // chunk histograms -> column prefix
+    uint16_t pl[LOC_CHUNKS][64];         // 2-D prefix (earlier chunks, smaller digit)
+    uint8_t low[LOCAL_SPAN];             // bits 0..5 of t, grouped by bits 6..11
+    uint32_t lstart[65];
+    uint32_t tmp[LOC_WAVES];
+};
+__device__ __forceinline__ void local_range(LocalLds &D, const uint32_t *in_t, const uint32_t *in_acc,
+                                            const uint32_t *prev, uint64_t n, const uint32_t *Zc, uint32_t *dist,
+                                            uint64_t chunk) {
+    uint32_t *slot = D.slot, *s_lstart = D.lstart, *s_tmp = D.tmp;
+    uint16_t(*s_h)[64] = D.h;
+    uint16_t(*s_pl)[64] = D.pl;
+    uint8_t *s_low = D.low;
     uint32_t(*s_part)[64] = reinterpret_cast<uint32_t(*)[64]>(slot);   // [LOC_PARTS][64]
 
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
     const int lane = tid & (WAVE - 1);
     const int w = tid / WAVE;
-    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
-    for (uint64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
     __syncthreads();   // the previous range has left the LDS
     const uint64_t r0 = chunk * LOCAL_SPAN;
     const uint64_t r1 = r0 + LOCAL_SPAN < n ? r0 + LOCAL_SPAN : n;
@@ -711,7 +676,98 @@ __global__ __launch_bounds__(LOC_THREADS, 6) void sd_local_kernel(
         for (int j = 0; j < PER; ++j)
             if (tbase + j < n) dist[tbase + j] = dv[j];
     }
-    }
+}
+
+// ---- one launch per step
+__global__ __launch_bounds__(256) void sd_cold_count_kernel(const uint32_t *__restrict__ prev, uint64_t n,
+                                                            uint32_t *__restrict__ cnt, int32_t *__restrict__ hdr, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t tmp[4];
+    if (hdr && blockIdx.x == 0 && threadIdx.x == 0) *hdr = 0;   // the call's status
+    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
+    for (uint64_t c = blockIdx.x; c < nchunks; c += gridDim.x) cold_count<256>(prev, n, c, cnt, tmp);
+}
+__global__ __launch_bounds__(SCAN_THREADS) void sd_scan_reduce_kernel(const uint32_t *__restrict__ in, uint64_t m,
+                                                                      uint32_t *__restrict__ part, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
+    scan_reduce(in, m, blockIdx.x, part, tmp);
+}
+__global__ __launch_bounds__(SCAN_THREADS) void sd_scan_apply_kernel(const uint32_t *__restrict__ in, uint64_t m,
+                                                                     const uint32_t *__restrict__ part,
+                                                                     uint32_t *__restrict__ out, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t tmp[SCAN_THREADS / WAVE];
+    scan_apply<SCAN_THREADS>(in, m, blockIdx.x, part, out, tmp);
+}
+__global__ __launch_bounds__(256) void sd_tile_map_kernel(const uint32_t *__restrict__ Zc, uint64_t n, int S,
+                                                          uint64_t nbuckets, uint32_t *__restrict__ tfirst,
+                                                          uint32_t *__restrict__ tile_bucket, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t tmp[4];
+    map_tiles(Zc, n, S, nbuckets, blockIdx.x, tfirst, tile_bucket, tmp);
+}
+template <bool FIRST>
+__global__ __launch_bounds__(DOM_THREADS) void sd_count_kernel(
+    const uint32_t *__restrict__ in_t, uint64_t n, const uint32_t *__restrict__ Zc, int s, int k,
+    const uint32_t *__restrict__ tfirst, uint64_t nbuckets, const uint32_t *__restrict__ tile_bucket,
+    uint16_t *__restrict__ cnt, uint8_t *__restrict__ seg, uint64_t groups, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t s_cnt[COUNT_TPW][DOM_RADIX];
+    for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x)
+        if (!count_tiles<FIRST>(in_t, n, Zc, s, k, tfirst, nbuckets, tile_bucket, cnt, seg, grp, s_cnt)) break;
+}
+__global__ __launch_bounds__(DOM_RADIX) void sd_seg_reduce_kernel(const uint16_t *__restrict__ cnt,
+                                                                  const uint8_t *__restrict__ seg,
+                                                                  const uint32_t *tfirst_end, uint64_t fixed,
+                                                                  uint64_t group, uint32_t *__restrict__ gsum,
+                                                                  uint8_t *__restrict__ ghas, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    const uint64_t rows = total_tiles(tfirst_end, fixed), r0 = blockIdx.x * group;
+    if (r0 < rows)
+        seg_reduce(cnt, seg, r0, r0 + group < rows ? r0 + group : rows, threadIdx.x, blockIdx.x, gsum, ghas);
+}
+__global__ __launch_bounds__(CARRY_WAVES_MAX *WAVE) void sd_seg_carry_kernel(const uint32_t *__restrict__ gsum,
+                                                                             const uint8_t *__restrict__ ghas,
+                                                                             const uint32_t *tfirst_end,
+                                                                             uint64_t fixed, uint64_t group,
+                                                                             uint32_t *__restrict__ gin, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t s_val[CARRY_WAVES_MAX], s_has[CARRY_WAVES_MAX];
+    const uint64_t rows = total_tiles(tfirst_end, fixed);
+    seg_carry(gsum, ghas, (rows + group - 1) / group, blockIdx.x, gin, s_val, s_has);
+}
+__global__ __launch_bounds__(DOM_RADIX) void sd_seg_scan_kernel(const uint16_t *__restrict__ cnt,
+                                                                const uint8_t *__restrict__ seg,
+                                                                const uint32_t *tfirst_end, uint64_t fixed,
+                                                                uint64_t group, const uint32_t *__restrict__ gin,
+                                                                uint32_t *__restrict__ pre, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    const uint64_t rows = total_tiles(tfirst_end, fixed), r0 = blockIdx.x * group;
+    if (r0 < rows)
+        seg_scan(cnt, seg, r0, r0 + group < rows ? r0 + group : rows, threadIdx.x, blockIdx.x, gin, pre);
+}
+template <bool FIRST>
+__global__ __launch_bounds__(DOM_THREADS) void sd_dominance_kernel(
+    const uint32_t *__restrict__ in_t, const uint32_t *__restrict__ in_acc, uint32_t *__restrict__ out_t,
+    uint32_t *__restrict__ out_acc, uint64_t n, const uint32_t *__restrict__ Zc, int s, int k,
+    const uint32_t *__restrict__ tfirst, uint64_t nbuckets, const uint32_t *__restrict__ tile_bucket,
+    const uint32_t *__restrict__ pre, int32_t *__restrict__ err, uint64_t ntiles, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ DomLds D;
+    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
+        if (!dominance_tile<FIRST>(D, in_t, in_acc, out_t, out_acc, n, Zc, s, k, tfirst, nbuckets, tile_bucket, pre,
+                                   err, tile))
+            break;
+}
+__global__ __launch_bounds__(LOC_THREADS, 6) void sd_local_kernel(
+    const uint32_t *__restrict__ in_t, const uint32_t *__restrict__ in_acc, const uint32_t *__restrict__ prev,
+    uint64_t n, const uint32_t *__restrict__ Zc, uint32_t *__restrict__ dist, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ LocalLds D;
+    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
+    for (uint64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x)
+        local_range(D, in_t, in_acc, prev, n, Zc, dist, chunk);
 }
 
 // ---- request-level residency --------------------------------------------
@@ -837,7 +893,7 @@ static SdPlan plan_sd(uint64_t n) {
 
 struct SdWs {
     int32_t *hdr;
-    uint32_t *cold, *Zc, *tcount, *tfirst, *part, *part_ex;
+    uint32_t *cold, *Zc, *part, *tfirst;
     uint32_t *at, *aa, *bt, *ba;
     uint16_t *cnt;
     uint8_t *seg, *ghas;
@@ -850,14 +906,16 @@ static SdWs carve_sd(void *ws, uint64_t n, const SdPlan &p) {
     Carver c{(char *)ws, 0};
     SdWs w;
     const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
-    const uint64_t groups = (p.max_grid + SEG_GROUP - 1) / SEG_GROUP;
+    uint64_t groups = 1;
+    for (int i = 0; i < p.passes; ++i) {
+        const uint64_t g = (p.grid[i] + seg_group(p.grid[i]) - 1) / seg_group(p.grid[i]);
+        if (g > groups) groups = g;
+    }
     w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
     w.cold = c.take<uint32_t>(nchunks + 1);
     w.Zc = c.take<uint32_t>(nchunks + 2);
     const uint64_t nblocks = (nchunks + SCAN_BLOCK - 1) / SCAN_BLOCK;
     w.part = c.take<uint32_t>(nblocks + 1);
-    w.part_ex = c.take<uint32_t>(nblocks + 2);
-    w.tcount = c.take<uint32_t>(p.max_buckets + 1);
     w.tfirst = c.take<uint32_t>(p.max_buckets + 2);
     w.at = c.take<uint32_t>(n);
     w.aa = c.take<uint32_t>(n);
@@ -866,100 +924,222 @@ static SdWs carve_sd(void *ws, uint64_t n, const SdPlan &p) {
     w.cnt = c.take<uint16_t>(p.max_grid * DOM_RADIX);
     w.seg = c.take<uint8_t>(p.max_grid);
     w.ghas = c.take<uint8_t>(groups);
-    w.gsum = c.take<uint32_t>(groups * DOM_RADIX);
-    w.gin = c.take<uint32_t>(groups * DOM_RADIX);
+    w.gsum = c.take<uint32_t>(DOM_RADIX);
+    w.gin = c.take<uint32_t>(DOM_RADIX);
     w.pre = c.take<uint32_t>(p.max_grid * DOM_RADIX);
     w.tile_bucket = c.take<uint32_t>(p.max_grid);
     w.bytes = c.off;
     return w;
 }
 
-// Workgroups per CU of the loops over tiles: enough that each takes only a
-// few tiles (one tile per workgroup balances best: a static share of many
-// tiles ran the dominance passes 25% slower), few enough that a launch gated
-// off costs little.
-constexpr int SD_GRID_PER_CU = 64;
-
-// Z at every multiple of 4096 from the cold (prev = none) flags
-static pc_status sd_cold_prefix(const uint32_t *prev, uint64_t n, SdWs &w, hipStream_t s, const int32_t *gate) {
-    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
-    PC_LAUNCH(K_SD_COLD, sd_cold_count_kernel, dim3(capped(nchunks, SD_GRID_PER_CU)), dim3(256), 0, s, prev, n,
-              w.cold, gate);
-    const uint64_t nblocks = (nchunks + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    PC_LAUNCH(K_SD_SCAN, sd_scan_reduce_kernel, dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, w.cold, nchunks,
-              w.part, gate);
-    PC_LAUNCH(K_SD_SCAN, sd_scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, w.part, nblocks, w.part_ex, gate);
-    PC_LAUNCH(K_SD_SCAN, sd_scan_apply_kernel, dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, w.cold, nchunks,
-              w.part_ex, nblocks, w.Zc, gate);
-    return PC_OK;
+// A level's group sums and carries: with more than one group they lie in the
+// level's output acc array, which is written only after they are used (there
+// are at least 4096 accesses then, and 32 per word needed).
+struct SegSpace {
+    uint32_t *gsum, *gin;
+};
+__host__ __device__ inline SegSpace seg_space(const SdWs &w, uint32_t *out_acc, uint64_t groups) {
+    if (groups <= 1) return SegSpace{w.gsum, w.gin};
+    return SegSpace{out_acc, out_acc + groups * DOM_RADIX};
 }
 
-// The MSD dominance levels over the elements listed in `first` (time t of
-// each element, PC_NONE for a slot without one), in the order whose
-// dominance count is wanted.  Leaves (t, acc) partitioned by t's 4096-range.
-static pc_status sd_levels(const uint32_t *first, uint64_t n, const SdPlan &p, SdWs &w, hipStream_t s,
-                           uint32_t **out_t, uint32_t **out_a, const int32_t *gate) {
+// Workgroups per CU of the loops over tiles: enough that each takes only a
+// few tiles (one tile per workgroup balances best: a static share of many
+// tiles ran the dominance passes 25% slower).
+constexpr int SD_GRID_PER_CU = 64;
+
+// The dominance count, one launch per step, each gated; errors go to *err
+// (nullptr: the workspace header, cleared here).
+static pc_status stack_distance_steps(const uint32_t *prev, const uint32_t *next, uint64_t n, uint32_t *dist,
+                                      void *ws, hipStream_t s, const int32_t *gate, int32_t *err) {
+    const SdPlan p = plan_sd(n);
+    const SdWs w = carve_sd(ws, n, p);
+    if (n == 0) return fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, 1, s);
+    // Z at every multiple of 4096 from the cold (prev = none) flags
+    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
+    const uint64_t nblocks = (nchunks + SCAN_BLOCK - 1) / SCAN_BLOCK;
+    PC_LAUNCH(K_SD_COLD, sd_cold_count_kernel, dim3(capped(nchunks, SD_GRID_PER_CU)), dim3(256), 0, s, prev, n,
+              w.cold, err ? nullptr : w.hdr, gate);
+    if (!err) err = w.hdr;
+    if (nblocks > 1)
+        PC_LAUNCH(K_SD_SCAN, sd_scan_reduce_kernel, dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s,
+                  (const uint32_t *)w.cold, nchunks, w.part, gate);
+    PC_LAUNCH(K_SD_SCAN, sd_scan_apply_kernel, dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s,
+              (const uint32_t *)w.cold, nchunks, (const uint32_t *)w.part, w.Zc, gate);
+    // The MSD levels over next[] in index order (PC_NONE: no element), leaving
+    // (t, acc) partitioned by t's 4096-range.
     uint32_t *src_t = nullptr, *src_a = nullptr;
     for (int i = 0; i < p.passes; ++i) {
         uint32_t *dt = (i & 1) ? w.bt : w.at;
         uint32_t *da = (i & 1) ? w.ba : w.aa;
         const int S = p.s[i] + p.k[i];
-        const uint64_t ntiles = p.grid[i];
-        const uint64_t cgroups = (p.grid[i] + COUNT_TPW - 1) / COUNT_TPW;
-        const unsigned groups = (unsigned)((p.grid[i] + SEG_GROUP - 1) / SEG_GROUP);
+        const uint64_t ntiles = p.grid[i], nb = p.nbuckets[i], group = seg_group(ntiles);
+        const uint64_t cgroups = (ntiles + COUNT_TPW - 1) / COUNT_TPW;
+        const unsigned groups = (unsigned)((ntiles + group - 1) / group);
         const unsigned grid = capped(ntiles, SD_GRID_PER_CU), cgrid = capped(cgroups, SD_GRID_PER_CU);
         const uint64_t fixed = (n + DOM_TILE - 1) / DOM_TILE;
         if (i == 0) {
-            PC_LAUNCH(K_SD_COUNT, sd_count_kernel<true>, dim3(cgrid), dim3(DOM_THREADS), 0, s, first, n, w.Zc,
+            PC_LAUNCH(K_SD_COUNT, sd_count_kernel<true>, dim3(cgrid), dim3(DOM_THREADS), 0, s, next, n, w.Zc,
                       p.s[i], p.k[i], (const uint32_t *)nullptr, (uint64_t)1, (const uint32_t *)nullptr, w.cnt, w.seg,
                       cgroups, gate);
         } else {
-            const uint64_t nb = p.nbuckets[i];
-            PC_LAUNCH(K_SD_TILES, sd_tile_count_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, w.Zc,
-                      n, S, nb, w.tcount, gate);
-            PC_LAUNCH(K_SD_SCAN, sd_scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, w.tcount, nb, w.tfirst, gate);
-            PC_LAUNCH(K_SD_TILES, sd_tile_bucket_kernel, dim3((unsigned)((p.grid[i] + 255) / 256)), dim3(256), 0,
-                      s, w.tfirst, nb, p.grid[i], w.tile_bucket, gate);
+            PC_LAUNCH(K_SD_TILES, sd_tile_map_kernel, dim3((unsigned)nb), dim3(256), 0, s, (const uint32_t *)w.Zc, n,
+                      S, nb, w.tfirst, w.tile_bucket, gate);
             PC_LAUNCH(K_SD_COUNT, sd_count_kernel<false>, dim3(cgrid), dim3(DOM_THREADS), 0, s, src_t, n, w.Zc,
                       p.s[i], p.k[i], w.tfirst, nb, w.tile_bucket, w.cnt, w.seg, cgroups, gate);
         }
-        const uint32_t *tend = i == 0 ? nullptr : w.tfirst + p.nbuckets[i];
+        const uint32_t *tend = i == 0 ? nullptr : w.tfirst + nb;
+        const SegSpace g = seg_space(w, da, groups);
         PC_LAUNCH(K_SD_SEG, sd_seg_reduce_kernel, dim3(groups), dim3(DOM_RADIX), 0, s, w.cnt, w.seg, tend, fixed,
-                  w.gsum, w.ghas, gate);
-        PC_LAUNCH(K_SD_SEG, sd_seg_carry_kernel, dim3(DOM_RADIX), dim3(CARRY_THREADS), 0, s, w.gsum, w.ghas, tend,
-                  fixed, w.gin, gate);
-        PC_LAUNCH(K_SD_SEG, sd_seg_scan_kernel, dim3(groups), dim3(DOM_RADIX), 0, s, w.cnt, w.seg, tend, fixed,
-                  w.gin, w.pre, gate);
+                  group, g.gsum, w.ghas, gate);
+        const unsigned carry = groups < CARRY_WAVES_MAX * WAVE ? (groups + WAVE - 1) / WAVE * WAVE : CARRY_WAVES_MAX * WAVE;
+        PC_LAUNCH(K_SD_SEG, sd_seg_carry_kernel, dim3(DOM_RADIX), dim3(carry), 0, s, g.gsum, w.ghas, tend, fixed,
+                  group, g.gin, gate);
+        PC_LAUNCH(K_SD_SEG, sd_seg_scan_kernel, dim3(groups), dim3(DOM_RADIX), 0, s, w.cnt, w.seg, tend, fixed, group,
+                  g.gin, w.pre, gate);
         if (i == 0) {
-            PC_LAUNCH(K_SD_PASS, sd_dominance_kernel<true>, dim3(grid), dim3(DOM_THREADS), 0, s, first,
+            PC_LAUNCH(K_SD_PASS, sd_dominance_kernel<true>, dim3(grid), dim3(DOM_THREADS), 0, s, next,
                       (const uint32_t *)nullptr, dt, da, n, w.Zc, p.s[i], p.k[i], (const uint32_t *)nullptr,
-                      (uint64_t)1, (const uint32_t *)nullptr, w.pre, w.hdr, ntiles, gate);
+                      (uint64_t)1, (const uint32_t *)nullptr, w.pre, err, ntiles, gate);
         } else {
             PC_LAUNCH(K_SD_PASS, sd_dominance_kernel<false>, dim3(grid), dim3(DOM_THREADS), 0, s, src_t, src_a, dt,
-                      da, n, w.Zc, p.s[i], p.k[i], w.tfirst, p.nbuckets[i], w.tile_bucket, w.pre, w.hdr, ntiles, gate);
+                      da, n, w.Zc, p.s[i], p.k[i], w.tfirst, nb, w.tile_bucket, w.pre, err, ntiles, gate);
         }
         src_t = dt;
         src_a = da;
     }
-    *out_t = src_t;
-    *out_a = src_a;
+    PC_LAUNCH(K_SD_LOCAL, sd_local_kernel, dim3(capped(nchunks, SD_GRID_PER_CU)), dim3(LOC_THREADS), 0, s, src_t, src_a,
+              prev, n, w.Zc, dist, gate);
     return PC_OK;
 }
 
-// The whole dominance count; with a gate, every launch is skipped on the
-// device unless the gate word is non-zero.
-pc_status stack_distance_gated(const uint32_t *prev, const uint32_t *next, uint64_t n, uint32_t *dist, void *ws,
-                               hipStream_t s, const int32_t *gate) {
-    const SdPlan p = plan_sd(n);
-    SdWs w = carve_sd(ws, n, p);
-    pc_status st = fill_u32_gated(reinterpret_cast<uint32_t *>(w.hdr), 0u, 1, s, gate);
-    if (st != PC_OK || n == 0) return st;
-    if ((st = sd_cold_prefix(prev, n, w, s, gate)) != PC_OK) return st;
-    uint32_t *lt, *la;
-    if ((st = sd_levels(next, n, p, w, s, &lt, &la, gate)) != PC_OK) return st;
-    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN;
-    PC_LAUNCH(K_SD_LOCAL, sd_local_kernel, dim3(capped(nchunks, SD_GRID_PER_CU)), dim3(LOC_THREADS), 0, s, lt, la,
-              prev, n, w.Zc, dist, gate);
+// ---- all steps in one launch, for the fallback behind the count over runs --
+// The choice between the two is made on the device, and a launch that its gate
+// turns off costs about 4.5 us in the stream, so up to SD_PERSISTENT_MAX
+// accesses the ten or so steps are the phases of one persistent kernel: a
+// phase hands out its chunks from a counter and counts the finished ones, and
+// a workgroup goes on once all are finished.  One workgroup per CU: the ends
+// of the phases cost about as much as launches then, and less than a tenth of
+// what they cost with four (3.0e6 random accesses 0.37 ms, 0.39 as launches,
+// 1.14 with four).  Larger calls keep the launches: one workgroup per CU is
+// too slow for the tiles (3.0e7: 1.42 against 0.89 ms), and 70 us of gated
+// launches are little beside the rest of such a step.
+constexpr uint64_t SD_PERSISTENT_MAX = 1ull << 22;
+struct SdJob {
+    const uint32_t *prev, *next;
+    uint32_t *dist;
+    uint64_t n;
+    SdPlan p;
+    SdWs w;
+    uint64_t group[4];
+    uint32_t *ctl;        // two zeroed words per phase
+    int32_t *status;      // the caller's status word
+};
+constexpr int SD_PHASES = 3 + 4 * 6 + 1;
+static_assert(2 * SD_PHASES <= SD_CTL_WORDS, "two control words per phase");
+
+union SdPersistentLds {
+    DomLds dom;
+    LocalLds local;
+    uint32_t cnt[COUNT_TPW][DOM_RADIX];
+};
+
+__global__ __launch_bounds__(DOM_THREADS, 4) void sd_persistent_kernel(SdJob j, const int32_t *gate) {
+    static_assert(DOM_THREADS == LOC_THREADS, "one workgroup size for all phases");
+    if (gated_off(gate)) return;
+    __shared__ SdPersistentLds L;
+    __shared__ uint32_t s_tmp[DOM_WAVES], s_has[DOM_WAVES], s_word;
+    const uint64_t n = j.n;
+    int phase = 0;
+    // f(chunk) over [0, chunks), then wait until every workgroup's are done; a
+    // workgroup takes a few chunks at a time, since the counter answers one
+    // workgroup after the other (about 10 ns each)
+    auto run = [&](uint64_t chunks, auto &&f) {
+        uint32_t *c = j.ctl + 2 * phase++;
+        uint32_t mine = 0;
+        uint64_t take = chunks / (4ull * gridDim.x);
+        take = take < 1 ? 1 : take > 8 ? 8 : take;
+        for (;;) {
+            __syncthreads();
+            if (threadIdx.x == 0) s_word = atomicAdd(&c[0], (uint32_t)take);
+            __syncthreads();
+            const uint64_t x = s_word;
+            if (x >= chunks) break;
+            for (uint64_t y = x; y < x + take && y < chunks; ++y) {
+                if (y > x) __syncthreads();
+                f(y);
+                ++mine;
+            }
+        }
+        finish_phase(&c[1], mine, (uint32_t)chunks, j.status);
+    };
+    const SdWs &w = j.w;
+    const uint64_t nchunks = (n + LOCAL_SPAN - 1) / LOCAL_SPAN, nblocks = (nchunks + SCAN_BLOCK - 1) / SCAN_BLOCK;
+    run(nchunks, [&](uint64_t c) { cold_count<DOM_THREADS>(j.prev, n, c, w.cold, s_tmp); });
+    run(nblocks, [&](uint64_t c) { scan_reduce(w.cold, nchunks, c, w.part, s_tmp); });
+    run(nblocks, [&](uint64_t c) { scan_apply<DOM_THREADS>(w.cold, nchunks, c, w.part, w.Zc, s_tmp); });
+    const uint32_t *src_t = j.next, *src_a = nullptr;
+#pragma unroll 1
+    for (int i = 0; i < j.p.passes; ++i) {
+        uint32_t *dt = (i & 1) ? w.bt : w.at, *da = (i & 1) ? w.ba : w.aa;
+        const int s = j.p.s[i], k = j.p.k[i];
+        const uint64_t nb = j.p.nbuckets[i], group = j.group[i];
+        if (i > 0) run(nb, [&](uint64_t c) { map_tiles(w.Zc, n, s + k, nb, c, w.tfirst, w.tile_bucket, s_tmp); });
+        else ++phase;
+        const uint64_t rows = i > 0 ? (uint64_t)ld_status(&w.tfirst[nb]) : (n + DOM_TILE - 1) / DOM_TILE;
+        const uint64_t groups = (rows + group - 1) / group;
+        const SegSpace g0 = seg_space(w, da, groups);
+        run((rows + COUNT_TPW - 1) / COUNT_TPW, [&](uint64_t c) {
+            if (i == 0) count_tiles<true>(src_t, n, w.Zc, s, k, nullptr, 1, nullptr, w.cnt, w.seg, c, L.cnt);
+            else count_tiles<false>(src_t, n, w.Zc, s, k, w.tfirst, nb, w.tile_bucket, w.cnt, w.seg, c, L.cnt);
+        });
+        // (a digit per thread: two groups at a time)
+        const int d = (int)threadIdx.x & (DOM_RADIX - 1);
+        auto rows_of = [&](uint64_t g, uint64_t *r0, uint64_t *r1) {
+            *r0 = g * group;
+            *r1 = *r0 + group < rows ? *r0 + group : rows;
+            return *r0 < rows;
+        };
+        run((groups + 1) / 2, [&](uint64_t c) {
+            const uint64_t g = 2 * c + threadIdx.x / DOM_RADIX;
+            uint64_t r0, r1;
+            if (rows_of(g, &r0, &r1)) seg_reduce(w.cnt, w.seg, r0, r1, d, g, g0.gsum, w.ghas);
+        });
+        run(DOM_RADIX, [&](uint64_t c) { seg_carry(g0.gsum, w.ghas, groups, (int)c, g0.gin, s_tmp, s_has); });
+        run((groups + 1) / 2, [&](uint64_t c) {
+            const uint64_t g = 2 * c + threadIdx.x / DOM_RADIX;
+            uint64_t r0, r1;
+            if (rows_of(g, &r0, &r1)) seg_scan(w.cnt, w.seg, r0, r1, d, g, g0.gin, w.pre);
+        });
+        run(rows, [&](uint64_t c) {
+            if (i == 0)
+                dominance_tile<true>(L.dom, src_t, nullptr, dt, da, n, w.Zc, s, k, nullptr, 1, nullptr, w.pre,
+                                     j.status, c);
+            else
+                dominance_tile<false>(L.dom, src_t, src_a, dt, da, n, w.Zc, s, k, w.tfirst, nb, w.tile_bucket, w.pre,
+                                      j.status, c);
+        });
+        src_t = dt;
+        src_a = da;
+    }
+    run(nchunks, [&](uint64_t c) { local_range(L.local, src_t, src_a, j.prev, n, w.Zc, j.dist, c); });
+}
+
+pc_status stack_distance_rare(const uint32_t *prev, const uint32_t *next, uint64_t n, uint32_t *dist, void *ws,
+                              uint32_t *ctl, hipStream_t s, const int32_t *gate, int32_t *status) {
+    if (n > SD_PERSISTENT_MAX) return stack_distance_steps(prev, next, n, dist, ws, s, gate, status);
+    SdJob j;
+    j.prev = prev;
+    j.next = next;
+    j.dist = dist;
+    j.n = n;
+    j.p = plan_sd(n);
+    j.w = carve_sd(ws, n, j.p);
+    for (int i = 0; i < j.p.passes; ++i) j.group[i] = seg_group(j.p.grid[i]);
+    j.ctl = ctl;
+    j.status = status;
+    const uint64_t tiles = (n + DOM_TILE - 1) / DOM_TILE;
+    PC_LAUNCH(K_SD_PASS, sd_persistent_kernel, dim3(capped(tiles, 1)), dim3(DOM_THREADS), 0, s, j, gate);
     return PC_OK;
 }
 
@@ -978,7 +1158,7 @@ pc_status pc_stack_distance(const uint32_t *prev, const uint32_t *next, uint64_t
     if (n > 0 && (!prev || !next || !dist)) return PC_ERR_INVALID;
     if (!ws) return PC_ERR_WORKSPACE;
     if (ws_bytes < pc_stack_distance_ws(n)) return PC_ERR_WORKSPACE;
-    return pc::stack_distance_gated(prev, next, n, dist, ws, (hipStream_t)stream, nullptr);
+    return pc::stack_distance_steps(prev, next, n, dist, ws, (hipStream_t)stream, nullptr, nullptr);
 }
 
 size_t pc_request_order_ws(void) { return pc::WS_HEADER; }

@@ -30,39 +30,31 @@ COPY_GRID = 131072            # the calibration copy's grid (4 GiB of int32)
 COPY_KIB = 4 * 1024 * 1024    # KiB it reads and writes
 
 # library kernel -> the kernel id the bench and the library's timers use
-IDS = {"pc::hash_fused_kernel": "hash_blocks",
-       "pc::sort_hist_kernel": "sort_digit_hist", "pc::sort_scan_kernel": "sort_digit_scan",
+IDS = {"pc::hash_kernel": "hash_blocks",
+       "pc::sort_hist_kernel": "sort_digit_hist", "pc::sort_persistent_kernel": "sort_high_bits",
        "pc::sort_pass_kernel": "sort_onesweep_pass", "pc::link_partition_kernel": "link_partition",
        "pc::perm_partition_kernel": "perm_partition", "pc::perm_local_kernel": "perm_local",
-       "pc::perm_cursor_kernel": "fill_u32", "pc::fill_u32_kernel": "fill_u32",
-       "pc::fill_u32_gated_kernel": "fill_u32",
-       "pc::sd_cold_count_kernel": "sd_cold_count", "pc::sd_scan_kernel": "sd_scan",
+       "pc::sort_init_kernel": "fill_u32", "pc::rare_gate_kernel": "fill_u32", "pc::fill_u32_kernel": "fill_u32",
+       "pc::fill_all_kernel": "fill_u32",
+       "pc::sd_cold_count_kernel": "sd_cold_count", "pc::sd_persistent_kernel": "sd_scan",
        "pc::sd_scan_reduce_kernel": "sd_scan", "pc::sd_scan_apply_kernel": "sd_scan",
-       "pc::sd_tile_count_kernel": "sd_tile_map", "pc::sd_tile_bucket_kernel": "sd_tile_map",
-       "pc::sd_count_kernel<true>": "sd_count", "pc::sd_count_kernel<false>": "sd_count",
+       "pc::sd_tile_map_kernel": "sd_tile_map", "pc::sd_count_kernel": "sd_count",
        "pc::sd_seg_reduce_kernel": "sd_seg_scan", "pc::sd_seg_carry_kernel": "sd_seg_scan",
-       "pc::sd_seg_scan_kernel": "sd_seg_scan",
-       "pc::sd_dominance_kernel<true>": "sd_dominance_pass", "pc::sd_dominance_kernel<false>": "sd_dominance_pass",
-       "pc::sd_local_kernel": "sd_local_finish", "pc::mrc_hist_kernel": "mrc_hist", "pc::mrc_cost_kernel": "mrc_cost",
+       "pc::sd_seg_scan_kernel": "sd_seg_scan", "pc::sd_dominance_kernel": "sd_dominance_pass",
+       "pc::sd_local_kernel": "sd_local_finish", "pc::mrc_hist_kernel": "mrc_hist",
        "pc::mrc_map_kernel": "mrc_map",
        "pc::req_order_kernel": "request_order", "pc::req_dist_kernel": "request_distance",
        "pc::sess_dist_kernel": "session_distance", "pc::sess_profile_kernel": "session_profile",
        "pc::prof_pack_kernel": "reuse_profile_pack", "pc::prof_walk_kernel": "reuse_profile_walk",
        "pc::sess_page_kernel": "session_requests", "pc::sess_keys_kernel": "session_requests",
        "pc::sess_status_kernel": "session_requests", "pc::sess_footprint_kernel": "session_requests",
-       "pc::chain_layout_kernel": "chain_anchor", "pc::chain_open_kernel": "chain_anchor",
        "pc::chain_anchor_kernel": "chain_anchor", "pc::chain_stair_kernel": "chain_stair",
-       "pc::chain_count_kernel": "chain_scan", "pc::chain_scan_tiles_kernel": "chain_scan",
-       "pc::chain_scan_top_kernel": "chain_scan", "pc::chain_scan_apply_kernel": "chain_scan",
-       "pc::chain_decide_kernel": "chain_scan", "pc::chain_compact_kernel": "chain_compact",
-       "pc::chain_merge_kernel": "chain_merge", "pc::chain_verdict_kernel": "chain_merge",
-       "pc::chain_status_kernel": "fill_u32", "pc::runs_count_kernel": "runs_count",
-       "pc::runs_scan_tiles_kernel": "runs_scan", "pc::runs_scan_top_kernel": "runs_scan",
-       "pc::runs_scan_apply_kernel": "runs_scan", "pc::runs_decide_kernel": "runs_scan",
-       "pc::runs_compact_kernel": "runs_compact", "pc::runs_init_kernel": "runs_merge",
-       "pc::runs_merge_kernel": "runs_merge", "pc::runs_dist_kernel": "runs_merge",
-       "pc::runs_fill_kernel": "runs_fill", "pc::runs_status_kernel": "fill_u32",
-       "pc::belady_kernel": "belady"}
+       "pc::chain_count_kernel": "chain_scan", "pc::chain_scan_kernel": "chain_scan",
+       "pc::chain_compact_kernel": "chain_compact", "pc::chain_merge_kernel": "chain_merge",
+       "pc::runs_count_kernel": "runs_count", "pc::runs_scan_tiles_kernel": "runs_scan",
+       "pc::runs_scan_kernel": "runs_scan", "pc::runs_compact_kernel": "runs_compact",
+       "pc::runs_block_kernel": "runs_merge", "pc::runs_merge_kernel": "runs_merge",
+       "pc::runs_fill_kernel": "runs_fill", "pc::belady_kernel": "belady"}
 
 
 def kernel_name(s):
