@@ -493,7 +493,7 @@ def main():
     if mt:
         mt["GBps_at_this_run"] = round(roof["traffic"] / (d["avg_working_launch_ms"] / 1e3) / 1e9, 1)
     roof["traffic_detail"] = mt
-    stage_of = {"hash_blocks": "hash", "sort_digit_hist": "prev_next",
+    stage_of = {"hash_blocks": "hash", "hash_order": "hash", "sort_digit_hist": "prev_next",
                 "sort_high_bits": "prev_next", "sort_onesweep_pass": "prev_next",
                 "link_partition": "prev_next",
                 "perm_partition": "prev_next", "perm_local": "prev_next", "chain_anchor": "prev_next",

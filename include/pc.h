@@ -98,6 +98,9 @@ int pc_version(void);
  *              request's range, i.e. block b goes to blk_off[r+1] - 1 - b
  *              (the recency order of request-level residency; the same as
  *              pc_request_order applied afterwards).
+ * The workspace holds the requests' table in the order of their length, so
+ * that the longest chains start first; with less than pc_hash_blocks_ws bytes,
+ * but at least 512, they are taken as they come.
  * A request whose tokens run past n_tokens, or whose blocks run past
  * n_blocks, is skipped and the workspace status (pc_workspace_status) is set
  * to 2; nothing is read or written out of bounds.

@@ -11,6 +11,7 @@ static const char *kernel_name(KernelId k) {
     switch (k) {
     case K_FILL32: return "fill_u32";
     case K_HASH: return "hash_blocks";
+    case K_HASH_ORDER: return "hash_order";
     case K_SORT_HIST: return "sort_digit_hist";
     case K_SORT_HIGH: return "sort_high_bits";
     case K_SORT_PASS: return "sort_onesweep_pass";

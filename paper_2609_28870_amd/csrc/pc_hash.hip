@@ -18,8 +18,9 @@
 // tiles (digests, turned into keys in place), and one barrier ends a phase.
 // The chain wave also plans the rounds: it takes requests from a global
 // counter, last to first (contexts grow turn by turn, so the longest chains
-// start first), two rounds ahead of the digests, with the counter's answer
-// and the request's table entries fetched while it chains.
+// come early; where it pays the requests are sorted by length first), two
+// rounds ahead of the digests, with the counter's answer and the request's
+// table entries fetched while it chains.
 //
 // Bound: the token reads where there are many requests (64 token bytes in
 // and 8 key bytes out per 16-token block), the longest request's chain where
@@ -118,10 +119,10 @@ constexpr int HASH_THREADS = (1 + DIGEST_WAVES) * WAVE;
 constexpr int HASH_SWEEPS = 8;                                       // most sweeps (64 blocks) per digest wave and round
 constexpr int HASH_ENTRIES = HASH_SWEEPS * DIGEST_WAVES * WAVE;      // most blocks per round: rows x SPAN
 constexpr int HASH_RING = 4;                                         // token chunks in flight per digest wave
-// Two workgroups per CU are enough to keep the vector units and the memory
+// At most two workgroups per CU: they keep the vector units and the memory
 // busy; with three or four the waves held each other up (on 2.2e8 accesses
-// 2.62, 2.75 and 2.79 ms; with one 3.27; on 2.8e7, where the longest chain
-// counts, 0.81, 0.97 and 1.16 ms).
+// 2.10 ms, with three 2.35; on 2.8e7, where the longest chain counts, 0.66 and
+// 0.83 ms).
 constexpr int HASH_WG_PER_CU = 2;
 static_assert(HASH_SWEEPS % HASH_RING == 0, "a round's chunks fill the ring a whole number of times");
 
@@ -134,7 +135,7 @@ struct RoundRow {
 
 template <int SPAN>
 struct HashLds {
-    static constexpr int ROWS = HASH_ENTRIES / SPAN;
+    static constexpr int ROWS = HASH_ENTRIES / SPAN < WAVE ? HASH_ENTRIES / SPAN : WAVE;
     static constexpr int ROW = SPAN + 1;         // padded: a lane per row reads without bank conflicts
     uint64_t tile[2][ROWS * ROW];                // round r in tile r mod 2
     RoundRow rows[2][ROWS];                      // round r in rows[r mod 2]
@@ -201,7 +202,9 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         // without the counter, neighbours (often equally long) to different
         // workgroups; later ones are taken `take` at a time.
         const uint32_t dealt = gridDim.x * (uint32_t)lanes;
-        const uint32_t take = (uint32_t)lanes > 2 ? (uint32_t)lanes / 2 : 1u;
+        // (short requests: a row may need one each round)
+        const bool brief = n_blocks / n_seqs < (uint64_t)SPAN;
+        const uint32_t take = brief || lanes < 2 ? (uint32_t)lanes : (uint32_t)lanes / 2;
         uint32_t pool = 0, pool_end = 0;      // counter range in hand
         bool asking = false, exhausted = dealt >= n_seqs;
         uint32_t asked = 0;
@@ -292,19 +295,37 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         const int G = G16 ? G16 : (int)((B + 15) / 16);
         const int last = G16 ? 16 : (int)(B - 16 * (uint32_t)(G - 1));   // tokens of a block's last chunk
         TokChunk ring[HASH_RING];
-        constexpr int H = SPAN / WAVE;
+        // (spans under 64: a sweep is the blocks of 64 / SPAN rows, and each
+        // lane fetches its row's values by ds_bpermute)
+        constexpr bool SHORT = SPAN < WAVE;
+        constexpr int H = SHORT ? 1 : SPAN / WAVE, RPS = SHORT ? WAVE / SPAN : 1;
         static_assert(DIGEST_WAVES % H == 0, "a wave's sweeps start at the same block of their rows");
-        const int row0 = (w - 1) / H, first = (w - 1) % H * WAVE;   // sweep 0's row, and every sweep's first block
+        // sweep 0's (first) row, and every sweep's first block
+        const int row0 = (w - 1) / H * RPS, first = (w - 1) % H * WAVE;
         RoundRow r2{}, r1{}, r0{}, rs{};   // rounds p + 2, p + 1, p, p - 1
-        auto row_of = [&](int q) { return row0 + DIGEST_WAVES / H * q; };
+        auto row_of = [&](int q) { return row0 + DIGEST_WAVES / H * RPS * q; };
         // blocks of sweep q (from 64 down; none below 1)
         auto count_of = [&](const RoundRow &r, int q) {
             return __builtin_amdgcn_readlane((int)r.m, row_of(q)) - first;
+        };
+        // SHORT: value x of the row that this lane's block is in
+        auto of_row = [&](uint32_t x, int q) {
+            return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (row_of(q) + lane / SPAN), (int)x);
         };
         // Every lane loads, idle ones the sweep's first block or, without one,
         // a few unused header words: with a branch around a load the wait for
         // an older one would count as a wait for all.
         auto fetch = [&](TokChunk &c, const RoundRow &r, int q, int g) {
+            if constexpr (SHORT) {
+                const uint32_t sub = lane % SPAN;
+                const bool mine = sub < of_row(r.m, q);
+                const uint64_t tok = (uint64_t)of_row((uint32_t)r.tok, q) |
+                                     (uint64_t)of_row((uint32_t)(r.tok >> 32), q) << 32;
+                const int32_t *src = mine ? tokens + tok + sub * B + 16 * (uint32_t)g : idle;
+                if (g < G - 1) load16(src, c);
+                else load_last(src, last, c);
+                return;
+            }
             const int cnt = count_of(r, q);
             const uint64_t tok = readlane64(r.tok, row_of(q)) + (uint64_t)(uint32_t)first * B + 16 * (uint32_t)g;
             const char *src = cnt > 0 ? reinterpret_cast<const char *>(tokens + tok)
@@ -315,7 +336,24 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         };
         // sweep q's keys of round p - 1 leave the tile, and the digests of
         // round p + 1 take their place
+        auto put = [&](uint64_t k, uint64_t at, uint32_t b) {
+            keys[at] = k;
+            if (depth) depth[at] = b;
+            if (key_hist) {
+                const uint32_t lo = (uint32_t)k;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) atomicAdd(&L.hist[256 * x + ((lo >> (8 * x)) & 0xFF)], 1u);
+            }
+        };
         auto exchange = [&](uint64_t *tile, int q, int cnt, uint64_t d) {
+            if constexpr (SHORT) {
+                const uint32_t sub = lane % SPAN, out = of_row(rs.m, q), pos = of_row(rs.pos, q), b = of_row(rs.b, q);
+                const uint32_t in = of_row(r1.m, q);
+                uint64_t *at = tile + (row_of(q) + lane / SPAN) * ROW + sub;
+                if (sub < out) put(*at, deepest_first ? pos - sub : pos + sub, b + sub);
+                if (sub < in) *at = d;
+                return;
+            }
             const int row = row_of(q);
             uint64_t *at = tile + row * ROW + lane;
             // (readlane before the branch: inside it a register may hold the
@@ -325,15 +363,8 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
             const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)rs.b, row) + (uint32_t)first;
             const uint64_t o = deepest_first ? (uint64_t)pos - (uint32_t)first : (uint64_t)pos + (uint32_t)first;
             if (lane < out) {
-                const uint64_t k = *at;
                 const int64_t j = deepest_first ? -lane : lane;
-                keys[o + j] = k;
-                if (depth) depth[o + j] = b + (uint32_t)lane;
-                if (key_hist) {
-                    const uint32_t lo = (uint32_t)k;
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) atomicAdd(&L.hist[256 * x + ((lo >> (8 * x)) & 0xFF)], 1u);
-                }
+                put(*at, o + j, b + (uint32_t)lane);
             }
             if (lane < cnt) *at = d;
         };
@@ -366,7 +397,9 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
                 while (q < sweeps) {
 #pragma unroll
                     for (int k = 0; k < HASH_RING; ++k) {
-                        const int cnt = count_of(r1, q);
+                        int cnt;
+                        if constexpr (SHORT) cnt = __popcll(ballot((uint32_t)(lane % SPAN) < of_row(r1.m, q)));
+                        else cnt = count_of(r1, q);
                         if (cnt > 0) {
                             if (g < G - 1) t = fold16(t, ring[k]);
                             else t = fold_last(t, ring[k], last);
@@ -375,13 +408,19 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
                             exchange(tile, q, cnt, fold_end(t));
                             t = 0;
                         }
-                        const bool here = fq < sweeps;
-                        RoundRow from;
-                        from.tok = here ? r1.tok : r2.tok;
-                        from.m = here ? r1.m : r2.m;
-                        fetch(ring[k], from, here ? fq : fq - sweeps, fg);
                         if (++g == G) { g = 0; ++q; }
-                        if (++fg == G) { fg = 0; ++fq; }
+                        // two at a time: mostly the halves of the same lines,
+                        // which do not stay in the caches until the next fetch
+                        if (k % 2)
+#pragma unroll
+                            for (int x = k - 1; x <= k; ++x) {
+                                const bool here = fq < sweeps;
+                                RoundRow from;
+                                from.tok = here ? r1.tok : r2.tok;
+                                from.m = here ? r1.m : r2.m;
+                                fetch(ring[x], from, here ? fq : fq - sweeps, fg);
+                                if (++fg == G) { fg = 0; ++fq; }
+                            }
                     }
                 }
             }
@@ -398,14 +437,109 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
     }
 }
 
+// ---- requests in the order of their length -------------------------------
+// The last request to end decides the kernel's time, so the longest should
+// start first.  A counting sort over 1024 length classes (32 to an octave, 3%
+// apart) copies the requests' table entries into that order: the hash kernel
+// walks them instead of the caller's, last to first as before.
+constexpr int LEN_CLASSES = 1024, ORDER_THREADS = 256;
+// requests: fewer are all in work at once, and among more the last hardly counts
+constexpr uint32_t ORDER_MIN = 1u << 10, ORDER_MAX = 1u << 24;
+__device__ __forceinline__ int length_class(uint32_t len, uint32_t B) {
+    const uint32_t nb = len / B;
+    if (nb < 32) return (int)nb;
+    const int e = 26 - __clz((int)nb);   // the five bits below the leading one
+    return 32 + e * 32 + (int)((nb >> e) & 31);
+}
+
+struct OrderWs {
+    uint32_t *hist, *ticket;   // hist[LEN_CLASSES], ticket: zeroed before
+    uint32_t *cursor;          // [LEN_CLASSES]
+    uint64_t *start, *off, *parent;
+    uint32_t *len;
+};
+
+// counts the classes; the last workgroup turns them into first positions
+__global__ __launch_bounds__(ORDER_THREADS) void hash_classes_kernel(const uint32_t *__restrict__ tok_len, uint32_t n,
+                                                                     uint32_t B, OrderWs o) {
+    __shared__ uint32_t h[LEN_CLASSES], tmp[ORDER_THREADS / WAVE], mine;
+    for (int i = threadIdx.x; i < LEN_CLASSES; i += ORDER_THREADS) h[i] = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * ORDER_THREADS + threadIdx.x; i < n; i += gridDim.x * ORDER_THREADS)
+        atomicAdd(&h[length_class(tok_len[i], B)], 1u);
+    __syncthreads();
+    for (int i = threadIdx.x; i < LEN_CLASSES; i += ORDER_THREADS)
+        if (h[i]) atomicAdd(&o.hist[i], h[i]);
+    atomics_performed();
+    __syncthreads();
+    if (threadIdx.x == 0) mine = atomicAdd(o.ticket, 1u);
+    __syncthreads();
+    if (mine != gridDim.x - 1) return;
+    constexpr int PER = LEN_CLASSES / ORDER_THREADS;
+    uint32_t v[PER], sum = 0, total;
+    for (int k = 0; k < PER; ++k) sum += v[k] = ld_status(&o.hist[threadIdx.x * PER + k]);
+    uint32_t at = block_excl_scan(sum, tmp, &total);
+    for (int k = 0; k < PER; ++k) {
+        o.cursor[threadIdx.x * PER + k] = at;
+        at += v[k];
+    }
+}
+
+// each workgroup takes room for its chunk's classes and moves the entries
+__global__ __launch_bounds__(ORDER_THREADS) void hash_order_kernel(
+    const uint64_t *__restrict__ tok_start, const uint32_t *__restrict__ tok_len,
+    const uint64_t *__restrict__ blk_off, const uint64_t *__restrict__ parent, uint32_t n, uint32_t B, uint32_t per,
+    OrderWs o) {
+    __shared__ uint32_t h[LEN_CLASSES];
+    const uint32_t lo = blockIdx.x * per, hi = n - lo < per ? n : lo + per;
+    for (int i = threadIdx.x; i < LEN_CLASSES; i += ORDER_THREADS) h[i] = 0;
+    __syncthreads();
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += ORDER_THREADS) atomicAdd(&h[length_class(tok_len[i], B)], 1u);
+    __syncthreads();
+    for (int i = threadIdx.x; i < LEN_CLASSES; i += ORDER_THREADS)
+        if (h[i]) h[i] = atomicAdd(&o.cursor[i], h[i]);
+    __syncthreads();
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += ORDER_THREADS) {
+        const uint32_t len = tok_len[i];
+        const uint32_t at = atomicAdd(&h[length_class(len, B)], 1u);
+        o.len[at] = len;
+        o.start[at] = tok_start[i];
+        o.off[at] = blk_off[i];
+        if (parent) o.parent[at] = parent[i];
+    }
+}
+
+// the workspace: header, work counters, then what the order needs
+struct HashWs {
+    int32_t *hdr;
+    uint32_t *counters;
+    OrderWs order;
+    size_t least, bytes;   // without and with the order
+};
+static HashWs hash_ws(void *ws, uint32_t n_seqs) {
+    Carver c{(char *)ws, 0};
+    HashWs w;
+    w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
+    w.counters = c.take<uint32_t>(3);
+    w.order.ticket = w.counters + 2;
+    w.least = WS_HEADER + WS_ALIGN;
+    w.bytes = w.least;
+    if (n_seqs <= ORDER_MIN || n_seqs > ORDER_MAX) return w;
+    w.order.hist = c.take<uint32_t>(LEN_CLASSES);
+    w.order.cursor = c.take<uint32_t>(LEN_CLASSES);
+    w.order.start = c.take<uint64_t>(n_seqs);
+    w.order.off = c.take<uint64_t>(n_seqs);
+    w.order.parent = c.take<uint64_t>(n_seqs);
+    w.order.len = c.take<uint32_t>(n_seqs);
+    w.bytes = c.off;
+    return w;
+}
+
 }  // namespace pc
 
 extern "C" {
 
-size_t pc_hash_blocks_ws(uint32_t n_seqs) {
-    (void)n_seqs;
-    return pc::WS_HEADER + pc::WS_ALIGN;   // header + two work counters
-}
+size_t pc_hash_blocks_ws(uint32_t n_seqs) { return pc::hash_ws(nullptr, n_seqs).bytes; }
 
 pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_t *tok_start,
                          const uint32_t *tok_len,
@@ -418,47 +552,89 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     if (n_seqs > 0 && (!tokens || !tok_start || !tok_len || !blk_off)) return PC_ERR_INVALID;
     if (n_blocks > 0 && !keys) return PC_ERR_INVALID;
     if (!ws) return PC_ERR_WORKSPACE;
-    if (ws_bytes < pc_hash_blocks_ws(n_seqs)) return PC_ERR_WORKSPACE;
+    const pc::HashWs hw = pc::hash_ws(ws, n_seqs);
+    if (ws_bytes < hw.least) return PC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     if (n_seqs == 0 || n_blocks == 0) {
         if (key_hist) return pc::fill_u32(key_hist, 0u, 4 * 256, s);
         return PC_OK;
     }
-    pc::Carver c{(char *)ws, 0};
-    int32_t *hdr = c.take<int32_t>(pc::WS_HEADER / sizeof(int32_t));
-    uint32_t *counters = c.take<uint32_t>(2);
-    pc::Fills fills;
-    fills.add(hdr, 0u, 1);
-    fills.add(counters, 0u, 2);
-    if (key_hist) fills.add(key_hist, 0u, 4 * 256);
-    const pc_status st = pc::fill_all(fills, s);
-    if (st != PC_OK) return st;
-
-    // Rows per workgroup: the requests spread over the resident workgroups.
-    const uint64_t wgs = (uint64_t)pc::device_cus() * pc::HASH_WG_PER_CU;
-    const uint64_t need = ((uint64_t)n_seqs + wgs - 1) / wgs;
-    // Larger blocks take fewer rows: a digest wave folds at least eight chunks
+    // Larger blocks take fewer rows: a digest wave folds at least sixteen chunks
     // of 16 tokens a phase (a multiple of the ring's four), and not many more,
-    // so that the waves of a workgroup end their phases together (256-token
-    // blocks, 1.7e6 accesses: 0.46 ms, with the eight sweeps of 16-token
-    // blocks 0.85).
+    // so that the waves of a workgroup end their phases together (64-token
+    // blocks, 5.0e7 accesses: 2.12 ms, with eight chunks 2.28; 256-token blocks,
+    // 1.7e6: 0.46 ms, with the eight sweeps of 16-token blocks 0.85).
     const int chunks = ((int)block_size + 15) / 16;
     int sweeps = 1;
-    while (sweeps < pc::HASH_SWEEPS && (sweeps * chunks < 8 || sweeps * chunks % pc::HASH_RING)) sweeps *= 2;
-    // With few requests per workgroup a round takes more blocks of fewer rows:
-    // what a phase costs besides the chain is then paid less often (17,758
-    // requests, 35 per workgroup: 0.81 ms with 16 rows of 128 blocks, 0.84 with
-    // 32 of 64, 0.92 with 8 of 256; 317 per workgroup: 2.64 and 2.59 ms).
+    while (sweeps < pc::HASH_SWEEPS && (sweeps * chunks < 16 || sweeps * chunks % pc::HASH_RING)) sweeps *= 2;
+    // Rows in work at once (256 CUs x workgroups per CU x entries / span): the
+    // fewer, the closer each request runs to its chain's own pace; the more,
+    // the better the memory is used.  Best is about a quarter of the requests,
+    // so that the shorter ones fill up behind the longest.  16-token blocks,
+    // ms with 16384 / 8192 / 4096 / 2048 rows:
+    //   156,497 requests of 1433 blocks on average  2.00 2.57 2.64 3.97
+    //    42,000                         1433        0.92 0.83 0.99 1.55
+    //    17,233                         1604        0.68 0.66 0.52 0.72
+    //     8,700                         1604        0.49 0.48 0.45 0.41
+    //    11,700                          171        0.12 0.13 0.13 0.20
+    // Larger blocks have more tokens to a chain step and fewer rows: they keep
+    // two workgroups per CU.  From 128 tokens on, where a request has few
+    // blocks, a sweep of 64 takes them from several rows, or its lanes would
+    // idle (ms with spans of 16 / 32 / 64 / 128: 2.0e7 blocks of 128 tokens in
+    // 111,000 requests 1.60 1.63 1.72 2.08; 1.0e7 of 256 in 111,000 1.54 1.68
+    // 2.16 2.26; 1.7e6 of 256 in 18,389 0.44 0.32 0.38 0.41; with smaller
+    // blocks the shorter rounds cost more: 5.0e7 of 64 in 156,000 2.77 against
+    // 2.01).
     const uint64_t entries = (uint64_t)sweeps * pc::DIGEST_WAVES * pc::WAVE;
-    const int span = need * 256 <= entries ? 256 : need * 32 <= entries ? 128 : 64;
+    const uint64_t cus = (uint64_t)pc::device_cus(), mean = n_blocks / n_seqs;
+    const uint64_t need = (n_seqs + 2 * cus - 1) / (2 * cus);
+    int per_cu = pc::HASH_WG_PER_CU, span = 0;
+    for (int x = chunks < 8 ? 64 : 16; x <= 128 && !span; x *= 2)
+        if (entries / x <= pc::WAVE && n_seqs >= 4 * per_cu * cus * (entries / x)) span = x;
+    if (!span && sweeps == pc::HASH_SWEEPS) {
+        per_cu = 1;
+        const uint64_t r = cus * (entries / 256);
+        span = n_seqs <= r || (mean >= 512 && n_seqs <= 6 * r) ? 256 : 128;
+    } else if (!span) {
+        span = need * 256 <= entries ? 256 : need * 32 <= entries ? 128 : 64;
+    }
+    // (8192 requests of 8 blocks 0.078 ms, with 64 0.094)
+    if (chunks >= 8 && span == 64 && mean < 32 && n_seqs >= 8 * cus * (entries / 128)) span = 32;
+    const uint64_t wgs = cus * per_cu, most = ((uint64_t)n_seqs + wgs - 1) / wgs;
     const int rows = (int)(entries / span);
-    const int lanes = need < (uint64_t)rows ? (int)need : rows;
+    const int lanes = most < (uint64_t)rows ? (int)most : rows;
     const uint64_t want = ((uint64_t)n_seqs + lanes - 1) / lanes;
     const dim3 grid((unsigned)(want < wgs ? want : wgs));
     const dim3 block(pc::HASH_THREADS);
+    // The order pays where requests are still waiting when the first ones end
+    // and the work is long against the two launches (12 us): 2.8e7 accesses
+    // 0.80 -> 0.66 ms, 2.2e8 2.71 -> 2.05, 8.0e8 7.90 -> 7.44.
+    const bool ordered = hw.bytes > hw.least && n_seqs > grid.x * (uint64_t)lanes && mean * block_size >= 1024 &&
+                         n_blocks * block_size >= 1ull << 26 && ws_bytes >= hw.bytes;
+    pc::Fills fills;
+    fills.add(hw.hdr, 0u, 1);
+    fills.add(hw.counters, 0u, 3);
+    if (ordered) fills.add(hw.order.hist, 0u, pc::LEN_CLASSES);
+    if (key_hist) fills.add(key_hist, 0u, 4 * 256);
+    const pc_status st = pc::fill_all(fills, s);
+    if (st != PC_OK) return st;
+    if (ordered) {
+        const uint32_t T = pc::ORDER_THREADS;
+        const uint32_t groups = n_seqs / (4 * T) < 256 ? n_seqs / (4 * T) + 1 : 256;
+        const uint32_t per = (n_seqs + groups - 1) / groups;
+        PC_LAUNCH(pc::K_HASH_ORDER, pc::hash_classes_kernel, dim3(groups), dim3(T), 0, s, tok_len, n_seqs, block_size,
+                  hw.order);
+        PC_LAUNCH(pc::K_HASH_ORDER, pc::hash_order_kernel, dim3((n_seqs + per - 1) / per), dim3(T), 0, s, tok_start,
+                  tok_len, blk_off, parent, n_seqs, block_size, per, hw.order);
+        tok_start = hw.order.start;
+        tok_len = hw.order.len;
+        blk_off = hw.order.off;
+        if (parent) parent = hw.order.parent;
+    }
 #define PC_HASH(S, G16)                                                                                              \
     PC_LAUNCH(pc::K_HASH, (pc::hash_kernel<S, G16>), grid, block, 0, s, tokens, n_tokens, tok_start, tok_len,        \
-              n_seqs, block_size, parent, root, blk_off, n_blocks, keys, depth, key_hist, flags, counters, hdr, hdr + 16, lanes, sweeps)
+              n_seqs, block_size, parent, root, blk_off, n_blocks, keys, depth, key_hist, flags, hw.counters,       \
+              hw.hdr, hw.hdr + 16, lanes, sweeps)
     if (block_size == 16) {
         if (span == 256) PC_HASH(256, 1);
         else if (span == 128) PC_HASH(128, 1);
@@ -466,7 +642,9 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     } else {
         if (span == 256) PC_HASH(256, 0);
         else if (span == 128) PC_HASH(128, 0);
-        else PC_HASH(64, 0);
+        else if (span == 64) PC_HASH(64, 0);
+        else if (span == 32) PC_HASH(32, 0);
+        else PC_HASH(16, 0);
     }
 #undef PC_HASH
     return PC_OK;

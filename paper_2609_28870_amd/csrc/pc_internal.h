@@ -41,6 +41,7 @@ constexpr int32_t DEV_ERR_BAD_HIST = 4;
 enum KernelId {
     K_FILL32 = 0,
     K_HASH,
+    K_HASH_ORDER,
     K_SORT_HIST,
     K_SORT_HIGH,
     K_SORT_PASS,

@@ -30,7 +30,8 @@ COPY_GRID = 131072            # the calibration copy's grid (4 GiB of int32)
 COPY_KIB = 4 * 1024 * 1024    # KiB it reads and writes
 
 # library kernel -> the kernel id the bench and the library's timers use
-IDS = {"pc::hash_kernel": "hash_blocks",
+IDS = {"pc::hash_kernel": "hash_blocks", "pc::hash_classes_kernel": "hash_order",
+       "pc::hash_order_kernel": "hash_order",
        "pc::sort_hist_kernel": "sort_digit_hist", "pc::sort_persistent_kernel": "sort_high_bits",
        "pc::sort_pass_kernel": "sort_onesweep_pass", "pc::link_partition_kernel": "link_partition",
        "pc::perm_partition_kernel": "perm_partition", "pc::perm_local_kernel": "perm_local",

@@ -13,7 +13,7 @@ from paper_2609_28870_amd import pc
 pytestmark = pytest.mark.gpu
 
 
-def check(blocks, B, seed, deepest=False, parent=False, pad=0):
+def check(blocks, B, seed, deepest=False, parent=False, pad=0, ws=None):
     g = np.random.default_rng(seed)
     blocks = np.asarray(blocks, np.int64)
     length = blocks * B + g.integers(0, B, size=blocks.size)
@@ -29,7 +29,7 @@ def check(blocks, B, seed, deepest=False, parent=False, pad=0):
     keys, dep, ws = pc.hash_blocks(torch.from_numpy(tokens).cuda(), pc.to_dev_u64(start), pc.to_dev_u32(length),
                                    pc.to_dev_u64(off), int(off[-1]), B,
                                    parent=None if par is None else pc.to_dev_u64(par), root=5, key_hist=hist,
-                                   deepest_first=deepest)
+                                   deepest_first=deepest, ws=ws)
     assert pc.workspace_status(ws) == 0
     assert np.array_equal(pc.as_u64(keys), want)
     assert np.array_equal(pc.as_u32(dep), depth)
@@ -53,6 +53,20 @@ def test_request_counts_around_the_rows_in_flight(n_seqs, B):
     blocks = np.minimum(g.geometric(0.15, size=n_seqs) - 1, 90)      # a fair share of empty requests
     blocks[g.integers(0, n_seqs, size=3)] = [300, 700, 65]
     check(blocks, B, n_seqs, deepest=n_seqs % 2 == 1, parent=n_seqs % 3 == 0, pad=1)
+
+
+@pytest.mark.parametrize("n_seqs,mean,B", [(9000, 520, 16), (13000, 400, 16), (17000, 300, 16), (40000, 120, 16),
+                                           (70001, 70, 16), (40000, 70, 24), (5000, 110, 128), (33000, 17, 128),
+                                           (17000, 17, 256), (4097, 9, 256), (8200, 36, 256)])
+def test_requests_ordered_by_length(n_seqs, mean, B):
+    # enough tokens for the order, at request counts on both sides of each rule
+    # on the rows in flight; lengths spread over many length classes
+    g = np.random.default_rng(n_seqs + B)
+    blocks = np.minimum(g.geometric(1 / mean, size=n_seqs), 40 * mean)
+    blocks[g.integers(0, n_seqs, size=3)] = [0, 1, 31]
+    check(blocks, B, n_seqs, deepest=n_seqs % 2 == 1, parent=n_seqs % 5 != 0, pad=1)
+    if n_seqs == 9000:      # a workspace without room for the order is enough
+        check(blocks, B, n_seqs, ws=pc.workspace(512))
 
 
 def test_a_bad_request_is_skipped_and_reported():
