@@ -8,17 +8,23 @@
 // when D < c, binning D on the capacity edges gives every capacity at once.
 //
 // GPU mapping: each thread takes 8 consecutive accesses (16 when the depths
-// come from the layout; 16-byte vector loads of dist / depth / next) and keeps the value range of the bin it is
-// filling in registers, so an access that stays in that bin (neighbouring
-// accesses of one request usually do) costs two compares; any other value
-// finds its bin by an upper-bound search of the edges held in LDS.  Runs of
-// equal bins are accumulated in registers, so one LDS atomic covers a run;
-// each workgroup then adds its non-zero LDS bins to the outputs with global
-// 64-bit atomics.  Up to 1024 edges sit in LDS at once; more are taken 1024
-// at a time, one launch each, a launch counting only the accesses that fall
-// between its edges.  Integer atomics make the result independent of
-// scheduling order.  The last workgroup to finish forms alpha*count +
-// beta*depthsum exactly as 128-bit integers.
+// come from the layout) at a time, the next ones' 16-byte loads on their way
+// meanwhile, and keeps the value range of the bin it is filling in registers,
+// so an access that stays in that bin (neighbouring accesses of one request
+// usually do) costs two compares; any other value finds its bin from a table
+// of value classes and the edges, both held in LDS.  Runs of equal bins are
+// accumulated in registers, so one LDS atomic covers a run; each workgroup
+// then adds its non-zero LDS bins to the outputs with global 64-bit atomics.
+// Up to 1024 edges sit in LDS at once; more are taken 1024 at a time, one
+// launch each, a launch counting only the accesses that fall between its
+// edges.  Integer atomics make the result independent of scheduling order.
+// The last workgroup to finish forms alpha*count + beta*depthsum exactly as
+// 128-bit integers.
+//
+// Bound: the reads of dist and next (2.2e8 accesses, 1.8 GB: 0.406 ms, 4.4
+// TB/s, before 0.426; 3.4e7 random keys 0.111, before 0.395, of which the
+// whole searches took 0.08 and the final adds of 16384 workgroups the rest;
+// 2.8e7 agent accesses 0.054, before 0.110).
 //
 // pc_mrc_weighted_layout takes the depths from the request layout instead
 // of an array: depth(t) = t - (start of t's request).  A map kernel writes a
@@ -36,11 +42,10 @@
 
 namespace pc {
 
-constexpr int MRC_THREADS = 256;
+constexpr int MRC_THREADS = 1024;
 
-// number of edges <= x (edges non-decreasing)
-__device__ __forceinline__ uint32_t upper_bound(const uint32_t *e, uint32_t m, uint32_t x) {
-    uint32_t lo = 0, hi = m;
+// number of edges <= x (edges non-decreasing), known to be in [lo, hi]
+__device__ __forceinline__ uint32_t upper_bound(const uint32_t *e, uint32_t lo, uint32_t hi, uint32_t x) {
     while (lo < hi) {
         const uint32_t mid = (lo + hi) >> 1;
         if (e[mid] <= x) lo = mid + 1; else hi = mid;
@@ -48,10 +53,9 @@ __device__ __forceinline__ uint32_t upper_bound(const uint32_t *e, uint32_t m, u
     return lo;
 }
 
-// consecutive accesses per thread: 8 with a depth array (32 registers of
-// loads per lane keep eight waves per SIMD), 16 with depths from the layout
-// (its map lookup per thread then covers twice the accesses: 4.6 -> 3.3 ms
-// on the full trace)
+// consecutive accesses per thread: 8 with a depth array (three arrays' loads
+// of two chunks in registers), 16 with depths from the layout (its map lookup
+// per thread then covers twice the accesses)
 template <bool LAYOUT> constexpr int mrc_per() { return LAYOUT ? 16 : 8; }
 constexpr uint32_t MRC_EDGES = 1024;   // edges held in LDS by one launch
 
@@ -72,10 +76,25 @@ struct BinRange {
 
 __device__ __forceinline__ uint32_t clamp_edge(uint64_t e) { return e < NONE ? (uint32_t)e : NONE; }
 
+// Where the search starts: values in classes, 32 to an octave (below 32 one
+// each), and per class the number of edges below it, so that mostly no edge or
+// one is left to compare.  A whole search is a chain of seven and more LDS
+// reads, which all lanes wait for as soon as one needs it.
+constexpr uint32_t MRC_CLASSES = 32 + 27 * 32;
+__device__ __forceinline__ uint32_t value_class(uint32_t x) {
+    if (x < 32) return x;
+    const int e = 26 - __clz((int)x);   // the five bits below the leading one
+    return 32 + (uint32_t)e * 32 + ((x >> e) & 31);
+}
+__device__ __forceinline__ uint32_t class_start(uint32_t c) {
+    return c < 32 ? c : (32 + (c & 31)) << (c / 32 - 1);
+}
+
 template <bool CHUNKED>
-__device__ __forceinline__ BinRange find_bin(const uint32_t *e, uint32_t K, uint32_t x, uint32_t below,
-                                             bool last) {
-    const uint32_t b = upper_bound(e, K, x);
+__device__ __forceinline__ BinRange find_bin(const uint32_t *e, const uint16_t *below_class, uint32_t K, uint32_t x,
+                                             uint32_t below, bool last) {
+    const uint32_t c = value_class(x);
+    const uint32_t b = upper_bound(e, below_class[c], below_class[c + 1], x);
     BinRange r{b ? e[b - 1] : 0u, b < K ? e[b] - 1 : NONE, b};
     if (CHUNKED) {
         if (b == 0 && x < below) r = BinRange{0u, below - 1, K + 1};
@@ -84,6 +103,28 @@ __device__ __forceinline__ BinRange find_bin(const uint32_t *e, uint32_t K, uint
     }
     return r;
 }
+
+// four words at any 4-byte alignment: one 16-byte load on this part
+struct __attribute__((packed, aligned(4))) Quad {
+    uint32_t x, y, z, w;
+};
+// one thread's loads of a chunk
+template <int PER>
+struct MrcChunk {
+    uint32_t d[PER], x[PER], p[PER];   // dist, next, depth
+    uint64_t bits;                     // request marks of the chunk's word of 64 positions
+    uint32_t entry;                    // and the word's entry in gstart
+    __device__ __forceinline__ static void load(uint32_t (&v)[PER], const uint32_t *from) {
+#pragma unroll
+        for (int q = 0; q < PER / 4; ++q) {
+            const Quad a = reinterpret_cast<const Quad *>(from)[q];
+            v[4 * q] = a.x;
+            v[4 * q + 1] = a.y;
+            v[4 * q + 2] = a.z;
+            v[4 * q + 3] = a.w;
+        }
+    }
+};
 
 // One launch covers bins k0 .. k0 + Kc of the n_caps + 1 (the last of them
 // only when k0 + Kc == n_caps) with its Kc edges caps[k0 .. k0 + Kc) in LDS.
@@ -96,6 +137,7 @@ __global__ __launch_bounds__(MRC_THREADS) void mrc_hist_kernel(
     int32_t *__restrict__ err, uint32_t *__restrict__ ticket, uint64_t alpha, uint64_t beta,
     uint64_t *__restrict__ cost_lo, uint64_t *__restrict__ cost_hi) {
     extern __shared__ uint64_t smem[];
+    __shared__ uint16_t s_class[MRC_CLASSES + 1];
     const uint32_t K = Kc;
     uint64_t *s_ds = smem;                    // K+2
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_ds + K + 2);   // K+2
@@ -114,83 +156,31 @@ __global__ __launch_bounds__(MRC_THREADS) void mrc_hist_kernel(
         s_nh[i] = 0;
     }
     __syncthreads();
-    constexpr int MRC_PER = mrc_per<LAYOUT>();
-    const uint64_t chunks = (n + MRC_PER - 1) / MRC_PER;
-    // vector loads only when every base pointer is 16-byte aligned
-    const bool vec = ((reinterpret_cast<uintptr_t>(dist) | reinterpret_cast<uintptr_t>(depth) |
-                       reinterpret_cast<uintptr_t>(next)) & 15) == 0;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t ch = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; ch < chunks; ch += stride) {
-        const uint64_t t0 = ch * MRC_PER;
-        const bool full = t0 + MRC_PER <= n;
-        uint32_t dv[MRC_PER], pv[MRC_PER], nv[MRC_PER];
-        if (full && vec) {
-#pragma unroll
-            for (int q = 0; q < MRC_PER / 4; ++q) {
-                const uint4 a = reinterpret_cast<const uint4 *>(dist + t0)[q];
-                dv[4 * q] = a.x; dv[4 * q + 1] = a.y; dv[4 * q + 2] = a.z; dv[4 * q + 3] = a.w;
-                if (depth) {
-                    const uint4 b = reinterpret_cast<const uint4 *>(depth + t0)[q];
-                    pv[4 * q] = b.x; pv[4 * q + 1] = b.y; pv[4 * q + 2] = b.z; pv[4 * q + 3] = b.w;
-                }
-                if (next) {
-                    const uint4 c = reinterpret_cast<const uint4 *>(next + t0)[q];
-                    nv[4 * q] = c.x; nv[4 * q + 1] = c.y; nv[4 * q + 2] = c.z; nv[4 * q + 3] = c.w;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < MRC_PER; ++j) {
-                const bool in = t0 + j < n;
-                dv[j] = in ? dist[t0 + j] : 0u;
-                pv[j] = (in && depth) ? depth[t0 + j] : 0u;
-                nv[j] = (in && next) ? next[t0 + j] : 0u;
-            }
-        }
-        if (LAYOUT) {
-            const uint64_t wd = t0 >> 6;
-            const uint64_t bits = reinterpret_cast<const uint64_t *>(startbits)[wd];
-            const uint32_t sh = (uint32_t)(t0 & 63);   // a multiple of MRC_PER, at most 64 - MRC_PER
-            const uint32_t sb = (uint32_t)(bits >> sh);
-            if (!desc) {
-                // the last request start at or below t0 (in the 64-position
-                // word, else the word's entry), then the starts among the
-                // thread's accesses
-                const uint64_t upto = bits & ((2ull << sh) - 1);
-                uint32_t st = upto ? (uint32_t)((wd << 6) + 63 - __builtin_clzll(upto)) : gstart[wd];
-#pragma unroll
-                for (int j = 0; j < MRC_PER; ++j) {
-                    if (j && ((sb >> j) & 1u)) st = (uint32_t)(t0 + j);
-                    pv[j] = (uint32_t)(t0 + j) - st;
-                }
-            } else {
-                // the first request end at or above t0 + 7 (in the word, else
-                // the word's entry), then the ends among the thread's accesses
-                const uint64_t from = bits >> (sh + MRC_PER - 1);
-                uint32_t en = from ? (uint32_t)((wd << 6) + sh + MRC_PER - 1 + __builtin_ctzll(from)) : gstart[wd];
-#pragma unroll
-                for (int j = MRC_PER - 1; j >= 0; --j) {
-                    if (j < MRC_PER - 1 && ((sb >> j) & 1u)) en = (uint32_t)(t0 + j);
-                    pv[j] = en - (uint32_t)(t0 + j);
-                }
-            }
-        } else if (!depth) {
-#pragma unroll
-            for (int j = 0; j < MRC_PER; ++j) pv[j] = 0;
-        }
-        const int m = full ? MRC_PER : (int)(n - t0);
+    for (uint32_t c = threadIdx.x; c <= MRC_CLASSES; c += blockDim.x)
+        s_class[c] = (uint16_t)(c == 0 ? 0u : c == MRC_CLASSES ? K : upper_bound(s_caps, 0, K, class_start(c) - 1));
+    __syncthreads();
+    constexpr int PER = mrc_per<LAYOUT>();
+    using Chunk = MrcChunk<PER>;
+    // the chunk's accesses into the bins; pv: their depths
+    auto take = [&](uint64_t t0, const uint32_t (&dv)[PER], const uint32_t (&pv)[PER], const uint32_t (&nv)[PER],
+                    int m) {
         // current bins (range empty at the start: lo > hi)
         BinRange cur{1u, 0u, K + 2}, ncur{1u, 0u, K + 2};
         uint32_t cnt = 0, ncnt = 0;
         uint64_t ds = 0;
-        for (int j = 0; j < m; ++j) {
+        auto flush = [&]() {
+            if (cnt) {
+                atomicAdd(&s_cnt[cur.bin], cnt);
+                if (ds) atomicAdd(reinterpret_cast<unsigned long long *>(&s_ds[cur.bin]), (unsigned long long)ds);
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (j >= m) continue;
             const uint32_t d = dv[j];
             if (d < cur.lo || d > cur.hi) {
-                if (cnt) {
-                    atomicAdd(&s_cnt[cur.bin], cnt);
-                    if (ds) atomicAdd(reinterpret_cast<unsigned long long *>(&s_ds[cur.bin]), (unsigned long long)ds);
-                }
-                cur = find_bin<CHUNKED>(s_caps, K, d, below, last);
+                flush();
+                cur = find_bin<CHUNKED>(s_caps, s_class, K, d, below, last);
                 cnt = 0;
                 ds = 0;
             }
@@ -201,17 +191,91 @@ __global__ __launch_bounds__(MRC_THREADS) void mrc_hist_kernel(
                 const uint32_t g = q == NONE ? NONE : q - (uint32_t)(t0 + j);
                 if (g < ncur.lo || g > ncur.hi) {
                     if (ncnt) atomicAdd(&s_nh[ncur.bin], ncnt);
-                    ncur = find_bin<CHUNKED>(s_caps, K, g, below, last);
+                    ncur = find_bin<CHUNKED>(s_caps, s_class, K, g, below, last);
                     ncnt = 0;
                 }
                 ++ncnt;
             }
         }
-        if (cnt) {
-            atomicAdd(&s_cnt[cur.bin], cnt);
-            if (ds) atomicAdd(reinterpret_cast<unsigned long long *>(&s_ds[cur.bin]), (unsigned long long)ds);
-        }
+        flush();
         if (ncnt) atomicAdd(&s_nh[ncur.bin], ncnt);
+    };
+    // depths from the request marks of the chunk's word and the word's entry
+    auto depths = [&](uint64_t t0, uint64_t bits, uint32_t entry, uint32_t (&pv)[PER]) {
+        const uint64_t wd = t0 >> 6;
+        const uint32_t sh = (uint32_t)(t0 & 63);   // a multiple of PER, at most 64 - PER
+        const uint32_t sb = (uint32_t)(bits >> sh);
+        if (!desc) {
+            // the last request start at or below t0 (in the 64-position word,
+            // else the word's entry), then the starts among the accesses
+            const uint64_t upto = bits & ((2ull << sh) - 1);
+            uint32_t st = upto ? (uint32_t)((wd << 6) + 63 - __builtin_clzll(upto)) : entry;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                if (j && ((sb >> j) & 1u)) st = (uint32_t)(t0 + j);
+                pv[j] = (uint32_t)(t0 + j) - st;
+            }
+        } else {
+            // the first request end at or above the chunk's last position (in
+            // the word, else the word's entry), then the ends among the accesses
+            const uint64_t from = bits >> (sh + PER - 1);
+            uint32_t en = from ? (uint32_t)((wd << 6) + sh + PER - 1 + __builtin_ctzll(from)) : entry;
+#pragma unroll
+            for (int j = PER - 1; j >= 0; --j) {
+                if (j < PER - 1 && ((sb >> j) & 1u)) en = (uint32_t)(t0 + j);
+                pv[j] = en - (uint32_t)(t0 + j);
+            }
+        }
+    };
+    const uint64_t *marks = reinterpret_cast<const uint64_t *>(startbits);
+    const uint64_t whole = n / PER, chunks = (n + PER - 1) / PER;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    uint64_t ch = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // whole chunks: the next one's loads are on their way while one is binned
+    auto fetch = [&](Chunk &c, uint64_t i) {
+        const uint64_t t0 = (i < whole ? i : 0) * PER;
+        c.load(c.d, dist + t0);
+        if (next) c.load(c.x, next + t0);
+        if (!LAYOUT && depth) c.load(c.p, depth + t0);
+        if (LAYOUT) {
+            c.bits = marks[t0 >> 6];
+            c.entry = gstart[t0 >> 6];
+        }
+    };
+    auto bin = [&](Chunk &c, uint64_t i) {
+        if (LAYOUT) {
+            uint32_t pv[PER];
+            depths(i * PER, c.bits, c.entry, pv);
+            take(i * PER, c.d, pv, c.x, PER);
+        } else {
+            take(i * PER, c.d, c.p, c.x, PER);
+        }
+    };
+    if (ch < whole) {
+        Chunk a{}, b{};
+        fetch(a, ch);
+        for (;;) {
+            fetch(b, ch + stride);
+            bin(a, ch);
+            if ((ch += stride) >= whole) break;
+            fetch(a, ch + stride);
+            bin(b, ch);
+            if ((ch += stride) >= whole) break;
+        }
+    }
+    // the last, short chunk
+    if (ch < chunks) {
+        const uint64_t t0 = ch * PER;
+        uint32_t dv[PER], pv[PER], nv[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool in = t0 + j < n;
+            dv[j] = in ? dist[t0 + j] : 0u;
+            pv[j] = (in && depth) ? depth[t0 + j] : 0u;
+            nv[j] = (in && next) ? next[t0 + j] : 0u;
+        }
+        if (LAYOUT) depths(t0, marks[t0 >> 6], gstart[t0 >> 6], pv);
+        take(t0, dv, pv, nv, (int)(n - t0));
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i <= K; i += blockDim.x) {
@@ -334,30 +398,35 @@ static pc_status mrc_run(const uint32_t *dist, const uint32_t *depth, const uint
     const uint8_t *sb = layout ? reinterpret_cast<const uint8_t *>(lw.startbits) : nullptr;
     const uint64_t per = layout ? mrc_per<true>() : mrc_per<false>();
     uint32_t *ticket = reinterpret_cast<uint32_t *>(hdr + 1);
-    uint64_t grid = (n + MRC_THREADS * per - 1) / (MRC_THREADS * per);
-    // up to 64 workgroups per CU: eight resident (32 registers of loads per
-    // lane keep eight waves per SIMD) and the rest queued behind them, which
-    // hid the load latency best; more make the final flush contend
-    if (grid > (uint64_t)cus * 64) grid = (uint64_t)cus * 64;
+    // One workgroup per CU, of 1024 threads where there is work for them: the
+    // fewer workgroups add their bins to the outputs, the better (an address
+    // takes about 60 ns per workgroup: 2.8e7 accesses 0.052 ms, with twice the
+    // workgroups of half the size 0.069).  Below that, small workgroups on more
+    // CUs (6.5e4 accesses 11 us, 16 with 1024 threads).
+    const uint64_t all = (n + per - 1) / per;
+    unsigned threads = 256;
+    while (threads < MRC_THREADS && all > (uint64_t)threads * cus) threads *= 2;
+    uint64_t grid = (all + threads - 1) / threads;
+    if (grid > (uint64_t)cus) grid = (uint64_t)cus;
     if (grid == 0) grid = 1;
     for (uint32_t k0 = 0; k0 < n_caps; k0 += MRC_EDGES) {
         const uint32_t Kc = n_caps - k0 < MRC_EDGES ? n_caps - k0 : MRC_EDGES;
         const size_t shmem = (size_t)(Kc + 2) * 16 + (size_t)Kc * 4;
         const bool chunked = n_caps > MRC_EDGES;
         if (!chunked && !layout)
-            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, false>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
+            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, false>), dim3((unsigned)grid), dim3(threads), shmem,
                       s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
                       ticket, alpha, beta, cost_lo, cost_hi);
         else if (!chunked)
-            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, true>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
+            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<false, true>), dim3((unsigned)grid), dim3(threads), shmem,
                       s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
                       ticket, alpha, beta, cost_lo, cost_hi);
         else if (!layout)
-            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, false>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
+            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, false>), dim3((unsigned)grid), dim3(threads), shmem,
                       s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
                       ticket, alpha, beta, cost_lo, cost_hi);
         else
-            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, true>), dim3((unsigned)grid), dim3(MRC_THREADS), shmem,
+            PC_LAUNCH(K_MRC_HIST, (mrc_hist_kernel<true, true>), dim3((unsigned)grid), dim3(threads), shmem,
                       s, dist, depth, gs, sb, next, n, caps, n_caps, k0, Kc, count, depthsum, nextuse_hist, desc, hdr,
                       ticket, alpha, beta, cost_lo, cost_hi);
     }

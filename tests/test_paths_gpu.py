@@ -2,7 +2,8 @@
 they change: run counts around a merge block of 2048 and its eightfolds, the
 dominance count as one launch and as several, the passes over the high key
 bits, and the generic prev / next behind the chained one as one launch and as
-several.  All results are whole numbers and must match exactly."""
+several; and the bins where their value classes, chunks and workgroup sizes
+change.  All results are whole numbers and must match exactly."""
 import numpy as np
 import pytest
 import torch
@@ -88,3 +89,41 @@ def test_the_generic_path_behind_the_chained_one(n, low_shared):
     if n <= 1 << 20:
         p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
         assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+
+
+@pytest.mark.parametrize("edges", ["classes", "one octave", "one edge", "top"])
+@pytest.mark.parametrize("n,shift", [(1, 0), (15, 1), (1 << 16, 3), ((1 << 20) + 1, 0), ((1 << 20) + 7, 2), (4_300_003, 1),
+                                     (9_000_001, 0)])
+def test_bins_of_values_around_the_edges(n, shift, edges):
+    # distances and next-use gaps on both sides of class starts (32 classes to
+    # an octave) and of edges, NONE among them; views at any 4-byte alignment
+    rng = np.random.default_rng(n)
+    starts = np.array([0, 1, 31, 32, 33] + [(32 + k) << e for e in range(1, 27) for k in (0, 1, 31)], np.uint64)
+    caps = {"classes": starts,
+            "one octave": np.sort(rng.integers(1 << 15, 1 << 16, 900)).astype(np.uint64),
+            "one edge": np.array([1 << 15], np.uint64),
+            "top": np.array([0, 2 ** 32 - 2, 2 ** 32 - 1, 2 ** 32, 2 ** 40], np.uint64)}[edges]
+    near = (np.concatenate([starts, caps, [2 ** 32 - 2, 2 ** 32]])[:, None] + np.array([-1, 0, 1], np.int64)).reshape(-1)
+    near = np.clip(near.astype(np.int64), 0, 2 ** 32 - 1)
+    d = near[rng.integers(0, near.size, n)]
+    dep = rng.integers(0, 1 << 20, n)
+    t = np.arange(n, dtype=np.int64)
+    gap = near[rng.integers(0, near.size, n)]
+    nxt = np.where((gap > 0) & (t + gap < 2 ** 32 - 1), t + gap, 2 ** 32 - 1)      # NONE: no next use
+    gap = np.where(nxt == 2 ** 32 - 1, 2 ** 32 - 1, nxt - t)
+    view = lambda a: pc.to_dev_u32(np.concatenate([np.zeros(shift), a]).astype(np.uint32))[shift:]
+    out, ws = pc.mrc_weighted(view(d), pc.to_dev_u64(caps), view(dep), view(nxt), 3, 2)
+    assert pc.workspace_status(ws) == 0
+    got = pc.bins_to_host(out)
+
+    def hist(x, w=None):   # NONE lies past every edge
+        b = np.where(x == 2 ** 32 - 1, caps.size, np.searchsorted(caps.astype(np.int64), x, side="right"))
+        full = np.zeros(caps.size + 1, object)
+        for k in np.unique(b):
+            full[k] = int((b == k).sum()) if w is None else int(w[b == k].sum())
+        return full.tolist()
+
+    count, depthsum = hist(d), hist(d, dep)
+    assert [int(x) for x in got["count"]] == count and [int(x) for x in got["depthsum"]] == depthsum
+    assert [int(x) for x in got["cost"]] == [3 * a + 2 * b for a, b in zip(count, depthsum)]
+    assert [int(x) for x in got["nextuse"]] == hist(gap)
