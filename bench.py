@@ -503,7 +503,8 @@ def main():
                 "session_requests": "session_profile" if args.profile else "session_distance",
                 "session_distance": "session_distance",
                 "reuse_profile_pack": "reuse_profile", "reuse_profile_walk": "reuse_profile",
-                "session_profile": "session_profile", "belady": "belady"}
+                "session_profile": "session_profile", "belady": "belady",
+                "belady_rank": "belady"}
     stage_bytes = {"hash": 4 * B + 8, "prev_next": 16, "stack_distance": 8,
                    "mrc": mrc_bytes, "request_distance": 12,
                    "session_distance": 8, "reuse_profile": 24}

@@ -30,9 +30,12 @@
 //     dead count, the bitmap or the buffer in bulk.
 //   * Otherwise the evictions (after the dead blocks) take the largest
 //     values present, which are among the buffer's top 64 and the batch's
-//     own inserts above theta; the wave decides them all at once from a
-//     joint ranking of those 128 candidates (a prefix maximum and, per rank,
-//     a lowest prefix sum over the batch).  When those candidates run out it
+//     own inserts above theta; the wave decides them all at once (a prefix
+//     maximum finds the evictions, and each lane, for its own insert, whether
+//     one of them takes it, from a walk over the batch, six accesses per entry
+//     of a table in LDS).  Which inserts of its batch lie above an access's own
+//     does not depend on the capacity: a kernel of its own finds that once, a
+//     64-bit mask per access.  When those candidates run out the wave
 //     walks the batch in access order instead, refilling the buffer from the
 //     bitmap's largest values above the window (whole words, top down) and
 //     taking the window's largest value when nothing above it is left.
@@ -43,21 +46,29 @@
 // the ring may still hold bits inserted before: every 16 batches, after a
 // fence, the words that entered are exchanged for zero and their bits are
 // merged into the ring at the next such sync, long before the window gets
-// there, so a batch waits on no global memory (the next uses themselves are
-// loaded four batches ahead).  A refill syncs at once.
+// there, so a batch waits on no global memory (the next uses, depths and
+// masks come four batches at a time through LDS).  A refill syncs at once.
+//
+// Bound: the instructions of one wave, batch after batch, at the capacities
+// that evict most: 4.0e6 agent accesses at 69 capacities 0.151 s, 2.4 us a
+// batch of 64 (0.333 s with the joint ranking of all 128 candidates worked out
+// per capacity and a walk per rank and access: the decision then took 7,600
+// cycles of 12,000, now 3,000 of 6,000).
 #include "pc_internal.h"
 
 namespace pc {
 
 constexpr uint32_t BEL_TARGET = 128;          // buffer size a refill aims for and a spill leaves
 constexpr uint32_t BEL_SPILL_AT = 256;        // buffer size above which the lowest values are spilled
-constexpr uint32_t BEL_BUF = BEL_SPILL_AT + 2 * WAVE;   // LDS buffer entries (largest fill: spill size + one batch)
+// LDS buffer entries: the largest fill (spill size + one batch), and what a
+// search reads past a short buffer
+constexpr uint32_t BEL_BUF = BEL_SPILL_AT + 3 * WAVE;
 constexpr uint64_t BEL_INF = 1ull << 40;      // theta before the first refill: everything in the bitmap
 constexpr int32_t DEV_ERR_BELADY = 5;
 constexpr uint64_t BEL_RING = 64;             // bitmap words just past the window held in LDS
 constexpr uint64_t BEL_SYNC = 16;             // batches between two exchanges with the global bitmap
 static_assert(2 * BEL_SYNC <= BEL_RING, "a word entering the ring is merged before the window reaches it");
-constexpr int BEL_AHEAD = 4;                  // batches of next[] and depth[] loaded ahead
+constexpr int BEL_GROUP = 4;                  // batches whose next[], depth[] and masks are loaded together
 
 __device__ __forceinline__ uint64_t bm_load(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -115,21 +126,79 @@ __device__ __forceinline__ uint32_t checked_next(uint32_t x, uint64_t t, uint64_
     return x;
 }
 
-// number of lanes whose value v (0 = none) exceeds x: the 64 values are
-// staged in LDS and every lane reads all of them (same addresses for all
-// lanes: broadcast reads, four values per read)
-__device__ __forceinline__ uint32_t count_above(uint32_t v, uint32_t x, uint32_t *s_tmp) {
-    __syncthreads();
-    s_tmp[threadIdx.x] = v;
-    __syncthreads();
-    const uint4 *q = reinterpret_cast<const uint4 *>(s_tmp);
+// Number of the descending values buf[0 .. len) above x, from a multiple of
+// 64 on that is known to be above x (len at most 512): eight ways at a time,
+// three LDS reads in a chain where a binary search has nine.
+__device__ __forceinline__ uint32_t above_in(const uint32_t *buf, uint32_t len, uint32_t x, uint32_t from) {
     uint32_t r = 0;
 #pragma unroll
-    for (int i = 0; i < WAVE / 4; ++i) {
-        const uint4 a = q[i];
-        r += (a.x > x) + (a.y > x) + (a.z > x) + (a.w > x);
+    for (uint32_t k = 0; k < 7; ++k) {
+        const uint32_t i = from + 8 * k + 7, v = buf[i];
+        r += i < len && v > x ? 8u : 0u;
     }
-    return r;
+    r += from;
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+        const uint32_t v = buf[r + k];
+        c += r + k < len && v > x ? 1u : 0u;
+    }
+    return r + c;
+}
+__device__ __forceinline__ uint32_t above_all(const uint32_t *buf, uint32_t len, uint32_t x) {
+    uint32_t from = 0;
+    for (uint32_t i = WAVE - 1; i < len; i += WAVE) from += buf[i] > x ? (uint32_t)WAVE : 0u;
+    // (from = len when all are above)
+    return from >= len ? len : above_in(buf, len, x, from);
+}
+
+// What a batch's evictions need of next[] alone, once for all capacities: per
+// access the accesses of its batch whose next uses lie past the batch and
+// above its own (their number is its rank), and per batch the positions that
+// the batch links to inside itself.  One wave per batch.
+__global__ __launch_bounds__(4 * WAVE) void belady_rank_kernel(const uint32_t *__restrict__ next, uint64_t n,
+                                                               uint64_t *__restrict__ higher,
+                                                               uint64_t *__restrict__ links,
+                                                               int32_t *__restrict__ err) {
+    __shared__ __align__(16) uint32_t s_val[4][WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const uint64_t batches = (n + WAVE - 1) / WAVE;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * 4; b0 < batches; b0 += (uint64_t)gridDim.x * 4) {
+        const uint64_t b = b0 + w, t = b * WAVE + lane;
+        const uint32_t x = checked_next(load_next(next, t, n), t, n, err);
+        const uint64_t we = (b + 1) * WAVE;
+        const uint32_t v = x != NONE && x >= we ? x : 0u;
+        const uint64_t link = wave_or64(x != NONE && x < we ? 1ull << (x & (WAVE - 1)) : 0ull);
+        __syncthreads();
+        s_val[w][lane] = v;
+        __syncthreads();
+        const uint4 *q = reinterpret_cast<const uint4 *>(s_val[w]);
+        uint32_t m[2] = {0, 0};
+#pragma unroll
+        for (int i = 0; i < WAVE / 4; ++i) {
+            const uint4 a = q[i];
+            m[i / 8] |= (uint32_t)(a.x > v) << (4 * i % 32) | (uint32_t)(a.y > v) << (4 * i % 32 + 1) |
+                        (uint32_t)(a.z > v) << (4 * i % 32 + 2) | (uint32_t)(a.w > v) << (4 * i % 32 + 3);
+        }
+        if (t < n) higher[t] = (uint64_t)m[0] | (uint64_t)m[1] << 32;
+        if (lane == 0 && b < batches) links[b] = link;
+    }
+}
+
+// A walk over six accesses: -1 for each bit of v (an eviction), then +1 for
+// each bit of i (an insert), access by access; the table holds the lowest sum
+// met right after an eviction (none: WALK_NONE, above every sum that counts).
+constexpr int WALK = 6, WALK_GROUPS = (WAVE + WALK - 1) / WALK, WALK_NONE = 127;
+__device__ __forceinline__ int walk_low(uint32_t v, uint32_t i) {
+    int sum = 0, low = WALK_NONE;
+    for (int j = 0; j < WALK; ++j) {
+        if ((v >> j) & 1) {
+            --sum;
+            low = sum < low ? sum : low;
+        }
+        sum += (i >> j) & 1;
+    }
+    return low;
 }
 
 // ---- the simulation of one capacity
@@ -308,30 +377,83 @@ __device__ __forceinline__ uint32_t buffer_top(const BelState &S) {
 
 __device__ __forceinline__ uint32_t clamp32(uint64_t v) { return v > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)v; }
 
+// four words at any 4-byte alignment
+struct __attribute__((packed, aligned(4))) BelQuad {
+    uint32_t x, y, z, w;
+};
+struct BelGroup {
+    alignas(16) uint32_t next[BEL_GROUP][WAVE], depth[BEL_GROUP][WAVE];
+    static_assert(BEL_GROUP == 4, "a lane loads four accesses of a group");
+    alignas(16) uint64_t higher[BEL_GROUP][WAVE];
+    uint64_t link[BEL_GROUP];
+};
+
 __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__restrict__ depth, uint64_t n,
                            uint64_t c64, uint64_t *__restrict__ l0, uint64_t *__restrict__ l1, uint64_t w0,
+                           const uint64_t *__restrict__ higher, const uint64_t *__restrict__ links,
                            uint8_t *__restrict__ flags, uint64_t *hits_out, uint64_t *dsum_out, int32_t *err,
-                           uint32_t *s_a, uint32_t *s_b, uint32_t *s_new, uint32_t *s_tmp, uint64_t *s_sb,
-                           uint64_t *s_ring) {
+                           uint32_t *s_a, uint32_t *s_b, uint32_t *s_new, uint8_t *s_mark, const int8_t *s_walk,
+                           uint64_t *s_ring, BelGroup &L) {
     const int lane = threadIdx.x;
     // the global bitmap starts empty, so the ring's first words are complete
     BelState S{s_a, s_b, 0, 0, BEL_INF, 0, s_ring, BEL_RING, 0, 0, 0, w0};
     for (uint64_t i = lane; i < BEL_RING; i += WAVE) s_ring[i] = 0;
+    // (next[] that is not one-to-one leaves places of the buffer unwritten)
+    for (uint32_t i = lane; i < BEL_BUF; i += WAVE) s_a[i] = s_b[i] = 0;
+    s_new[lane] = 0;
     __syncthreads();
     // resident blocks never exceed n, so the capacity is clamped to 32 bits
     const uint32_t c = clamp32(c64 < n ? c64 : n);
     uint32_t dead = 0, size = 0;
     uint64_t hits = 0, dsum = 0;
-    // next uses and depths loaded BEL_AHEAD batches ahead (xq, dq: this batch)
-    uint32_t xa[BEL_AHEAD], da[BEL_AHEAD];
-#pragma unroll
-    for (int b = 0; b < BEL_AHEAD; ++b) {
-        const uint64_t tb = (uint64_t)b * WAVE + lane;
-        xa[b] = load_next(next, tb, n);
-        da[b] = (tb < n && depth) ? depth[tb] : 0u;
-    }
+    const int own = lane / WALK, own_at = own * WALK;   // the lane's group of the walk, its first access
+    // A group's next uses, depths and masks lie in LDS, and the next group's
+    // are on their way in registers: a batch that waited for a load of its own
+    // would wait for the newest one too, and for its inserts into the bitmap.
+    const uint64_t batches = (n + WAVE - 1) / WAVE;
+    // each lane four consecutive accesses, one load per array
+    BelQuad xa, da{0, 0, 0, 0}, ha0, ha1;
+    uint64_t lk = 0;   // the links of the group's batches, one per lane
+    auto load_group = [&](uint64_t b0) {
+        const uint64_t t = b0 * WAVE + 4 * lane;
+        if ((b0 + BEL_GROUP) * WAVE <= n) {
+            xa = *reinterpret_cast<const BelQuad *>(next + t);
+            if (depth) da = *reinterpret_cast<const BelQuad *>(depth + t);
+            ha0 = reinterpret_cast<const BelQuad *>(higher + t)[0];
+            ha1 = reinterpret_cast<const BelQuad *>(higher + t)[1];
+        } else {
+            auto one = [&](const uint32_t *p, uint64_t k, uint64_t m, uint32_t none) { return k < m ? p[k] : none; };
+            xa = BelQuad{one(next, t, n, NONE), one(next, t + 1, n, NONE), one(next, t + 2, n, NONE),
+                         one(next, t + 3, n, NONE)};
+            if (depth) da = BelQuad{one(depth, t, n, 0), one(depth, t + 1, n, 0), one(depth, t + 2, n, 0),
+                                    one(depth, t + 3, n, 0)};
+            const uint32_t *h = reinterpret_cast<const uint32_t *>(higher);
+            ha0 = BelQuad{one(h, 2 * t, 2 * n, 0), one(h, 2 * t + 1, 2 * n, 0), one(h, 2 * t + 2, 2 * n, 0),
+                          one(h, 2 * t + 3, 2 * n, 0)};
+            ha1 = BelQuad{one(h, 2 * t + 4, 2 * n, 0), one(h, 2 * t + 5, 2 * n, 0), one(h, 2 * t + 6, 2 * n, 0),
+                          one(h, 2 * t + 7, 2 * n, 0)};
+        }
+        if (lane < BEL_GROUP) lk = b0 + lane < batches ? links[b0 + lane] : 0ull;
+    };
+    load_group(0);
     for (uint64_t t0 = 0; t0 < n; t0 += WAVE) {
-        const uint32_t xq = checked_next(xa[0], t0 + lane, n, err), dq = da[0];
+        const int in_group = (int)((t0 / WAVE) % BEL_GROUP);
+        if (in_group == 0) {
+            __syncthreads();
+            const uint64_t t = t0 + 4 * lane;
+            reinterpret_cast<uint4 *>(L.next)[lane] =
+                make_uint4(checked_next(xa.x, t, n, err), checked_next(xa.y, t + 1, n, err),
+                           checked_next(xa.z, t + 2, n, err), checked_next(xa.w, t + 3, n, err));
+            reinterpret_cast<uint4 *>(L.depth)[lane] = make_uint4(da.x, da.y, da.z, da.w);
+            reinterpret_cast<uint4 *>(L.higher)[2 * lane] = make_uint4(ha0.x, ha0.y, ha0.z, ha0.w);
+            reinterpret_cast<uint4 *>(L.higher)[2 * lane + 1] = make_uint4(ha1.x, ha1.y, ha1.z, ha1.w);
+            if (lane < BEL_GROUP) L.link[lane] = lk;
+            __syncthreads();
+            load_group(t0 / WAVE + BEL_GROUP);
+        }
+        const uint32_t xq = L.next[in_group][lane], dq = L.depth[in_group][lane];
+        const uint64_t hi_mask = L.higher[in_group][lane];
+        const uint32_t rank = (uint32_t)__popcll(hi_mask);
         const uint64_t t = t0 + lane;
         const bool valid = t < n;
         const uint32_t xv = xq, dv = dq;
@@ -367,8 +489,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             if (lane == 0) S.ring[w % BEL_RING] = 0;
             __syncthreads();
         }
-        const bool inwin = xv != NONE && xv < we32;
-        const uint64_t link = wave_or64(inwin ? 1ull << (xv - t32) : 0ull);
+        const uint64_t link = readlane64(L.link[in_group], 0);   // (uniform)
         uint64_t hm = (wbits | link) & vmask;
         const uint32_t misses = (uint32_t)__popcll(vmask & ~hm);
         const uint32_t E = size + misses > c ? size + misses - c : 0u;
@@ -376,6 +497,8 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
 
         bool to_buffer, to_bitmap;
         uint32_t popped = 0;
+        uint32_t above = NONE;   // buffer values above this lane's (before any is popped), once known
+        uint32_t order = rank;   // rank among the values that go to the buffer
         if (E <= dead) {
             // nothing in the window can leave: bulk
             dead += (uint32_t)__popcll(ballot(valid && xv == NONE)) - E;
@@ -383,46 +506,17 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             to_buffer = valid && xv != NONE && xv >= we32 && (uint64_t)xv >= S.theta;
             to_bitmap = valid && xv != NONE && xv >= we32 && (uint64_t)xv < S.theta;
         } else {
-            // access by access.  The batch's inserts above the window are ranked
-            // by value; so are they jointly with the buffer's top 64 values
+            // The candidates: the batch's inserts above the window (pending) and
+            // the buffer's top 64 values, ranked jointly.
             const bool pend = valid && xv != NONE && xv >= we32;
             const uint64_t pmask = ballot(pend);
-            // pending values above this one (values are distinct)
-            const uint32_t rank = count_above(pend ? xv : 0u, xv, s_tmp);
-            __syncthreads();
-            if (pend) s_new[rank] = xv;
-            __syncthreads();
             const uint32_t np = (uint32_t)__popcll(pmask);
-            const uint32_t sorted = (uint32_t)lane < np ? s_new[lane] : 0u;
-            uint32_t top = buffer_top(S);
             const uint32_t nbt = S.bufn < (uint32_t)WAVE ? S.bufn : (uint32_t)WAVE;
-            const uint32_t th32 = clamp32(S.theta);
-            // joint rank: a pending value's rank plus the top buffer values above
-            // it; a top buffer value's index plus the pending values above it
-            uint32_t jr = 0, jb = 0;
-            if (pend) {
-                uint32_t lo = 0, hi = nbt;
-                while (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (S.buf[S.head + mid] > xv) lo = mid + 1; else hi = mid;
-                }
-                jr = rank + lo;
-            }
-            const bool isb = (uint32_t)lane < nbt;
-            if (isb) {
-                uint32_t lo = 0, hi = np;
-                while (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (s_new[mid] > top) lo = mid + 1; else hi = mid;
-                }
-                jb = (uint32_t)lane + lo;
-            }
-            const uint64_t b_lo = wave_or64(isb && jb < 64 ? 1ull << jb : 0ull);
-            const uint64_t b_hi = wave_or64(isb && jb >= 64 ? 1ull << (jb - 64) : 0ull);
-            // candidates at or above theta rank first; below them the bitmap
-            // may hold larger values, which only the general walk below handles
-            const uint32_t nhigh = nbt + (uint32_t)__popcll(ballot(pend && (uint64_t)xv >= S.theta));
-            (void)th32;
+            const uint32_t in_top = above_in(S.buf + S.head, nbt, xv, 0);   // of those, the ones above this lane's
+            if (in_top < nbt || nbt == S.bufn) above = in_top;
+            // below theta the bitmap may hold larger values, which only the
+            // general walk below handles
+            const uint64_t high = ballot(pend && (uint64_t)xv >= S.theta);
             // evictions: the misses after the cache has filled up
             uint64_t ev = vmask & ~hm;
             for (uint32_t k = size; k < c && ev; ++k) ev &= ev - 1;
@@ -435,91 +529,60 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             const uint64_t le = lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1;   // lanes up to this one
             const int64_t gap = (int64_t)__popcll(ev & le) - (int64_t)dead - (int64_t)__popcll(dm & (le >> 1));
             const uint32_t un = wave_incl_max(gap > 0 ? (uint32_t)gap : 0u);
-            const uint32_t un_prev = (uint32_t)__shfl((int)un, (lane + WAVE - 1) & (WAVE - 1), WAVE);
-            const uint64_t real = ballot(un > (lane ? un_prev : 0u));
+            // (wave_shr:1, 0 into lane 0)
+            const uint32_t un_prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)un, 0x138, 0xf, 0xf, false);
+            const uint64_t real = ballot(un > un_prev);
             const uint32_t E = (uint32_t)__popcll(real);
             // (2) Which candidates the real evictions take.  Each takes the
-            // largest one present (the lowest joint rank); the buffer's are
-            // present from the start, a pending one after its own access.  For
-            // a joint rank k let R(k) be the number of evictions that take a
-            // candidate ranked below k.  With A(k) buffer candidates below k,
-            // and r_i the count after the i-th eviction, r_i = min(r_{i-1} + 1,
-            // A(k) + P_i(k)) where P_i(k) counts the pending candidates below k
-            // inserted before it, hence R(k) = min(E, A(k) + E + m(k)) with
-            // m(k) the lowest prefix sum (from 0) of the sequence "-1 per
-            // eviction, then +1 per such insert", access by access.  The
-            // candidate of rank k is taken iff R(k + 1) > R(k).
-            s_sb[lane] = 0;
-            s_sb[lane + WAVE] = 0;
-            __syncthreads();
-            if (pend) s_sb[jr] = 1ull << lane;   // jr < 128: rank < 64, plus at most 64 buffer values
-            __syncthreads();
-            const uint64_t i0 = wave_incl_or64(s_sb[lane]), i1 = wave_incl_or64(s_sb[lane + WAVE]);
-            const uint64_t tot0 = readlane64(i0, WAVE - 1), tot1 = readlane64(i1, WAVE - 1);
-            // (the shuffles run on every lane: a lane that is off reads as 0)
-            const int prev_lane = (lane + WAVE - 1) & (WAVE - 1);
-            const uint64_t sh0 = shfl64(i0, prev_lane), sh1 = shfl64(i1, prev_lane);
-            const uint64_t below0 = lane ? sh0 : 0ull;            // access bits of pending ranks < lane
-            const uint64_t below1 = tot0 | (lane ? sh1 : 0ull);   // ranks < lane + 64
-            const uint64_t below2 = tot0 | tot1;                  // ranks < 128
-            const uint64_t lt = (1ull << lane) - 1;
-            const int a0 = __popcll(b_lo & lt), a1 = __popcll(b_lo) + __popcll(b_hi & lt);
-            const int a2 = __popcll(b_lo) + __popcll(b_hi);
-            // ranks 64 and up exist only when there are more than 64 candidates
-            const bool wide = nbt + np > (uint32_t)WAVE;
-            int r0 = 0, r2 = 0, m0 = 0, m2 = 0;
-            int r1 = 0, m1 = 0;
-            if (wide) {
+            // largest one present; the buffer's are present from the start, a
+            // pending one after its own access.  For a value x let R(x) be the
+            // number of evictions that take a candidate above x.  With A(x)
+            // buffer candidates above x, and r_i the count after the i-th
+            // eviction, r_i = min(r_{i-1} + 1, A(x) + P_i(x)) where P_i(x)
+            // counts the pending candidates above x inserted before it, hence
+            // R(x) = min(E, A(x) + E + m(x)) with m(x) the lowest sum of the
+            // walk "-1 per eviction, then +1 per such insert", access by access.
+            // x itself is taken iff counting it too makes R larger: iff the walk
+            // gets, after x's own access, below both -A(x) and every sum before.
+            // Each lane walks for its own value, six accesses per table entry.
+            int in = 0, pre = -(int)in_top, post = WALK_NONE;
+            int8_t low[WALK_GROUPS];
 #pragma unroll
-                for (int j = 0; j < WAVE; ++j) {
-                    const int pj = (int)((real >> j) & 1);
-                    r0 -= pj;
-                    r1 -= pj;
-                    r2 -= pj;
-                    m0 = r0 < m0 ? r0 : m0;
-                    m1 = r1 < m1 ? r1 : m1;
-                    m2 = r2 < m2 ? r2 : m2;
-                    r0 += (int)((below0 >> j) & 1);
-                    r1 += (int)((below1 >> j) & 1);
-                    r2 += (int)((below2 >> j) & 1);
-                }
-            } else {
+            for (int g = 0; g < WALK_GROUPS; ++g)
+                low[g] = s_walk[((uint32_t)(real >> (WALK * g)) & 63) * 64 + ((uint32_t)(hi_mask >> (WALK * g)) & 63)];
+            const uint32_t vg = (uint32_t)(real >> own_at) & 63, ig = (uint32_t)(hi_mask >> own_at) & 63;
+            const uint32_t upto = (2u << (lane - own_at)) - 1;
+            const int low_pre = s_walk[(vg & upto) * 64 + ig], low_post = s_walk[(vg & ~upto) * 64 + ig];
 #pragma unroll
-                for (int j = 0; j < WAVE; ++j) {
-                    const int pj = (int)((real >> j) & 1);
-                    r0 -= pj;
-                    r2 -= pj;
-                    m0 = r0 < m0 ? r0 : m0;
-                    m2 = r2 < m2 ? r2 : m2;
-                    r0 += (int)((below0 >> j) & 1);
-                    r2 += (int)((below2 >> j) & 1);
-                }
-                m1 = m2;   // every rank from 64 on counts all candidates
+            for (int g = 0; g < WALK_GROUPS; ++g) {
+                const int at = in - (int)__popcll(real & ((1ull << (WALK * g)) - 1));
+                const int x = at + (g == own ? low_pre : (int)low[g]);
+                if (g <= own) pre = x < pre ? x : pre;
+                const int y = at + (g == own ? low_post - (int)__popc(vg & upto) : (int)low[g]);
+                if (g >= own) post = y < post ? y : post;
+                in += (int)__popc((uint32_t)(hi_mask >> (WALK * g)) & 63);
             }
-            const int Ei = (int)E;
-            const int R0 = a0 + Ei + m0 < Ei ? a0 + Ei + m0 : Ei;   // R(lane)
-            const int R1 = a1 + Ei + m1 < Ei ? a1 + Ei + m1 : Ei;   // R(lane + 64) (= R(128) when not wide)
-            const int R2 = a2 + Ei + m2 < Ei ? a2 + Ei + m2 : Ei;   // R(128)
-            const int Rn = nhigh < (uint32_t)WAVE ? __builtin_amdgcn_readlane(R0, (int)nhigh)
-                           : nhigh < 2u * WAVE ? __builtin_amdgcn_readlane(R1, (int)nhigh - WAVE) : R2;
-            const int nxt_lane = (lane + 1) & (WAVE - 1);
-            const int R0n = __shfl(R0, nxt_lane, WAVE), R1n = __shfl(R1, nxt_lane, WAVE);
-            const int R0up = lane < WAVE - 1 ? R0n : __builtin_amdgcn_readlane(R1, 0);   // R(lane + 1)
-            const int R1up = lane < WAVE - 1 ? R1n : R2;                                  // R(lane + 65)
-            const uint64_t gl = ballot(R0up > R0), gh = ballot(R1up > R1);
-            const bool ok = Rn == Ei;
+            const uint64_t gone_if = ballot(pend && post < pre);
+            // all real evictions find a candidate at or above theta
+            const uint64_t lt = (1ull << lane) - 1;
+            const int sum = (int)__popcll(high & lt) - (int)__popcll(real & le);
+            const bool ok = ballot(((real >> lane) & 1) && sum < -(int)nbt) == 0;
             const uint32_t d = dead + (uint32_t)__popcll(dm) - ((uint32_t)__popcll(ev) - E);
-            uint64_t gone = 0;   // by pending rank
+            uint64_t gone = 0;   // lane mask
             if (ok) {
                 dead = d;
                 size = c;   // evictions happened, so the cache is full
-                popped = (uint32_t)__popcll(gl & b_lo) + (uint32_t)__popcll(gh & b_hi);
-                const bool g = jr < 64 ? (gl >> jr) & 1 : (gh >> (jr - 64)) & 1;
-                gone = ballot(pend && g);   // lane mask
+                gone = gone_if;
+                popped = E - (uint32_t)__popcll(gone);
             } else {
             // the general walk: the window in a register, a refill when the
             // buffer and the batch's inserts above theta run out, the window's
             // largest value when nothing above the window is left
+            __syncthreads();
+            if (pend) s_new[rank] = xv;
+            __syncthreads();
+            const uint32_t sorted = (uint32_t)lane < np ? s_new[lane] : 0u;
+            uint32_t top = buffer_top(S);
             uint64_t avail = 0, rgone = 0;   // by pending rank: inserted so far / evicted again
             uint64_t wreg = wbits;
             hm = 0;
@@ -542,6 +605,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
                         S.head += popped;
                         S.bufn -= popped;
                         popped = 0;
+                        above = NONE;
                         refill(S, l0, l1, we, n, rend);
                         top = buffer_top(S);
                         pb = S.bufn ? (uint32_t)__builtin_amdgcn_readlane((int)top, 0) : 0u;
@@ -572,6 +636,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             const bool alive = pend && !((gone >> lane) & 1);
             to_buffer = alive && (uint64_t)xv >= S.theta;
             to_bitmap = alive && (uint64_t)xv < S.theta;
+            order = rank - (uint32_t)__popcll(hi_mask & gone);
         }
 
         // the batch's results
@@ -591,28 +656,32 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
         const uint64_t alive = ballot(to_buffer);
         const uint32_t nn = (uint32_t)__popcll(alive);
         if (nn) {
-            // rank among the new values (all distinct), largest first
-            const uint32_t r = count_above(to_buffer ? xv : 0u, xv, s_tmp);
-            // buffer values above it (descending array: a lower bound)
-            uint32_t lo = 0, hi = S.bufn;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (S.buf[S.head + mid] > xv) lo = mid + 1; else hi = mid;
+            // (values go to the buffer from the largest on, so `order` counts
+            // from 0 without gaps); buffer values above it, after the popped ones
+            uint32_t lo;
+            if (ballot(to_buffer && above == NONE)) {
+                lo = above_all(S.buf + S.head, S.bufn, xv);
+            } else {
+                lo = above > popped ? above - popped : 0u;
             }
-            __syncthreads();   // s_new may still be read above
+            // marks at the new values' places; the others keep their order
+            __syncthreads();
+            reinterpret_cast<uint64_t *>(s_mark)[lane] = 0;
+            __syncthreads();
             if (to_buffer) {
-                s_new[r] = xv;
-                S.alt[r + lo] = xv;
+                s_new[order] = xv;
+                s_mark[order + lo] = 1;
             }
             __syncthreads();
-            for (uint32_t i = lane; i < S.bufn; i += WAVE) {
-                const uint32_t b = S.buf[S.head + i];
-                uint32_t a = 0, z = nn;   // new values above b
-                while (a < z) {
-                    const uint32_t mid = (a + z) >> 1;
-                    if (s_new[mid] > b) a = mid + 1; else z = mid;
-                }
-                S.alt[i + a] = b;
+            const uint32_t len = S.bufn + nn;
+            uint32_t before = 0;   // new values ahead of the chunk
+            for (uint32_t p0 = 0; p0 < len; p0 += WAVE) {
+                const uint32_t p = p0 + lane;
+                const bool is_new = s_mark[p] != 0;
+                const uint64_t m = ballot(is_new);
+                const uint32_t k = before + mbcnt(m);
+                if (p < len) S.alt[p] = is_new ? s_new[k] : S.buf[S.head + p - k];
+                before += (uint32_t)__popcll(m);
             }
             __syncthreads();
             uint32_t *tmp = S.buf;
@@ -634,15 +703,6 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
         // every BEL_SYNC batches: the ring against the global bitmap, for the
         // next batch's ring end
         if ((w + 1) % BEL_SYNC == 0) ring_sync(S, l0, l1, rend + 1, false);
-        // the loads BEL_AHEAD batches ahead
-#pragma unroll
-        for (int b = 0; b + 1 < BEL_AHEAD; ++b) {
-            xa[b] = xa[b + 1];
-            da[b] = da[b + 1];
-        }
-        const uint64_t tn = t + (uint64_t)BEL_AHEAD * WAVE;
-        xa[BEL_AHEAD - 1] = load_next(next, tn, n);
-        da[BEL_AHEAD - 1] = (tn < n && depth) ? depth[tn] : 0u;
     }
     if (lane == 0) {
         *hits_out = hits;
@@ -654,11 +714,16 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
                                                       const uint32_t *__restrict__ depth, uint64_t n,
                                                       const uint64_t *__restrict__ caps, uint64_t *__restrict__ l0s,
                                                       uint64_t *__restrict__ l1s, uint64_t w0, uint64_t w1,
+                                                      const uint64_t *__restrict__ higher,
+                                                      const uint64_t *__restrict__ links,
                                                       uint64_t *__restrict__ hits, uint64_t *__restrict__ dsum,
                                                       uint8_t *__restrict__ flags, int32_t *__restrict__ err) {
     __shared__ uint32_t s_a[BEL_BUF], s_b[BEL_BUF], s_new[WAVE];
-    __shared__ __align__(16) uint32_t s_tmp[WAVE];
-    __shared__ uint64_t s_sb[2 * WAVE];
+    __shared__ __align__(8) uint8_t s_mark[8 * WAVE];
+    __shared__ int8_t s_walk[64 * 64];
+    __shared__ BelGroup s_group;
+    for (int i = threadIdx.x; i < 64 * 64; i += WAVE) s_walk[i] = (int8_t)walk_low((uint32_t)i / 64, (uint32_t)i % 64);
+    __syncthreads();
     __shared__ uint64_t s_ring[BEL_RING];
     const uint32_t k = blockIdx.x;
     const uint64_t c = caps[k];
@@ -672,8 +737,8 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
         }
         return;
     }
-    belady_one(next, depth, n, c, l0s + (uint64_t)k * w0, l1s + (uint64_t)k * w1, w0, fl, hits + k, dsum + k, err,
-               s_a, s_b, s_new, s_tmp, s_sb, s_ring);
+    belady_one(next, depth, n, c, l0s + (uint64_t)k * w0, l1s + (uint64_t)k * w1, w0, higher, links,
+               fl, hits + k, dsum + k, err, s_a, s_b, s_new, s_mark, s_walk, s_ring, s_group);
 }
 
 // bitmap words per capacity: one bit per position plus a word of slack, and
@@ -681,13 +746,28 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
 static uint64_t bel_w0(uint64_t n) { return (n + 2 * WAVE) / 64 + 1; }
 static uint64_t bel_w1(uint64_t n) { return bel_w0(n) / 64 + 2; }
 
+struct BelWs {
+    int32_t *hdr;
+    uint64_t *l0, *l1, *links, *higher;
+    size_t bytes;
+};
+static BelWs bel_ws(void *ws, uint64_t n, uint32_t n_caps) {
+    Carver c{(char *)ws, 0};
+    BelWs w;
+    w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
+    w.l0 = c.take<uint64_t>(n_caps * (bel_w0(n) + bel_w1(n)));
+    w.l1 = w.l0 + n_caps * bel_w0(n);
+    w.links = c.take<uint64_t>((n + WAVE - 1) / WAVE);
+    w.higher = c.take<uint64_t>(n);
+    w.bytes = c.off;
+    return w;
+}
+
 }  // namespace pc
 
 extern "C" {
 
-size_t pc_belady_ws(uint64_t n, uint32_t n_caps) {
-    return pc::WS_HEADER + pc::align_up((size_t)n_caps * (pc::bel_w0(n) + pc::bel_w1(n)) * sizeof(uint64_t));
-}
+size_t pc_belady_ws(uint64_t n, uint32_t n_caps) { return pc::bel_ws(nullptr, n, n_caps).bytes; }
 
 pc_status pc_belady(const uint32_t *next, const uint32_t *depth, uint64_t n, const uint64_t *caps, uint32_t n_caps,
                     uint64_t *hits, uint64_t *depthsum, uint8_t *hit_flags, void *ws, size_t ws_bytes,
@@ -699,16 +779,20 @@ pc_status pc_belady(const uint32_t *next, const uint32_t *depth, uint64_t n, con
     if (!ws) return PC_ERR_WORKSPACE;
     if (ws_bytes < pc_belady_ws(n, n_caps)) return PC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    int32_t *hdr = reinterpret_cast<int32_t *>(ws);
-    uint64_t *l0 = reinterpret_cast<uint64_t *>((char *)ws + pc::WS_HEADER);
+    const pc::BelWs w = pc::bel_ws(ws, n, n_caps);
     const uint64_t w0 = pc::bel_w0(n), w1 = pc::bel_w1(n);
-    uint64_t *l1 = l0 + (uint64_t)n_caps * w0;
-    pc_status st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(hdr), 0u, 1, s)) != PC_OK) return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(l0), 0u, 2 * (size_t)n_caps * (w0 + w1), s)) != PC_OK)
-        return st;
-    PC_LAUNCH(pc::K_BELADY, pc::belady_kernel, dim3(n_caps), dim3(pc::WAVE), 0, s, next, depth, n, caps, l0, l1, w0,
-              w1, hits, depthsum, hit_flags, hdr);
+    pc::Fills f;
+    f.add(w.hdr, 0u, 1);
+    f.add(w.l0, 0u, 2 * (size_t)n_caps * (w0 + w1));
+    const pc_status st = pc::fill_all(f, s);
+    if (st != PC_OK) return st;
+    if (n > 0) {
+        const uint64_t groups = (n + 4 * pc::WAVE - 1) / (4 * pc::WAVE), most = (uint64_t)pc::device_cus() * 16;
+        PC_LAUNCH(pc::K_BELADY_RANK, pc::belady_rank_kernel, dim3((unsigned)(groups < most ? groups : most)),
+                  dim3(4 * pc::WAVE), 0, s, next, n, w.higher, w.links, w.hdr);
+    }
+    PC_LAUNCH(pc::K_BELADY, pc::belady_kernel, dim3(n_caps), dim3(pc::WAVE), 0, s, next, depth, n, caps, w.l0, w.l1, w0,
+              w1, w.higher, w.links, hits, depthsum, hit_flags, w.hdr);
     return PC_OK;
 }
 

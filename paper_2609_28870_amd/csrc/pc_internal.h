@@ -73,6 +73,7 @@ enum KernelId {
     K_RUNS_COMPACT,
     K_RUNS_MERGE,
     K_RUNS_FILL,
+    K_BELADY_RANK,
     K_BELADY,
     K_MRC_MAP,
     K_COUNT

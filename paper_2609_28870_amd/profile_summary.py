@@ -55,7 +55,8 @@ IDS = {"pc::hash_kernel": "hash_blocks", "pc::hash_classes_kernel": "hash_order"
        "pc::runs_count_kernel": "runs_count", "pc::runs_scan_tiles_kernel": "runs_scan",
        "pc::runs_scan_kernel": "runs_scan", "pc::runs_compact_kernel": "runs_compact",
        "pc::runs_block_kernel": "runs_merge", "pc::runs_merge_kernel": "runs_merge",
-       "pc::runs_fill_kernel": "runs_fill", "pc::belady_kernel": "belady"}
+       "pc::runs_fill_kernel": "runs_fill", "pc::belady_rank_kernel": "belady_rank",
+       "pc::belady_kernel": "belady"}
 
 
 def kernel_name(s):

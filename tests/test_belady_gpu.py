@@ -71,6 +71,19 @@ def test_random_streams(seed):
     check_against_oracle(keys, CAPS, depth)
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 511, 4095, 4097, 16385])
+@pytest.mark.parametrize("distinct", [40, 300, 3000])
+def test_stream_lengths_around_batches_and_groups(n, distinct):
+    # batches of 64 accesses, loaded four at a time; capacities about the
+    # buffer's fill and the 64 values that a batch's evictions may take
+    rng = np.random.default_rng(n + distinct)
+    keys = rng.integers(0, distinct, size=n).astype(np.uint64)
+    keys[n // 2:] = np.minimum(keys[n // 2:], distinct // 2)
+    depth = rng.integers(0, 5000, size=n).astype(np.uint32)
+    check_against_oracle(keys, [1, 2, 5, 31, 32, 33, 60, 63, 64, 65, 96, 127, 128, 129, 192, 256, 257, 320, 700, 1500],
+                         depth)
+
+
 def test_looping_scan_and_degenerate_streams():
     # a cyclic scan one block larger than the cache: MIN keeps c - 1 of the
     # loop's blocks per round
