@@ -43,10 +43,16 @@ constexpr int SORT_THREADS = 512;
 constexpr int SORT_WAVES = SORT_THREADS / WAVE;
 constexpr int SORT_ITEMS = 16;
 constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;   // 8192
+// Small calls take small tiles: with few tiles a pass is one tile's latency.
+// us per pass with tiles of 2048 / 4096 / 8192 keys, launch included: 1400 to
+// 6000 keys 8.8 10.2 13.0, 4.5e4 11.1 11.1 13.0, 4.5e5 18.9 18.6 19.4, 1.0e6
+// 26 20 21 (the runs of a tile's digits in the output get short).
+constexpr uint64_t SORT_MAX_4 = 1u << 18, SORT_MAX_8 = 1u << 20;
 constexpr int SORT_PASSES = 8;
 constexpr uint64_t FLAG_AGG = 1ull << 32;
 constexpr uint64_t FLAG_INC = 1ull << 33;
 constexpr uint32_t SPIN_LIMIT = 1u << 22;
+constexpr int LOOKBACK = 4;   // tiles per look-back step (33.5 M keys: 223 us a pass, one at a time 229, 8 228)
 
 // Words of the control block (zeroed before each call): tile counters of the
 // passes, tickets, and for the persistent kernel a chunk counter and a count
@@ -128,8 +134,9 @@ __global__ __launch_bounds__(256) void sort_hist_kernel(const uint64_t *__restri
 // staged twice through one buffer (keys, then values) and the per-wave digit
 // counters are 16-bit (a tile holds at most 8192 elements), which keeps two
 // workgroups on a CU
+template <int ITEMS>
 struct SortLds {
-    uint64_t stage[SORT_TILE];
+    uint64_t stage[ITEMS * SORT_THREADS];
     uint16_t wcnt[SORT_WAVES][RADIX];
     uint32_t lstart[RADIX];
     uint32_t gbase[RADIX];
@@ -140,10 +147,12 @@ struct SortLds {
 // One tile of a pass: the workgroup takes the next tile from the counter
 // (tiles are handed out in order, so every tile a look-back waits on belongs
 // to a workgroup already running it); false when none is left.
-__device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, const uint32_t *vals_in,
+template <int ITEMS>
+__device__ __forceinline__ bool sort_tile(SortLds<ITEMS> &L, const uint64_t *keys_in, const uint32_t *vals_in,
                                           uint64_t *keys_out, uint32_t *vals_out, uint64_t n, int shift,
                                           const uint32_t *start, uint64_t *status, uint32_t *counter, uint32_t epoch,
                                           int32_t *err) {
+    constexpr int TILE = ITEMS * SORT_THREADS;
     // (an opaque copy: in a loop over tiles what is derived from it is worked
     // out per tile instead of being held, and spilled, across the loop)
     int tid = threadIdx.x;
@@ -154,16 +163,16 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, c
     for (int i = tid; i < SORT_WAVES * RADIX / 2; i += SORT_THREADS) reinterpret_cast<uint32_t *>(&L.wcnt[0][0])[i] = 0;
     __syncthreads();
     const uint32_t tile = L.tile;
-    const uint64_t base = (uint64_t)tile * SORT_TILE;
+    const uint64_t base = (uint64_t)tile * TILE;
     if (base >= n) return false;
 
-    uint64_t k[SORT_ITEMS];
-    uint32_t v[SORT_ITEMS];
-    uint32_t pos[SORT_ITEMS];
-    bool ok[SORT_ITEMS];
+    uint64_t k[ITEMS];
+    uint32_t v[ITEMS];
+    uint32_t pos[ITEMS];
+    bool ok[ITEMS];
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
-        const uint64_t idx = base + (uint64_t)(w * SORT_ITEMS + j) * WAVE + lane;
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint64_t idx = base + (uint64_t)(w * ITEMS + j) * WAVE + lane;
         ok[j] = idx < n;
         k[j] = ok[j] ? keys_in[idx] : 0ull;
         v[j] = ok[j] ? (vals_in ? vals_in[idx] : (uint32_t)idx) : 0u;
@@ -171,7 +180,7 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, c
     // stable rank inside the wave: lanes with the same digit are matched by
     // eight ballots; a per-wave running count orders the wave's chunks
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         const uint32_t d = (uint32_t)(k[j] >> shift) & 0xFF;
         const uint64_t m = match_digit<8>(d, ballot(ok[j]));
         const uint32_t before = mbcnt(m);
@@ -194,7 +203,7 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, c
     if (tid < RADIX) L.lstart[tid] = lst;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         if (ok[j]) {
             const uint32_t d = (uint32_t)(k[j] >> shift) & 0xFF;
             pos[j] += L.lstart[d] + L.wcnt[w][d];
@@ -210,40 +219,54 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, c
             st_status64(mine, ep | FLAG_INC | cnt);
         } else {
             st_status64(mine, ep | FLAG_AGG | cnt);
+            // LOOKBACK tiles at a time: the tiles of a small call all start
+            // together, and then a tile has about half the earlier ones to add
             int64_t j = (int64_t)tile - 1;
             uint32_t spins = 0;
             while (j >= 0) {
-                const uint64_t x = ld_status64(status + (uint64_t)j * RADIX + tid);
-                if ((x >> 34) != epoch || (x & (FLAG_AGG | FLAG_INC)) == 0) {
+                uint64_t x[LOOKBACK];
+#pragma unroll
+                for (int b = 0; b < LOOKBACK; ++b)
+                    x[b] = ld_status64(status + (uint64_t)(j >= b ? j - b : 0) * RADIX + tid);
+                bool done = false, wait = false;
+#pragma unroll
+                for (int b = 0; b < LOOKBACK; ++b) {
+                    if (done || wait || j < 0) continue;
+                    if ((x[b] >> 34) != epoch || (x[b] & (FLAG_AGG | FLAG_INC)) == 0) {
+                        wait = true;
+                    } else {
+                        excl += (uint32_t)x[b];
+                        done = (x[b] & FLAG_INC) != 0;
+                        --j;
+                    }
+                }
+                if (done) break;
+                if (wait) {
                     if (++spins > SPIN_LIMIT) {
                         atomicOr(err, DEV_ERR_LOOKBACK_TIMEOUT);
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
-                    continue;
                 }
-                excl += (uint32_t)x;
-                if (x & FLAG_INC) break;
-                --j;
             }
             st_status64(mine, ep | FLAG_INC | (uint32_t)(excl + cnt));
         }
         L.gbase[tid] = start[tid] + excl - lst;
         // the last tile holds every digit's total: it must fill the digit's
         // range exactly (a caller's histogram that does not match the keys)
-        if ((uint64_t)(tile + 1) * SORT_TILE >= n) {
+        if ((uint64_t)(tile + 1) * TILE >= n) {
             const uint32_t hi = tid + 1 < RADIX ? start[tid + 1] : (uint32_t)n;
             if (start[tid] + excl + cnt != hi) atomicOr(err, DEV_ERR_BAD_HIST);
         }
     }
     __syncthreads();
     const uint64_t left = n - base;
-    const uint32_t n_tile = left < (uint64_t)SORT_TILE ? (uint32_t)left : (uint32_t)SORT_TILE;
+    const uint32_t n_tile = left < (uint64_t)TILE ? (uint32_t)left : (uint32_t)TILE;
     // keys out, remembering each slot's destination for the values (a
     // histogram that does not match the keys cannot send a write outside)
-    uint32_t dst[SORT_ITEMS];
+    uint32_t dst[ITEMS];
 #pragma unroll
-    for (int r = 0; r < SORT_ITEMS; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t i = (uint32_t)(tid + r * SORT_THREADS);
         dst[r] = NONE;
         if (i < n_tile) {
@@ -255,17 +278,18 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint64_t *keys_in, c
     __syncthreads();
     uint32_t *s_val = reinterpret_cast<uint32_t *>(L.stage);
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j)
+    for (int j = 0; j < ITEMS; ++j)
         if (ok[j]) s_val[pos[j]] = v[j];
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < SORT_ITEMS; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t i = (uint32_t)(tid + r * SORT_THREADS);
         if (i < n_tile && dst[r] < n) vals_out[dst[r]] = s_val[i];
     }
     return true;
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(SORT_THREADS, 4) void sort_pass_kernel(
     const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in,
     uint64_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out, uint64_t n, int shift,
@@ -277,8 +301,8 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_pass_kernel(
     // Workgroups past the tile count take no tile (the counter then hands
     // out exactly the tiles there are) and leave at once: a grid sized for a
     // bound well above a device count costs little.
-    if ((uint64_t)blockIdx.x * SORT_TILE >= n) return;
-    __shared__ SortLds L;
+    if ((uint64_t)blockIdx.x * (ITEMS * SORT_THREADS) >= n) return;
+    __shared__ SortLds<ITEMS> L;
     sort_tile(L, keys_in, vals_in, keys_out, vals_out, n, shift, start, status, counter, epoch, err);
 }
 
@@ -853,6 +877,11 @@ void sort_ctl_clear(Fills &f, const SortCtl &k) {
     f.add(k.hist, 0u, k.zero_words);
 }
 
+// tiles of a sort pass over n keys
+static uint64_t pass_tiles(uint64_t n) {
+    const uint64_t t = n <= SORT_MAX_4 ? 4 * SORT_THREADS : n <= SORT_MAX_8 ? 8 * SORT_THREADS : SORT_TILE;
+    return (n + t - 1) / t;
+}
 struct SortBufs {
     uint64_t *k1, *k2;   // sort ping-pong; afterwards (prev, next) pairs
     uint32_t *v1, *v2;   // sort ping-pong; afterwards times t
@@ -864,7 +893,11 @@ static SortBufs take_bufs(Carver &c, uint64_t n) {
     b.k2 = c.take<uint64_t>(n);
     b.v1 = c.take<uint32_t>(n);
     b.v2 = c.take<uint32_t>(n);
-    b.status = c.take<uint64_t>((n + SORT_TILE - 1) / SORT_TILE * RADIX);
+    // (at least the smaller tiles' words, so that a larger n never needs less)
+    uint64_t tiles = pass_tiles(n);
+    for (const uint64_t m : {SORT_MAX_4, SORT_MAX_8})
+        if (n > m && tiles < pass_tiles(m)) tiles = pass_tiles(m);
+    b.status = c.take<uint64_t>(tiles * RADIX);
     return b;
 }
 size_t sort_bufs_bytes(uint64_t n) {
@@ -901,7 +934,7 @@ struct SortJob {
 };
 
 union PersistentLds {
-    SortLds sort;
+    SortLds<SORT_ITEMS> sort;
     PermLds<LINK_TILE, SORT_THREADS, LINK_RADIX> link;
     PermLds<PERM_TILE, PART_THREADS, PERM_RADIX> perm;
     uint32_t hist[HIST_DIGITS * RADIX];
@@ -1048,7 +1081,7 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     Carver c{(char *)bufs, 0};
     const SortBufs b = take_bufs(c, n);
     if (n == 0) return PC_OK;
-    const uint64_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
+    const uint64_t tiles = pass_tiles(n);
     const int cus = device_cus();
     // The plan is made for the bound n: with fewer elements its later buckets
     // stay empty.
@@ -1070,9 +1103,11 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     for (int p = 0; p < SORT_PASSES / 2; ++p) {
         uint64_t *kout = (p & 1) ? b.k2 : b.k1;
         uint32_t *vout = (p & 1) ? b.v2 : b.v1;
-        PC_LAUNCH(K_SORT_PASS, sort_pass_kernel, dim3((unsigned)tiles), dim3(SORT_THREADS), 0, s, kin, vin, kout,
-                  vout, n, 8 * p, k.start + p * RADIX, b.status, k.words + CTL_TILE + p, (uint32_t)(p + 1), k.hdr,
-                  n_dev, gate);
+        const auto pass = n <= SORT_MAX_4   ? sort_pass_kernel<4>
+                          : n <= SORT_MAX_8 ? sort_pass_kernel<8>
+                                            : sort_pass_kernel<SORT_ITEMS>;
+        PC_LAUNCH(K_SORT_PASS, pass, dim3((unsigned)tiles), dim3(SORT_THREADS), 0, s, kin, vin, kout, vout, n, 8 * p,
+                  k.start + p * RADIX, b.status, k.words + CTL_TILE + p, (uint32_t)(p + 1), k.hdr, n_dev, gate);
         kin = kout;
         vin = vout;
     }
@@ -1087,7 +1122,8 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     // the passes over the high bits and a second link, if the first one met a
     // mixed run too long to scan (header word 1)
     const SortJob j{keys, n, n_dev, key_hist, k, b, pp, cus, false, RareGate{}};
-    PC_LAUNCH(K_SORT_HIGH, sort_persistent_kernel, dim3(capped(tiles, 2)), dim3(SORT_THREADS), 0, s, j, gate);
+    PC_LAUNCH(K_SORT_HIGH, sort_persistent_kernel, dim3(capped((n + SORT_TILE - 1) / SORT_TILE, 2)),
+              dim3(SORT_THREADS), 0, s, j, gate);
     uint32_t *bt[2] = {b.v1, b.v2};
     uint64_t *bpn[2] = {b.k1, b.k2};
     for (int i = 1; i < pp.passes; ++i) {

@@ -1,5 +1,5 @@
 """The size rules inside prev / next and the stack distance, at the sizes where
-they change: run counts around a merge block of 2048 and its eightfolds, the
+they change: the sort's tiles, run counts around a merge block of 2048 and its eightfolds, the
 dominance count as one launch and as several, the passes over the high key
 bits, and the generic prev / next behind the chained one as one launch and as
 several; and the bins where their value classes, chunks and workgroup sizes
@@ -69,6 +69,22 @@ def test_high_key_bits(n):
     p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
     assert pc.high_key_passes_ran(ws) and pc.workspace_status(ws) == 0
     assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 4097, (1 << 18) - 1, 1 << 18, (1 << 18) + 1, (1 << 20) - 1, 1 << 20,
+                               (1 << 20) + 1, (1 << 20) + 8193])
+def test_sort_tile_sizes(n):
+    keys = device_keys(n, max(2, n // 3))
+    prev, nxt, ws = pc.prev_next_use(keys)
+    p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
+    assert pc.workspace_status(ws) == 0
+    assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+
+
+def test_a_larger_call_never_needs_less_workspace():
+    sizes = [pc.lib().pc_prev_next_use_ws(n) for k in (11, 18, 20, 21, 22) for n in range((1 << k) - 8200, (1 << k) + 8200, 511)
+             if n > 0]
+    assert sizes == sorted(sizes)
 
 
 @pytest.mark.parametrize("n,low_shared",
