@@ -12,9 +12,21 @@ constexpr int PROF_THREADS = 256;
 constexpr int PROF_WAVES = PROF_THREADS / WAVE;
 constexpr int PROF_QUEUE = 128;   // pending chain starts per wave (>= 64 idle lanes + one 64-wide scan)
 
-// bin of x over edges[0..k): the number of edges <= x (edges non-decreasing)
-__device__ __forceinline__ uint32_t edge_bin(const uint64_t *e, uint32_t k, uint64_t x) {
-    uint32_t lo = 0, hi = k;
+// Bin of x over edges[0..k): the number of edges <= x (edges non-decreasing).
+// Values are in classes, eight to an octave (below eight one each); per class
+// the table holds the number of edges below it, so that mostly one edge or
+// none is left to compare where a whole search is a chain of six LDS reads and
+// more (the walk over 2.0e8 accesses: 1.74 ms, with the table 1.38).
+constexpr uint32_t TIME_CLASSES = 8 + 61 * 8;
+__device__ __forceinline__ uint32_t time_class(uint64_t x) {
+    if (x < 8) return (uint32_t)x;
+    const int e = 60 - __clzll((long long)x);   // the three bits below the leading one
+    return 8 + (uint32_t)e * 8 + ((uint32_t)(x >> e) & 7);
+}
+__device__ __forceinline__ uint64_t time_class_start(uint32_t c) {
+    return c < 8 ? c : (uint64_t)(8 + (c & 7)) << (c / 8 - 1);
+}
+__device__ __forceinline__ uint32_t edge_bin(const uint64_t *e, uint32_t lo, uint32_t hi, uint64_t x) {
     while (lo < hi) {
         const uint32_t mid = (lo + hi) >> 1;
         if (e[mid] <= x) lo = mid + 1;
@@ -39,7 +51,15 @@ __global__ __launch_bounds__(256) void prof_pack_kernel(const uint32_t *__restri
             if (lane == 0) atomicOr(err, DEV_ERR_BAD_LAYOUT);
             continue;
         }
-        for (uint64_t t = a + lane; t < b; t += WAVE) packed[t] = (uint64_t)next[t] | ((uint64_t)r << 32);
+        uint64_t t = a + lane;
+        for (uint64_t base = a; b - base >= 8 * WAVE; base += 8 * WAVE, t += 8 * WAVE) {
+            uint32_t x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = next[t + k * WAVE];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) packed[t + k * WAVE] = (uint64_t)x[k] | ((uint64_t)r << 32);
+        }
+        for (; t < b; t += WAVE) packed[t] = (uint64_t)next[t] | ((uint64_t)r << 32);
     }
 }
 
@@ -62,6 +82,7 @@ __global__ __launch_bounds__(PROF_THREADS) void prof_walk_kernel(
     // histograms leave room for more waves, and the walk is latency-bound
     extern __shared__ uint64_t smem[];
     __shared__ uint32_t s_queue[PROF_WAVES][PROF_QUEUE];
+    __shared__ uint8_t s_below[TIME_CLASSES + 1];   // at most PC_MAX_PROFILE_EDGES
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int wv = tid / WAVE;
@@ -78,6 +99,15 @@ __global__ __launch_bounds__(PROF_THREADS) void prof_walk_kernel(
     for (uint32_t i = tid; i < PC_FREQ_CLASSES * kb; i += PROF_THREADS) s_class[i] = 0;
     for (uint32_t i = tid; i <= freq_max; i += PROF_THREADS) s_freq[i] = 0;
     __syncthreads();
+    for (uint32_t k = tid; k <= TIME_CLASSES; k += PROF_THREADS)
+        s_below[k] = (uint8_t)(k == 0              ? 0u
+                               : k == TIME_CLASSES ? n_edges
+                                                   : edge_bin(s_edges, 0, n_edges, time_class_start(k) - 1));
+    __syncthreads();
+    auto bin_of = [&](uint64_t x) {
+        const uint32_t k = time_class(x);
+        return edge_bin(s_edges, s_below[k], s_below[k + 1], x);
+    };
 
     const uint64_t chunks = (n + WAVE - 1) / WAVE;
     const uint64_t stride = (uint64_t)gridDim.x * PROF_WAVES;
@@ -124,14 +154,14 @@ __global__ __launch_bounds__(PROF_THREADS) void prof_walk_kernel(
             if (f == 0) {
                 ts_first = ts;
             } else {
-                atomicAdd(&s_ival[edge_bin(s_edges, n_edges, ts - ts_last)], 1u);
+                atomicAdd(&s_ival[bin_of(ts - ts_last)], 1u);
             }
             ts_last = ts;
             ++f;
             if (ends) {   // anything but a later position ends the chain
                 if (nx != NONE) atomicOr(err, DEV_ERR_BAD_LAYOUT);
                 const uint32_t cls = 31u - (uint32_t)__builtin_clz(f);
-                atomicAdd(&s_class[cls * kb + edge_bin(s_edges, n_edges, ts_last - ts_first)], 1u);
+                atomicAdd(&s_class[cls * kb + bin_of(ts_last - ts_first)], 1u);
                 atomicAdd(&s_freq[f < freq_max ? f : freq_max], 1u);
                 active = false;
             } else {
@@ -190,21 +220,23 @@ pc_status pc_reuse_profile(const uint32_t *prev, const uint32_t *next, const uin
     if (ws_bytes < pc_reuse_profile_ws(n)) return PC_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     pc::ProfWs w = pc::carve_prof(ws, n);
-    pc_status st = pc::fill_u32(reinterpret_cast<uint32_t *>(w.hdr), 0u, 1, s);
-    if (st != PC_OK) return st;
     const size_t kb = (size_t)n_edges + 1;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(interval), 0u, 2 * kb, s)) != PC_OK) return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(lifetime), 0u, 2 * kb, s)) != PC_OK) return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(freq), 0u, 2 * ((size_t)freq_max + 1), s)) != PC_OK)
-        return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(life_by_class), 0u, 2 * kb * PC_FREQ_CLASSES, s)) != PC_OK)
-        return st;
+    pc::Fills fills;
+    fills.add(w.hdr, 0u, 1);
+    fills.add(interval, 0u, 2 * kb);
+    fills.add(lifetime, 0u, 2 * kb);
+    fills.add(freq, 0u, 2 * ((size_t)freq_max + 1));
+    fills.add(life_by_class, 0u, 2 * kb * PC_FREQ_CLASSES);
+    const pc_status st = pc::fill_all(fills, s);
+    if (st != PC_OK) return st;
     if (n == 0) return PC_OK;
     const int cus = pc::device_cus();
-    uint64_t pg = ((uint64_t)n_seqs + 3) / 4;
-    if (pg > (uint64_t)cus * 64) pg = (uint64_t)cus * 64;   // 64 per CU: 5.9 -> 5.3 ms on the full trace
-    PC_LAUNCH(pc::K_PROF_PACK, pc::prof_pack_kernel, dim3((unsigned)pg), dim3(256), 0, s, next, blk_off, n_seqs, n,
-              w.packed, w.hdr);
+    // workgroups of one wave where requests are long, as they differ in length
+    const unsigned pw = n / n_seqs >= 256 ? 1 : 4;
+    uint64_t pg = ((uint64_t)n_seqs + pw - 1) / pw;
+    if (pg > (uint64_t)cus * (pw == 1 ? 1024 : 64)) pg = (uint64_t)cus * (pw == 1 ? 1024 : 64);
+    PC_LAUNCH(pc::K_PROF_PACK, pc::prof_pack_kernel, dim3((unsigned)pg), dim3(pw * pc::WAVE), 0, s, next, blk_off,
+              n_seqs, n, w.packed, w.hdr);
     const uint64_t chunks = (n + pc::WAVE - 1) / pc::WAVE;
     uint64_t grid = (chunks + pc::PROF_WAVES - 1) / pc::PROF_WAVES;
     if (grid > (uint64_t)cus * 7) grid = (uint64_t)cus * 7;   // about one resident round

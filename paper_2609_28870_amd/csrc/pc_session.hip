@@ -358,15 +358,15 @@ pc_status pc_session_profile(const uint64_t *blk_off, const uint32_t *session, c
     int32_t *hdr = c.take<int32_t>(pc::WS_HEADER / sizeof(int32_t));
     pc::SessLinks l;
     pc::take_links(c, n_seqs, l);
-    pc_status st = pc::fill_u32(reinterpret_cast<uint32_t *>(hdr), 0u, 1, s);
-    if (st != PC_OK) return st;
     const size_t kb = (size_t)n_edges + 1;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(footprint), 0u, 2 * ((size_t)fp_max + 1), s)) != PC_OK)
-        return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(requests), 0u, 2 * ((size_t)rq_max + 1), s)) != PC_OK)
-        return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(duration), 0u, 2 * kb, s)) != PC_OK) return st;
-    if ((st = pc::fill_u32(reinterpret_cast<uint32_t *>(gap), 0u, 2 * kb, s)) != PC_OK) return st;
+    pc::Fills fills;
+    fills.add(hdr, 0u, 1);
+    fills.add(footprint, 0u, 2 * ((size_t)fp_max + 1));
+    fills.add(requests, 0u, 2 * ((size_t)rq_max + 1));
+    fills.add(duration, 0u, 2 * kb);
+    fills.add(gap, 0u, 2 * kb);
+    pc_status st = pc::fill_all(fills, s);
+    if (st != PC_OK) return st;
     if (n_seqs == 0) return PC_OK;
     if ((st = pc::link_sessions(session, n_seqs, l, hdr, s)) != PC_OK) return st;
     const int cus = pc::device_cus();

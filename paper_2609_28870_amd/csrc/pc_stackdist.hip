@@ -779,9 +779,14 @@ __global__ __launch_bounds__(LOC_THREADS, 6) void sd_local_kernel(
 // the last use of any shallower block of its chain, and each request lists
 // its shallower blocks after its deeper ones.  Other key streams take a
 // direct count over [s, t) for the accesses that break the order.
-// One wave per request (grid-stride), REQ_ITEMS x 64 accesses per step.
+// One wave per request (grid-stride), REQ_ITEMS x 64 accesses per step.  Bound:
+// the reads of prev and dist, now that a step's are under way during the one
+// before (6.0e7 accesses 0.168 ms, 4.3 TB/s; loaded step by step in workgroups
+// of four waves 0.318).
 constexpr int REQ_ITEMS = 8;
 
+// AHEAD: for long requests, whole steps with the next one's loads on their way.
+template <bool AHEAD>
 __global__ __launch_bounds__(256) void req_dist_kernel(const uint32_t *__restrict__ prev,
                                                        const uint32_t *__restrict__ dist,
                                                        const uint64_t *__restrict__ blk_off, uint32_t n_seqs,
@@ -798,15 +803,8 @@ __global__ __launch_bounds__(256) void req_dist_kernel(const uint32_t *__restric
             continue;
         }
         uint32_t carry = 0;   // max v over the request's accesses before this step
-        for (uint64_t base = s; base < e; base += REQ_ITEMS * WAVE) {
-            uint32_t v[REQ_ITEMS], d[REQ_ITEMS];
-#pragma unroll
-            for (int i = 0; i < REQ_ITEMS; ++i) {
-                const uint64_t t = base + i * WAVE + lane;
-                const bool ok = t < e;
-                v[i] = ok ? prev[t] + 1u : 0u;
-                d[i] = ok ? dist[t] : 0u;
-            }
+        uint32_t v[REQ_ITEMS], d[REQ_ITEMS];
+        auto step = [&](uint64_t base) {
 #pragma unroll
             for (int i = 0; i < REQ_ITEMS; ++i) {
                 const uint64_t t = base + i * WAVE + lane;
@@ -826,6 +824,37 @@ __global__ __launch_bounds__(256) void req_dist_kernel(const uint32_t *__restric
                     dist_req[t] = d[i] - c;
                 }
             }
+        };
+        uint64_t base = s;
+        if (AHEAD && e - s >= REQ_ITEMS * WAVE) {
+            uint32_t pn[REQ_ITEMS], dn[REQ_ITEMS];
+            auto fetch = [&](uint64_t at) {
+#pragma unroll
+                for (int i = 0; i < REQ_ITEMS; ++i) {
+                    pn[i] = prev[at + i * WAVE + lane];
+                    dn[i] = dist[at + i * WAVE + lane];
+                }
+            };
+            fetch(base);
+            for (; e - base >= REQ_ITEMS * WAVE; base += REQ_ITEMS * WAVE) {
+#pragma unroll
+                for (int i = 0; i < REQ_ITEMS; ++i) {
+                    v[i] = pn[i] + 1u;
+                    d[i] = dn[i];
+                }
+                if (e - base >= 2 * REQ_ITEMS * WAVE) fetch(base + REQ_ITEMS * WAVE);
+                step(base);
+            }
+        }
+        for (; base < e; base += REQ_ITEMS * WAVE) {
+#pragma unroll
+            for (int i = 0; i < REQ_ITEMS; ++i) {
+                const uint64_t t = base + i * WAVE + lane;
+                const bool ok = t < e;
+                v[i] = ok ? prev[t] + 1u : 0u;
+                d[i] = ok ? dist[t] : 0u;
+            }
+            step(base);
         }
     }
 }
@@ -1198,9 +1227,15 @@ pc_status pc_stack_distance_req(const uint32_t *prev, const uint32_t *dist, cons
     pc_status st = pc::fill_u32(reinterpret_cast<uint32_t *>(hdr), 0u, 1, s);
     if (st != PC_OK || n == 0) return st;
     const int cus = pc::device_cus();
-    uint64_t grid = ((uint64_t)n_seqs + 3) / 4;
-    if (grid > (uint64_t)cus * 64) grid = (uint64_t)cus * 64;   // 64 per CU: 7.44 -> 7.15 ms on the full trace
-    PC_LAUNCH(pc::K_REQ_DIST, pc::req_dist_kernel, dim3((unsigned)grid), dim3(256), 0, s, prev, dist, blk_off, n_seqs,
+    // Workgroups of one wave where requests are long (they differ in length, and
+    // a workgroup's place is free only when all its waves are through), of four
+    // and no loads ahead where they are short (1.0e7 accesses in requests of 70:
+    // 52 us, 71 the other way).
+    const unsigned waves = n / n_seqs >= 256 ? 1 : 4;
+    uint64_t grid = ((uint64_t)n_seqs + waves - 1) / waves;
+    if (grid > (uint64_t)cus * 256 / waves) grid = (uint64_t)cus * 256 / waves;
+    const auto kernel = waves == 1 ? pc::req_dist_kernel<true> : pc::req_dist_kernel<false>;
+    PC_LAUNCH(pc::K_REQ_DIST, kernel, dim3((unsigned)grid), dim3(waves * pc::WAVE), 0, s, prev, dist, blk_off, n_seqs,
               n, dist_req, hdr);
     return PC_OK;
 }

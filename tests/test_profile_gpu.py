@@ -145,3 +145,21 @@ def test_profiler_pipeline_matches_the_stages():
     o_sp = oracle.session_profile(tr.blk_off(16), tr.session, tr.ts_us.astype(np.uint64), EDGES, 20000, 64)
     assert pc.hists_to_host(p.reuse) == o_rp
     assert pc.hists_to_host(p.sessions) == o_sp
+
+
+@pytest.mark.parametrize("edges", ["classes", "one octave", "one edge", "widest"])
+def test_gaps_around_the_edges(edges):
+    # gaps on both sides of value-class starts (eight to an octave) and of the
+    # edges, up to the widest 64-bit ones; requests of every length about a
+    # wave's step of 512 accesses
+    rng = np.random.default_rng(len(edges))
+    starts = [0, 1, 7, 8, 9] + [(8 + k) << e for e in range(1, 50) for k in (0, 7)]
+    E = {"classes": starts, "one octave": sorted(rng.integers(1 << 20, 1 << 21, 128).tolist()), "one edge": [4096],
+         "widest": [1, 2 ** 40, 2 ** 62, 2 ** 63, 2 ** 64 - 1]}[edges]
+    lens = [0, 1, 63, 64, 65, 511, 512, 513, 1025, 0] * 3
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    keys = rng.integers(0, 300, int(off[-1])).astype(np.uint64)
+    near = np.array(starts + [int(e) for e in E if e < 2 ** 52])
+    steps = near[rng.integers(0, near.size, len(lens))] + rng.integers(-1, 2, len(lens))
+    ts = np.cumsum(np.maximum(steps, 0)).astype(np.uint64)
+    check_profiles(keys, off, rng.integers(0, 7, len(lens)).astype(np.uint32), ts, edges=E, label=edges)

@@ -223,6 +223,19 @@ def test_scrambled_reuse_takes_the_direct_count():
     check_request_path(keys, bo, label="scrambled", exact_walk=False)
 
 
+@pytest.mark.parametrize("scrambled", [False, True])
+def test_long_requests_around_the_steps(scrambled):
+    # requests of whole steps of 512 accesses, and one less or more, where the
+    # next step's loads run ahead; scrambled ones take the direct count
+    rng = np.random.default_rng(3)
+    lens = [511, 512, 513, 1023, 1024, 1025, 1536, 1537, 700, 0, 1, 2048, 512, 1024, 512]
+    reqs = [np.arange(m, dtype=np.uint64) + np.uint64(10000 * (i % 3)) for i, m in enumerate(lens)]
+    if scrambled:
+        reqs = [rng.permutation(r) for r in reqs]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    check_request_path(np.concatenate(reqs), off, label="long %s" % scrambled)
+
+
 @pytest.mark.parametrize("n", [0, 1, 2, 4095, 4096, 4097, 8193])
 def test_ragged_sizes(n):
     keys = pcgen.random_keys(max(n, 1), max(n // 4, 1), n)[:n]
