@@ -277,24 +277,29 @@ __global__ __launch_bounds__(SCAN_THREADS) void chain_scan_kernel(const uint32_t
 // are open), from the stair kernel's lane masks.  Most slots have no open
 // lane (a request that continues an earlier one links all its depths but
 // the last few), so a wave first reads 64 slots' masks, offsets and records,
-// one per lane, and then takes only the slots with open lanes, two at a
-// time, one lane per depth.
+// one per lane, and then takes only the slots with open lanes, CC_SLOTS at a
+// time, one lane per depth.  Where there are too few slots to go round, a
+// wave takes every parts-th of its 64 (n_slots 1400: 20 -> 6 us; 4.5e4: 21 ->
+// 10).  Bound: a slot's scattered reads, hence several slots' at once (4.5e5
+// slots 45 us, two at a time 55).
+constexpr int CC_SLOTS = 8;
 __global__ __launch_bounds__(CH_THREADS) void chain_compact_kernel(
     const uint64_t *__restrict__ keys, uint64_t n_slots, const uint4 *__restrict__ rec,
     const uint4 *__restrict__ open, const uint32_t *__restrict__ coff, int deepest,
     uint64_t *__restrict__ ckeys, uint32_t *__restrict__ cpos, uint8_t *__restrict__ cflag,
-    const int32_t *__restrict__ hdr) {
+    const int32_t *__restrict__ hdr, uint32_t parts) {
     if (!hdr[HW_CHAIN]) return;   // (so the offsets stay below the unresolved capacity)
     const int lane = threadIdx.x & (WAVE - 1);
     const uint64_t waves = (uint64_t)gridDim.x * (CH_THREADS / WAVE);
     const uint64_t bit = 1ull << lane;
     const uint64_t above = ~((2ull << lane) - 1);   // lanes above this one (none for lane 63)
-    for (uint64_t j0 = ((uint64_t)blockIdx.x * (CH_THREADS / WAVE) + wave_id_uniform()) * WAVE; j0 < n_slots;
-         j0 += waves * WAVE) {
-        const uint64_t j = j0 + lane;
+    // a unit is the slots j0 + part, j0 + part + parts, .. of 64
+    const uint64_t units = (n_slots + WAVE - 1) / WAVE * parts;
+    for (uint64_t u = (uint64_t)blockIdx.x * (CH_THREADS / WAVE) + wave_id_uniform(); u < units; u += waves) {
+        const uint64_t j0 = u / parts * WAVE, j = j0 + lane;
         uint64_t mp = 0, mx = 0, pos = 0;
         uint32_t base = 0;
-        if (j < n_slots) {
+        if (j < n_slots && (uint32_t)lane % parts == (uint32_t)(u % parts)) {
             const uint4 o = open[j];
             mp = (uint64_t)o.x | ((uint64_t)o.y << 32);
             mx = (uint64_t)o.z | ((uint64_t)o.w << 32);
@@ -305,26 +310,28 @@ __global__ __launch_bounds__(CH_THREADS) void chain_compact_kernel(
         }
         uint64_t todo = ballot((mp | mx) != 0);
         while (todo) {
-            int src[2];
-            src[0] = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            src[1] = todo ? __builtin_ctzll(todo) : -1;
-            if (todo) todo &= todo - 1;
-            uint64_t m[2], p[2], kk[2];
-            uint32_t b[2], f[2];
+            int src[CC_SLOTS];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < CC_SLOTS; ++k) {
+                src[k] = todo ? __builtin_ctzll(todo) : -1;
+                if (todo) todo &= todo - 1;
+            }
+            uint64_t m[CC_SLOTS], p[CC_SLOTS], kk[CC_SLOTS];
+            uint32_t b[CC_SLOTS], f[CC_SLOTS];
+#pragma unroll
+            for (int k = 0; k < CC_SLOTS; ++k) {
                 const int L = src[k] < 0 ? src[0] : src[k];
-                const uint64_t a = shfl64(mp, L), x = shfl64(mx, L);
+                const uint64_t a = readlane64(mp, L), x = readlane64(mx, L);
                 m[k] = src[k] < 0 ? 0ull : (a | x);
                 f[k] = (a & bit ? 1u : 0u) | (x & bit ? 2u : 0u);
-                const uint64_t ps = shfl64(pos, L);
+                const uint64_t ps = readlane64(pos, L);
                 p[k] = deepest ? ps - (uint64_t)lane : ps + (uint64_t)lane;
-                b[k] = (uint32_t)__shfl((int)base, L, WAVE);
-                kk[k] = (m[k] & bit) ? keys[p[k]] : 0ull;
+                b[k] = (uint32_t)__builtin_amdgcn_readlane((int)base, L);
+                // (lanes without an access read the slot's first: no branch about the load)
+                kk[k] = keys[(m[k] & bit) ? p[k] : ps];
             }
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < CC_SLOTS; ++k) {
                 if (m[k] & bit) {
                     // time order: lanes ascending, or descending in the deepest-first layout
                     const uint32_t rank = deepest ? (uint32_t)__popcll(m[k] & above) : mbcnt(m[k]);
@@ -540,9 +547,12 @@ pc_status pc_prev_next_chained(const uint64_t *keys, uint64_t n, const uint64_t 
     PC_LAUNCH(K_CHAIN_SCAN, chain_scan_kernel, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, s,
               (const uint32_t *)w.cnt, ns, (const uint32_t *)w.tsum, w.coff, w.hdr, (const int32_t *)w.anchors.hdr,
               (uint32_t)m_cap);
-    PC_LAUNCH(K_CHAIN_COMPACT, chain_compact_kernel, dim3(wave_grid((ns + WAVE - 1) / WAVE, cus)),
+    const uint64_t chunks = (ns + WAVE - 1) / WAVE;
+    uint32_t parts = 1;   // up to 32 units per CU
+    while (parts < 16 && chunks * parts * 2 <= (uint64_t)cus * 32) parts *= 2;
+    PC_LAUNCH(K_CHAIN_COMPACT, chain_compact_kernel, dim3(wave_grid(chunks * parts, cus)),
               dim3(CH_THREADS), 0, s, keys, ns, (const uint4 *)w.rec, (const uint4 *)w.open, w.coff, deepest,
-              o.ckeys, o.cpos, o.cflag, (const int32_t *)w.hdr);
+              o.ckeys, o.cpos, o.cflag, (const int32_t *)w.hdr, parts);
     const uint32_t *m_dev = reinterpret_cast<const uint32_t *>(w.hdr + HW_UNRESOLVED);
     if ((st = prev_next_core(o.ckeys, m_cap, m_dev, o.cprev, o.cnext, nullptr, w.rest, o.bufs, s, chain,
                              SortReport{w.hdr, HW_HIGH_UNRESOLVED})) != PC_OK)
