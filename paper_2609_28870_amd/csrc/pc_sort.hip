@@ -341,27 +341,32 @@ constexpr int PERM_LOCAL_BITS = 14;
 constexpr uint64_t PERM_CHUNK_MAX = 1ull << 20;   // elements per workgroup, later passes
 constexpr uint64_t LINK_CHUNK_MAX = 1ull << 16;   // elements per workgroup, link
 
-// Work per workgroup: later passes take chunks of up to 2^20 elements (they
-// reserve per tile, so the chunk only spreads the work).  The link reserves
-// per chunk and its chunks are smaller: the runs that its workgroups in
-// flight append to then lie closer together, and the link, which waits on
-// more loads per element than the plain partition, gains from that.  About
-// two chunks per CU; the same on the host (grids) and the device (a count
-// the GPU wrote).
-__host__ __device__ inline uint64_t chunk_elems(uint64_t n, int cus, uint64_t cap, uint64_t tile) {
-    uint64_t c = (n + (uint64_t)cus * 2 - 1) / ((uint64_t)cus * 2);
+// Work per workgroup: later passes take chunks of up to 2^20 elements, about
+// two per CU (they reserve per tile, so the chunk only spreads the work).  The
+// link reserves per chunk and its chunks are smaller: the runs that its
+// workgroups in flight append to then lie closer together, and the link, which
+// waits on more loads per element than the plain partition, gains from eight
+// workgroups per CU (3.4e7 elements 337 us, with two 409).  The same on the
+// host (grids) and the device (a count the GPU wrote).
+constexpr int LINK_CHUNKS_PER_CU = 8, PERM_CHUNKS_PER_CU = 2;
+__host__ __device__ inline uint64_t chunk_elems(uint64_t n, uint64_t chunks, uint64_t cap, uint64_t tile) {
+    uint64_t c = (n + chunks - 1) / chunks;
     c = (c + tile - 1) / tile * tile;
     if (c > cap) c = cap;
     return c < tile ? tile : c;
 }
+__host__ __device__ inline uint64_t link_chunk(uint64_t n, int cus) {
+    return chunk_elems(n, (uint64_t)cus * LINK_CHUNKS_PER_CU, LINK_CHUNK_MAX, LINK_TILE);
+}
+__host__ __device__ inline uint64_t perm_chunk(uint64_t n, int cus) {
+    return chunk_elems(n, (uint64_t)cus * PERM_CHUNKS_PER_CU, PERM_CHUNK_MAX, PERM_TILE);
+}
 // the most chunks any count up to n splits into (the grid of a pass)
-static uint64_t max_chunks(uint64_t n, int cus, uint64_t cap, uint64_t tile) {
-    const uint64_t by_cap = (n + cap - 1) / cap;
-    const uint64_t by_cus = (uint64_t)cus * 2 + 1;
-    const uint64_t at_n = (n + chunk_elems(n, cus, cap, tile) - 1) / chunk_elems(n, cus, cap, tile);
-    uint64_t g = by_cap > by_cus ? by_cap : by_cus;
+static uint64_t max_chunks(uint64_t n, uint64_t chunk, uint64_t chunks, uint64_t cap) {
+    const uint64_t by_cap = (n + cap - 1) / cap, at_n = (n + chunk - 1) / chunk;
+    uint64_t g = by_cap > chunks + 1 ? by_cap : chunks + 1;
     if (at_n > g) g = at_n;
-    return g ? g : 1;
+    return g;
 }
 
 // After the four passes over the low 32 key bits, equal keys are contiguous
@@ -757,7 +762,7 @@ __global__ __launch_bounds__(LINK_THREADS, 4) void link_partition_kernel(
     int32_t *__restrict__ flag, const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
     if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
-    const uint64_t per_wg = chunk_elems(n, cus, LINK_CHUNK_MAX, LINK_TILE);
+    const uint64_t per_wg = link_chunk(n, cus);
     __shared__ PermLds<LINK_TILE, LINK_THREADS, LINK_RADIX> L;
     perm_partition_body<true, LINK_THREADS, LINK_ITEMS, LINK_RADIX, false>(L, sk, in_t, nullptr, n, s, blockIdx.x,
                                                                            per_wg, cursor, out_t, out_pn, false, flag);
@@ -769,7 +774,7 @@ __global__ __launch_bounds__(PART_THREADS, 4) void perm_partition_kernel(
     const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
     if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
-    const uint64_t per_wg = chunk_elems(n, cus, PERM_CHUNK_MAX, PERM_TILE);
+    const uint64_t per_wg = perm_chunk(n, cus);
     __shared__ PermLds<PERM_TILE, PART_THREADS, PERM_RADIX> L;
     perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(L, nullptr, in_t, in_pn, n, s, blockIdx.x,
                                                                            per_wg, cursor, out_t, out_pn, true, nullptr);
@@ -839,19 +844,21 @@ static PermPlan plan_perm(uint64_t n) {
     PermPlan p{};
     int nbits = 0;
     while (nbits < 64 && (1ull << nbits) < n) ++nbits;
-    int hi = nbits;   // bits above PERM_LOCAL_BITS still to split
     int cur = nbits;
     int shifts[4], k = 0;
-    // 8 bits in the link (its tiles are small), up to 9 in later passes:
-    // longer runs per tile and bucket than 10
+    // Up to 8 bits in the link (its tiles are small), up to 9 in later passes:
+    // longer runs per tile and bucket than 10.  With one later pass the link
+    // takes half of the bits, for the same reason (3.4e7 elements, 12 bits: link
+    // and later pass 278 + 214 us, as 8 and 4 bits 337 + 206).
+    const int total = nbits - PERM_LOCAL_BITS;
     int width = 8;
+    if (total > 8 && total <= 17 && (total + 1) / 2 < 8) width = (total + 1) / 2;
     while (cur > PERM_LOCAL_BITS && k < 4) {
         int next_s = cur - width > PERM_LOCAL_BITS ? cur - width : PERM_LOCAL_BITS;
         shifts[k++] = next_s;
         cur = next_s;
         width = 9;
     }
-    (void)hi;
     if (k == 0) shifts[k++] = PERM_LOCAL_BITS;
     p.passes = k;
     p.max_buckets = 1;
@@ -1034,7 +1041,7 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_persistent_kernel(SortJo
         finish_phase(phase_done(ctl, phase), mine, tiles, j.k.hdr);
     };
     auto link = [&](int phase, uint32_t *cursor, bool full) {
-        const uint64_t per = chunk_elems(n, j.cus, LINK_CHUNK_MAX, LINK_TILE);
+        const uint64_t per = link_chunk(n, j.cus);
         const uint32_t chunks = (uint32_t)((n + per - 1) / per);
         uint32_t mine = 0;
         for (uint32_t c; (c = next_chunk(ctl, phase, &s_word)) < chunks; ++mine)
@@ -1061,7 +1068,7 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_persistent_kernel(SortJo
     if (j.whole) {
 #pragma unroll 1
         for (int i = 1; i < j.plan.passes; ++i) {
-            const uint64_t per = chunk_elems(n, j.cus, PERM_CHUNK_MAX, PERM_TILE);
+            const uint64_t per = perm_chunk(n, j.cus);
             const uint32_t chunks = (uint32_t)((n + per - 1) / per);
             // (selected, not indexed: the job stays out of scratch memory)
             const bool odd = i & 1;
@@ -1128,8 +1135,10 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     // (k2, v2) after four passes and again after eight; the triples ping-pong
     // between the first sort buffers ((prev, next) pairs in k1, t in v1) and,
     // once the sorted keys have been consumed, the second ones (k2, v2).
-    const unsigned ptiles = (unsigned)max_chunks(n, cus, PERM_CHUNK_MAX, PERM_TILE);
-    const unsigned ltiles = (unsigned)max_chunks(n, cus, LINK_CHUNK_MAX, LINK_TILE);
+    const unsigned ptiles =
+        (unsigned)max_chunks(n, perm_chunk(n, cus), (uint64_t)cus * PERM_CHUNKS_PER_CU, PERM_CHUNK_MAX);
+    const unsigned ltiles =
+        (unsigned)max_chunks(n, link_chunk(n, cus), (uint64_t)cus * LINK_CHUNKS_PER_CU, LINK_CHUNK_MAX);
     PC_LAUNCH(K_LINK, link_partition_kernel, dim3(ltiles), dim3(LINK_THREADS), 0, s, kin, vin, n, pp.s[0], cus,
               k.cursor[0], b.v1, b.k1, k.hdr + 1, n_dev, gate);
     // the passes over the high bits and a second link, if the first one met a
