@@ -40,7 +40,7 @@
 //     bitmap's largest values above the window (whole words, top down) and
 //     taking the window's largest value when nothing above it is left.
 // Values inserted above theta are merged into the buffer in sorted order
-// after the batch; a buffer above 256 values spills its lowest into the
+// after the batch; a buffer above 160 values spills its lowest into the
 // bitmap.  Global bitmap words are touched only by their capacity's wave,
 // through relaxed device-scope atomics (they live in L2).  A word entering
 // the ring may still hold bits inserted before: every 16 batches, after a
@@ -50,16 +50,16 @@
 // masks come four batches at a time through LDS).  A refill syncs at once.
 //
 // Bound: the instructions of one wave, batch after batch, at the capacities
-// that evict most: 4.0e6 agent accesses at 69 capacities 0.151 s, 2.4 us a
+// that evict most: 4.0e6 agent accesses at 69 capacities 0.139 s, 2.2 us a
 // batch of 64 (0.333 s with the joint ranking of all 128 candidates worked out
-// per capacity and a walk per rank and access: the decision then took 7,600
-// cycles of 12,000, now 3,000 of 6,000).
+// per capacity and a walk per rank and access).
 #include "pc_internal.h"
 
 namespace pc {
 
-constexpr uint32_t BEL_TARGET = 128;          // buffer size a refill aims for and a spill leaves
-constexpr uint32_t BEL_SPILL_AT = 256;        // buffer size above which the lowest values are spilled
+constexpr uint32_t BEL_TARGET = 96;           // buffer size a refill aims for and a spill leaves
+constexpr uint32_t BEL_SPILL_AT = 160;        // buffer size above which the lowest values are spilled (a merge moves the
+                                              // whole buffer: 147.5 ms, with 128 and 256 152.2, 160 and 320 159.3)
 // LDS buffer entries: the largest fill (spill size + one batch), and what a
 // search reads past a short buffer
 constexpr uint32_t BEL_BUF = BEL_SPILL_AT + 3 * WAVE;
@@ -545,24 +545,28 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             // x itself is taken iff counting it too makes R larger: iff the walk
             // gets, after x's own access, below both -A(x) and every sum before.
             // Each lane walks for its own value, six accesses per table entry.
-            int in = 0, pre = -(int)in_top, post = WALK_NONE;
+            // (Below every sum before its own access, and -A(x): then the lowest of
+            // all is also the lowest after it.)
+            int in = 0, all = 0, pre = -(int)in_top;
             int8_t low[WALK_GROUPS];
 #pragma unroll
             for (int g = 0; g < WALK_GROUPS; ++g)
                 low[g] = s_walk[((uint32_t)(real >> (WALK * g)) & 63) * 64 + ((uint32_t)(hi_mask >> (WALK * g)) & 63)];
-            const uint32_t vg = (uint32_t)(real >> own_at) & 63, ig = (uint32_t)(hi_mask >> own_at) & 63;
+            const uint64_t before = (1ull << own_at) - 1;   // the groups before the lane's own
             const uint32_t upto = (2u << (lane - own_at)) - 1;
-            const int low_pre = s_walk[(vg & upto) * 64 + ig], low_post = s_walk[(vg & ~upto) * 64 + ig];
+            const int own_pre = s_walk[((uint32_t)(real >> own_at) & 63 & upto) * 64 +
+                                       ((uint32_t)(hi_mask >> own_at) & 63)] +
+                                (int)__popcll(hi_mask & before) - (int)__popcll(real & before);
 #pragma unroll
             for (int g = 0; g < WALK_GROUPS; ++g) {
-                const int at = in - (int)__popcll(real & ((1ull << (WALK * g)) - 1));
-                const int x = at + (g == own ? low_pre : (int)low[g]);
-                if (g <= own) pre = x < pre ? x : pre;
-                const int y = at + (g == own ? low_post - (int)__popc(vg & upto) : (int)low[g]);
-                if (g >= own) post = y < post ? y : post;
+                const int x = in - (int)__popcll(real & ((1ull << (WALK * g)) - 1)) + (int)low[g];
+                all = x < all ? x : all;
+                const int y = g < own ? x : 0;
+                pre = y < pre ? y : pre;
                 in += (int)__popc((uint32_t)(hi_mask >> (WALK * g)) & 63);
             }
-            const uint64_t gone_if = ballot(pend && post < pre);
+            pre = own_pre < pre ? own_pre : pre;
+            const uint64_t gone_if = ballot(pend && all < pre);
             // all real evictions find a candidate at or above theta
             const uint64_t lt = (1ull << lane) - 1;
             const int sum = (int)__popcll(high & lt) - (int)__popcll(real & le);
