@@ -58,8 +58,8 @@
 namespace pc {
 
 constexpr uint32_t BEL_TARGET = 96;           // buffer size a refill aims for and a spill leaves
-constexpr uint32_t BEL_SPILL_AT = 160;        // buffer size above which the lowest values are spilled (a merge moves the
-                                              // whole buffer: 147.5 ms, with 128 and 256 152.2, 160 and 320 159.3)
+constexpr uint32_t BEL_SPILL_AT = 160;        // buffer size above which the lowest values are spilled
+// (a merge moves the whole buffer: 147.5 ms, with 128 and 256 152.2, with 160 and 320 159.3)
 // LDS buffer entries: the largest fill (spill size + one batch), and what a
 // search reads past a short buffer
 constexpr uint32_t BEL_BUF = BEL_SPILL_AT + 3 * WAVE;

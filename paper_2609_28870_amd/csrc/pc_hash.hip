@@ -116,9 +116,9 @@ __device__ __forceinline__ bool request_in_bounds(uint64_t st, uint32_t len, uin
 
 constexpr int DIGEST_WAVES = 4;
 constexpr int HASH_THREADS = (1 + DIGEST_WAVES) * WAVE;
-constexpr int HASH_SWEEPS = 8;                                       // most sweeps (64 blocks) per digest wave and round
-constexpr int HASH_ENTRIES = HASH_SWEEPS * DIGEST_WAVES * WAVE;      // most blocks per round: rows x SPAN
-constexpr int HASH_RING = 4;                                         // token chunks in flight per digest wave
+constexpr int HASH_SWEEPS = 8;                                      // most sweeps (64 blocks) per digest wave and round
+constexpr int HASH_ENTRIES = HASH_SWEEPS * DIGEST_WAVES * WAVE;     // most blocks per round: rows x SPAN
+constexpr int HASH_RING = 4;                                        // token chunks in flight per digest wave
 // At most two workgroups per CU: they keep the vector units and the memory
 // busy; with three or four the waves held each other up (on 2.2e8 accesses
 // 2.10 ms, with three 2.35; on 2.8e7, where the longest chain counts, 0.66 and

@@ -19,10 +19,10 @@
 //     workgroup scans them into digit bases;
 //   * each of the four sort passes is a single "onesweep" kernel: a
 //     workgroup takes the next tile from an atomic counter (so every tile it
-//     waits on is already running), ranks its 8192 elements by digit with
-//     wave ballots (stable: lanes in order, waves in order), publishes its
-//     per-digit counts and reads its predecessors' with a decoupled
-//     look-back, then writes the tile out through LDS so each digit run is a
+//     waits on is already running), ranks its elements (8192, fewer in small
+//     calls) by digit with wave ballots (stable: lanes in order, waves in
+//     order), publishes its per-digit counts and reads its predecessors' with
+//     a decoupled look-back, then writes the tile out through LDS so each digit run is a
 //     contiguous burst;
 //   * the link + partition kernels read sorted neighbours into (t, prev,
 //     next) triples and move them back to time order (see below).
@@ -937,7 +937,16 @@ size_t sort_bufs_bytes(uint64_t n) {
 // workgroup goes on to the next phase once all are finished.  Only running
 // workgroups hold chunks, so the wait ends whatever part of the grid is
 // resident.
-enum SortPhase { PH_HIST, PH_PASS, PH_LINK = PH_PASS + 4, PH_HIST2, PH_PASS2, PH_LINK2 = PH_PASS2 + 4, PH_PERM, PH_COUNT = PH_PERM + 3 };
+enum SortPhase {
+    PH_HIST,
+    PH_PASS,
+    PH_LINK = PH_PASS + 4,
+    PH_HIST2,
+    PH_PASS2,
+    PH_LINK2 = PH_PASS2 + 4,
+    PH_PERM,
+    PH_COUNT = PH_PERM + 3
+};
 static_assert(CTL_PHASE + 2 * PH_COUNT <= CTL_WORDS, "the control words hold every phase");
 
 struct SortJob {

@@ -59,8 +59,13 @@ IDS = {"pc::hash_kernel": "hash_blocks", "pc::hash_classes_kernel": "hash_order"
        "pc::belady_kernel": "belady"}
 
 
+# instances that are tile sizes of one kernel, reported together
+ONE_KERNEL = ("pc::sort_pass_kernel",)
+
+
 def kernel_name(s):
-    return s.split("(")[0].replace("void ", "").strip()
+    name = s.split("(")[0].replace("void ", "").strip()
+    return name.split("<")[0] if name.startswith(ONE_KERNEL) else name
 
 
 def source_sha256():

@@ -107,3 +107,63 @@ def test_hand_worked_batch():
     # the buffer's candidate
     assert greedy(3, 0b111, 0, 1, [1], {0: 0}, 2) == (True, {0, 1}, 0)
     assert closed_form(3, 0b111, 0, 1, [1], {0: 0}, 2) == (True, {0, 1}, 0)
+
+
+def per_insert(nb, ev, dm, d0, n_buffer, pend):
+    """The kernel's form: each insert asks for itself, with the walk taken six
+    accesses at a time from the lowest sum inside each group."""
+    popc = lambda x: bin(x).count("1")
+    real = best = 0
+    for j in range(nb):
+        gap = popc(ev & ((2 << j) - 1)) - d0 - popc(dm & ((1 << j) - 1))
+        if gap > best:
+            real |= 1 << j
+            best = gap
+
+    def low(v, i):
+        run, least = 0, 127
+        for j in range(6):
+            if (v >> j) & 1:
+                run -= 1
+                least = min(least, run)
+            run += (i >> j) & 1
+        return least
+
+    gone = set()
+    for j, value in pend.items():
+        higher = sum(1 << k for k, v in pend.items() if v > value)
+        above = sum(1 for v in n_buffer if v > value)
+        own = j // 6
+        lowest, before = 0, -above
+        for g in range(11):
+            at = popc(higher & ((1 << 6 * g) - 1)) - popc(real & ((1 << 6 * g) - 1))
+            v, i = (real >> 6 * g) & 63, (higher >> 6 * g) & 63
+            lowest = min(lowest, at + low(v, i))
+            if g < own:
+                before = min(before, at + low(v, i))
+            elif g == own:
+                before = min(before, at + low(v & ((2 << (j - 6 * g)) - 1), i))
+        if lowest < before:
+            gone.add(j)
+    return gone, popc(real) - len(gone)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_per_insert_walk_takes_what_the_greedy_takes(seed):
+    rng = random.Random(100 + seed)
+    for _ in range(150):
+        nb = rng.choice([1, 2, 5, 6, 7, 12, 13, 59, 60, 61, 63, 64])
+        values = rng.sample(range(1000), 128)
+        buf = values[:rng.choice([0, 1, 7, 40, 64])]
+        pend = {j: v for j, v in zip(range(nb), values[64:]) if rng.random() < rng.choice([0.1, 0.6, 1.0])}
+        dm = sum(1 << j for j in range(nb) if j not in pend and rng.random() < 0.5)
+        ev = sum(1 << j for j in range(nb) if rng.random() < rng.choice([0.2, 0.9]))
+        d0 = rng.randrange(4)
+        order = sorted(buf + list(pend.values()), reverse=True)
+        rank = {v: k for k, v in enumerate(order)}
+        ok, gone, _ = greedy(nb, ev, dm, d0, [rank[v] for v in buf], {j: rank[v] for j, v in pend.items()}, len(order))
+        if not ok:
+            continue
+        mine, popped = per_insert(nb, ev, dm, d0, buf, pend)
+        assert {rank[pend[j]] for j in mine} == {r for r in gone if order[r] not in buf}
+        assert popped == sum(1 for r in gone if order[r] in buf)
