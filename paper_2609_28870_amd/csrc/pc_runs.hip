@@ -370,7 +370,9 @@ __global__ __launch_bounds__(256) void runs_merge_kernel(const uint32_t *__restr
 // exactly one run [h, e], every other position is cold.  The runs that can
 // touch a tile are the one in progress at its start and those starting in
 // it; a thread finds the run at its first position by binary search and
-// walks on.  A run's distance is z + acc - p - 1.
+// walks on.  A run's distance is z + acc - p - 1.  Bound: the stores (8.0e8
+// accesses 0.586 ms, 5.5 TB/s; with the search and the run's words read from
+// memory as needed, a chain of five loads a tile, 0.765).
 __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, const uint2 *__restrict__ off,
                                                                 uint64_t tiles, const uint32_t *__restrict__ rh,
                                                                 const uint32_t *__restrict__ re,
@@ -381,53 +383,104 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_fill_kernel(uint64_t n, cons
                                                                 const int32_t *__restrict__ hdr) {
     if (!hdr[RW_RUNS_OK]) return;
     const uint64_t r = runs_of(hdr);
-    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        // thread i holds positions tile0 + 1024 g + 4 i .. + 3 for g = 0..3
-        // (increasing), so each 16-byte store covers 1 KB across the wave
-        const uint64_t tile0 = tile * RUN_TILE;
-        const uint64_t t0 = tile0 + (uint64_t)threadIdx.x * 4;
-        const uint64_t first = off[tile].x;
-        const int64_t lo = first ? (int64_t)first - 1 : 0;
-        const int64_t hi = tile + 1 < tiles ? (int64_t)off[tile + 1].x : (int64_t)r;
-        // last run in [lo, hi) with head <= t0, or lo - 1
-        int64_t a = lo, b = hi;
-        while (a < b) {
-            const int64_t m = (a + b) >> 1;
-            if (rh[m] <= t0) a = m + 1;
-            else b = m;
+    const int tid = threadIdx.x;
+    // The runs that a tile's positions may lie in are [lo, hi): the ones that
+    // start in it and the last one before.  Mostly they are few; then their
+    // heads, ends and distances pass through LDS, one per thread, loaded while
+    // the tile before is written (and the tile's bounds while the one before
+    // that is).
+    __shared__ uint32_t s_head[2][RUN_THREADS], s_end[2][RUN_THREADS], s_dist[2][RUN_THREADS];
+    struct Bounds {
+        uint32_t lo, hi;
+    };
+    auto bounds = [&](uint64_t tile) {
+        Bounds b{0u, 0u};
+        if (tile < tiles) {
+            const uint32_t first = off[tile].x;
+            b.lo = first ? first - 1 : 0u;
+            b.hi = tile + 1 < tiles ? off[tile + 1].x : (uint32_t)r;
         }
-        int64_t s = a - 1;
+        return b;
+    };
+    uint32_t h = 0, e = 0, z = 0, c = 0, p = 0;
+    auto fetch = [&](const Bounds &b) {
+        if ((uint32_t)tid < b.hi - b.lo && b.hi - b.lo <= RUN_THREADS) {
+            const uint32_t k = b.lo + (uint32_t)tid;
+            h = rh[k];
+            e = re[k];
+            z = rz[k];
+            c = acc[k];
+            p = rp[k];
+        }
+    };
+    Bounds now = bounds(blockIdx.x), next = bounds((uint64_t)blockIdx.x + gridDim.x);
+    fetch(now);
+    int buf = 0;
+    const bool vec = (reinterpret_cast<uintptr_t>(dist) & 15) == 0;
+    // thread i holds positions tile0 + 1024 g + 4 i .. + 3 for g = 0..3
+    // (increasing), so each 16-byte store covers 1 KB across the wave
+    auto write = [&](uint64_t tile, uint32_t runs, auto head_of, auto end_of, auto dist_of) {
+        const uint64_t t0 = tile * RUN_TILE + (uint64_t)tid * 4;
+        // the runs with head <= t0
+        uint32_t lo = 0, hi = runs;
+        while (lo < hi) {
+            const uint32_t m = (lo + hi) >> 1;
+            if (head_of(m) <= t0) lo = m + 1;
+            else hi = m;
+        }
+        uint32_t s = lo;   // the current run is s - 1, the next one s
         // the current run's end and distance and the next run's head, in
-        // registers: loads only where a run starts
-        bool in_run = s >= lo;
-        uint64_t end = in_run ? re[s] : 0;
-        uint32_t dv = in_run ? rz[s] + acc[s] - rp[s] - 1 : NONE;
-        uint64_t next_head = s + 1 < hi ? rh[s + 1] : ~0ull;
-        const bool vec = (reinterpret_cast<uintptr_t>(dist) & 15) == 0;
-    #pragma unroll
+        // registers: read only where a run starts
+        bool in_run = s > 0;
+        uint64_t end = in_run ? end_of(s - 1) : 0;
+        uint32_t dv = in_run ? dist_of(s - 1) : NONE;
+        uint64_t next_head = s < runs ? head_of(s) : ~0ull;
+#pragma unroll
         for (int g = 0; g < RUN_ITEMS / 4; ++g) {
             const uint64_t tg = t0 + (uint64_t)g * (RUN_THREADS * 4);
             uint32_t d[4];
-    #pragma unroll
+#pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint64_t t = tg + k;
                 while (t >= next_head) {
-                    ++s;
                     in_run = true;
-                    end = re[s];
-                    dv = rz[s] + acc[s] - rp[s] - 1;
-                    next_head = s + 1 < hi ? rh[s + 1] : ~0ull;
+                    end = end_of(s);
+                    dv = dist_of(s);
+                    ++s;
+                    next_head = s < runs ? head_of(s) : ~0ull;
                 }
                 d[k] = (in_run && end >= t) ? dv : NONE;
             }
             if (vec && tg + 4 <= n) {
                 *reinterpret_cast<uint4 *>(dist + tg) = make_uint4(d[0], d[1], d[2], d[3]);
             } else {
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 4; ++k)
                     if (tg + k < n) dist[tg + k] = d[k];
             }
         }
+    };
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x, buf ^= 1) {
+        const uint32_t runs = now.hi - now.lo;
+        if (runs <= RUN_THREADS && (uint32_t)tid < runs) {
+            s_head[buf][tid] = h;
+            s_end[buf][tid] = e;
+            s_dist[buf][tid] = z + c - p - 1;
+        }
+        __syncthreads();
+        fetch(next);
+        const Bounds after = bounds(tile + 2 * (uint64_t)gridDim.x);
+        if (runs <= RUN_THREADS)
+            write(
+                tile, runs, [&](uint32_t k) -> uint64_t { return s_head[buf][k]; },
+                [&](uint32_t k) -> uint64_t { return s_end[buf][k]; }, [&](uint32_t k) { return s_dist[buf][k]; });
+        else
+            write(
+                tile, runs, [&](uint32_t k) -> uint64_t { return rh[now.lo + k]; },
+                [&](uint32_t k) -> uint64_t { return re[now.lo + k]; },
+                [&](uint32_t k) { return rz[now.lo + k] + acc[now.lo + k] - rp[now.lo + k] - 1; });
+        now = next;
+        next = after;
     }
 }
 
@@ -520,7 +573,7 @@ pc_status pc_stack_distance_runs(const uint32_t *prev, const uint32_t *next, uin
                   w.idx[cur ^ 1], w.acc, ok);
         cur ^= 1;
     }
-    PC_LAUNCH(K_RUNS_FILL, runs_fill_kernel, dim3(capped(tiles, 16)), dim3(RUN_THREADS), 0, s, n,
+    PC_LAUNCH(K_RUNS_FILL, runs_fill_kernel, dim3(capped(tiles, 32)), dim3(RUN_THREADS), 0, s, n,
               (const uint2 *)w.off, tiles, (const uint32_t *)w.rh, (const uint32_t *)w.re, (const uint32_t *)w.rp,
               (const uint32_t *)w.rz, (const uint32_t *)w.acc, dist, ok);
     return PC_OK;

@@ -134,3 +134,16 @@ def test_degenerate_and_ragged(case):
         keys = copied_segments(rng, 4096 * 3 + 17, 300, 0.3)
     info = exact(keys, offset=1 if case == "ragged_unaligned" else 0)
     say(case, info)
+
+
+@pytest.mark.parametrize("burst", [253, 254, 255, 4096])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_many_runs_in_one_tile(burst, offset):
+    """`burst` runs of one access at the start of one 4096-position tile, which
+    also holds the end of the run before it and the start of the one after
+    it: 255 to 257 runs, and a tile that only the runs' own arrays can hold."""
+    a = np.arange(131072, dtype=np.uint64)
+    keys = np.concatenate([a, a[:4096], a[9000 - burst:9000][::-1], a[9000:16000], a[:20001]])
+    info = exact(keys, offset)
+    say(burst, info)
+    assert not info["generic"] and info["runs"] >= burst
