@@ -335,20 +335,18 @@ constexpr int LINK_TILE = LINK_THREADS * LINK_ITEMS;
 constexpr int PART_THREADS = 512;
 constexpr int PART_ITEMS = 16;                         // plain partition: 8192-element tiles
 constexpr int PERM_TILE = PART_THREADS * PART_ITEMS;   // the larger tile
-constexpr int PERM_RADIX = 1024;   // digits of a later pass (a chunk spans two earlier buckets)
+constexpr int PERM_RADIX = 1024;   // digits of a later pass (a tile spans two earlier buckets)
 constexpr int LINK_RADIX = 256;    // digits of the first pass: at most 256 buckets
 constexpr int PERM_LOCAL_BITS = 14;
-constexpr uint64_t PERM_CHUNK_MAX = 1ull << 20;   // elements per workgroup, later passes
 constexpr uint64_t LINK_CHUNK_MAX = 1ull << 16;   // elements per workgroup, link
 
-// Work per workgroup: later passes take chunks of up to 2^20 elements, about
-// two per CU (they reserve per tile, so the chunk only spreads the work).  The
-// link reserves per chunk and its chunks are smaller: the runs that its
-// workgroups in flight append to then lie closer together, and the link, which
-// waits on more loads per element than the plain partition, gains from eight
-// workgroups per CU (3.4e7 elements 337 us, with two 409).  The same on the
-// host (grids) and the device (a count the GPU wrote).
-constexpr int LINK_CHUNKS_PER_CU = 8, PERM_CHUNKS_PER_CU = 2;
+// Work per workgroup: a later pass takes one tile (it reserves per tile), the
+// link, which reserves per chunk, chunks of up to 2^16 elements: with small
+// chunks the runs that its workgroups in flight append to lie close together,
+// and the link, which waits on more loads per element than the plain partition,
+// gains from eight workgroups per CU (3.4e7 elements 337 us, with two 409).  The
+// same on the host (grids) and the device (a count the GPU wrote).
+constexpr int LINK_CHUNKS_PER_CU = 8;
 __host__ __device__ inline uint64_t chunk_elems(uint64_t n, uint64_t chunks, uint64_t cap, uint64_t tile) {
     uint64_t c = (n + chunks - 1) / chunks;
     c = (c + tile - 1) / tile * tile;
@@ -358,8 +356,17 @@ __host__ __device__ inline uint64_t chunk_elems(uint64_t n, uint64_t chunks, uin
 __host__ __device__ inline uint64_t link_chunk(uint64_t n, int cus) {
     return chunk_elems(n, (uint64_t)cus * LINK_CHUNKS_PER_CU, LINK_CHUNK_MAX, LINK_TILE);
 }
-__host__ __device__ inline uint64_t perm_chunk(uint64_t n, int cus) {
-    return chunk_elems(n, (uint64_t)cus * PERM_CHUNKS_PER_CU, PERM_CHUNK_MAX, PERM_TILE);
+// Which tile of a later pass a workgroup takes: workgroups go to the eight XCDs
+// in turn, and each XCD gets one contiguous eighth of the tiles.  Tiles that
+// follow each other append to the same runs, and only within one XCD's L2 do
+// their ends meet in the same line before it is written.  A grid of
+// perm_grid(m) covers every count up to m; a tile past the last is none.
+constexpr uint64_t XCDS = 8;
+__host__ __device__ inline uint64_t perm_tiles(uint64_t n) { return (n + PERM_TILE - 1) / PERM_TILE; }
+static unsigned perm_grid(uint64_t n) { return (unsigned)((perm_tiles(n) + XCDS - 1) / XCDS * XCDS); }
+__device__ inline uint64_t perm_tile(uint64_t n, uint64_t block) {
+    const uint64_t share = (perm_tiles(n) + XCDS - 1) / XCDS;
+    return block / XCDS < share ? block % XCDS * share + block / XCDS : ~0ull;
 }
 // the most chunks any count up to n splits into (the grid of a pass)
 static uint64_t max_chunks(uint64_t n, uint64_t chunk, uint64_t chunks, uint64_t cap) {
@@ -768,16 +775,22 @@ __global__ __launch_bounds__(LINK_THREADS, 4) void link_partition_kernel(
                                                                            per_wg, cursor, out_t, out_pn, false, flag);
 }
 
+// Bound: the writes, whose runs are a few lines long.  One tile per workgroup,
+// an XCD's tiles contiguous: two launches over 9.4e7 elements in all 511 us
+// (4.4 TB/s of 24 bytes each), in the order of the workgroups 580, as two
+// chunks per CU 648.
 __global__ __launch_bounds__(PART_THREADS, 4) void perm_partition_kernel(
-    const uint32_t *__restrict__ in_t, const uint64_t *__restrict__ in_pn, uint64_t n, int s, int cus,
+    const uint32_t *__restrict__ in_t, const uint64_t *__restrict__ in_pn, uint64_t n, int s,
     uint32_t *__restrict__ cursor, uint32_t *__restrict__ out_t, uint64_t *__restrict__ out_pn,
     const uint32_t *__restrict__ n_dev, const int32_t *__restrict__ gate) {
     if (gated_off(gate)) return;
     n = dev_count(n, n_dev);
-    const uint64_t per_wg = perm_chunk(n, cus);
+    const uint64_t tile = perm_tile(n, blockIdx.x);
+    if (tile >= perm_tiles(n)) return;
     __shared__ PermLds<PERM_TILE, PART_THREADS, PERM_RADIX> L;
-    perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(L, nullptr, in_t, in_pn, n, s, blockIdx.x,
-                                                                           per_wg, cursor, out_t, out_pn, true, nullptr);
+    perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(L, nullptr, in_t, in_pn, n, s, tile,
+                                                                           PERM_TILE, cursor, out_t, out_pn, true,
+                                                                           nullptr);
 }
 
 // every 16384-range of t holds exactly its own triples: place the (prev,
@@ -1077,8 +1090,7 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_persistent_kernel(SortJo
     if (j.whole) {
 #pragma unroll 1
         for (int i = 1; i < j.plan.passes; ++i) {
-            const uint64_t per = perm_chunk(n, j.cus);
-            const uint32_t chunks = (uint32_t)((n + per - 1) / per);
+            const uint32_t chunks = (uint32_t)perm_tiles(n);
             // (selected, not indexed: the job stays out of scratch memory)
             const bool odd = i & 1;
             const int shift = i == 1 ? j.plan.s[1] : i == 2 ? j.plan.s[2] : j.plan.s[3];
@@ -1086,7 +1098,7 @@ __global__ __launch_bounds__(SORT_THREADS, 4) void sort_persistent_kernel(SortJo
             uint32_t mine = 0;
             for (uint32_t c; (c = next_chunk(ctl, PH_PERM + i - 1, &s_word)) < chunks; ++mine)
                 perm_partition_body<false, PART_THREADS, PART_ITEMS, PERM_RADIX, true>(
-                    L.perm, nullptr, odd ? j.b.v1 : j.b.v2, odd ? j.b.k1 : j.b.k2, n, shift, c, per, cursor,
+                    L.perm, nullptr, odd ? j.b.v1 : j.b.v2, odd ? j.b.k1 : j.b.k2, n, shift, c, PERM_TILE, cursor,
                     odd ? j.b.v2 : j.b.v1, odd ? j.b.k2 : j.b.k1, true, nullptr);
             finish_phase(phase_done(ctl, PH_PERM + i - 1), mine, chunks, j.k.hdr);
         }
@@ -1144,8 +1156,6 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     // (k2, v2) after four passes and again after eight; the triples ping-pong
     // between the first sort buffers ((prev, next) pairs in k1, t in v1) and,
     // once the sorted keys have been consumed, the second ones (k2, v2).
-    const unsigned ptiles =
-        (unsigned)max_chunks(n, perm_chunk(n, cus), (uint64_t)cus * PERM_CHUNKS_PER_CU, PERM_CHUNK_MAX);
     const unsigned ltiles =
         (unsigned)max_chunks(n, link_chunk(n, cus), (uint64_t)cus * LINK_CHUNKS_PER_CU, LINK_CHUNK_MAX);
     PC_LAUNCH(K_LINK, link_partition_kernel, dim3(ltiles), dim3(LINK_THREADS), 0, s, kin, vin, n, pp.s[0], cus,
@@ -1159,8 +1169,8 @@ pc_status prev_next_core(const uint64_t *keys, uint64_t n, const uint32_t *n_dev
     uint64_t *bpn[2] = {b.k1, b.k2};
     for (int i = 1; i < pp.passes; ++i) {
         const int from = (i - 1) & 1;
-        PC_LAUNCH(K_PERM, perm_partition_kernel, dim3(ptiles), dim3(PART_THREADS), 0, s, bt[from], bpn[from], n,
-                  pp.s[i], cus, k.cursor[i], bt[from ^ 1], bpn[from ^ 1], n_dev, gate);
+        PC_LAUNCH(K_PERM, perm_partition_kernel, dim3(perm_grid(n)), dim3(PART_THREADS), 0, s, bt[from], bpn[from], n,
+                  pp.s[i], k.cursor[i], bt[from ^ 1], bpn[from ^ 1], n_dev, gate);
     }
     return perm_local(j, prev, next, s, gate, report);
 }

@@ -81,6 +81,18 @@ def test_sort_tile_sizes(n):
     assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
 
 
+@pytest.mark.parametrize("n", [(1 << 22) + 1, (1 << 22) + 57_344, (1 << 22) + 65_535, (1 << 22) + 65_536,
+                               (1 << 22) + 65_537])
+def test_tiles_of_a_later_partition_pass(n):
+    """Above 2^22 keys the way back to time order has a later pass, whose
+    8192-element tiles are dealt in eighths: 513, 519, 520 and 521 tiles."""
+    keys = device_keys(n, n // 3)
+    prev, nxt, ws = pc.prev_next_use(keys)
+    p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
+    assert pc.workspace_status(ws) == 0
+    assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+
+
 def test_a_larger_call_never_needs_less_workspace():
     sizes = [pc.lib().pc_prev_next_use_ws(n) for k in (11, 18, 20, 21, 22) for n in range((1 << k) - 8200, (1 << k) + 8200, 511)
              if n > 0]
