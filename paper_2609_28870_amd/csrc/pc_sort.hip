@@ -862,7 +862,8 @@ static PermPlan plan_perm(uint64_t n) {
     // Up to 8 bits in the link (its tiles are small), up to 9 in later passes:
     // longer runs per tile and bucket than 10.  With one later pass the link
     // takes half of the bits, for the same reason (3.4e7 elements, 12 bits: link
-    // and later pass 278 + 214 us, as 8 and 4 bits 337 + 206).
+    // and later pass 278 + 214 us, as 8 and 4 bits 337 + 206, both with the
+    // later pass as two chunks per CU; it takes 188 now).
     const int total = nbits - PERM_LOCAL_BITS;
     int width = 8;
     if (total > 8 && total <= 17 && (total + 1) / 2 < 8) width = (total + 1) / 2;
