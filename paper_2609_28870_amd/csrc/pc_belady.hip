@@ -578,6 +578,13 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
                 size = c;   // evictions happened, so the cache is full
                 gone = gone_if;
                 popped = E - (uint32_t)__popcll(gone);
+                // With next[] one-to-one the buffer gives the rest of the
+                // evictions; copies of a value each count as taken, so that
+                // more may be gone than were evicted.
+                if (popped > S.bufn) {   // (below 0 too: the count wraps)
+                    if (lane == 0) atomicOr(err, DEV_ERR_BELADY);
+                    return;
+                }
             } else {
             // the general walk: the window in a register, a refill when the
             // buffer and the batch's inserts above theta run out, the window's

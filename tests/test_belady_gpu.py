@@ -132,3 +132,27 @@ def test_invalid_next_is_reported_and_stays_in_bounds():
     out, ws = pc.belady(pc.to_dev_u32(nxt), pc.to_dev_u64(np.array([1, 2000], np.uint64)))
     torch.cuda.synchronize()
     assert pc.workspace_status(ws) == 2
+
+
+@pytest.mark.parametrize("case", ["one value", "few values", "any later position"])
+def test_a_next_that_is_not_one_to_one_stays_in_bounds(case):
+    # several accesses share a next use: the results are undefined, but the call
+    # ends, writes nothing outside its arrays and leaves a status other than 2;
+    # `one value` needs the check on what a batch's evictions take off the buffer
+    n = 5000
+    rng = np.random.default_rng(len(case))
+    t = np.arange(n - 1)
+    later = {"one value": np.full(n - 1, n - 1), "few values": np.minimum((t // 900 + 1) * 900 + t % 3, n - 1),
+             "any later position": t + 1 + (rng.random(n - 1) * (n - 1 - t)).astype(np.int64)}[case]
+    nxt = np.concatenate([np.maximum(later, t + 1), [0xFFFFFFFF]]).astype(np.uint32)
+    caps = np.array([1, 40, 64, 100, 150, 1000], np.uint64)
+    need, pad = pc.lib().pc_belady_ws(n, caps.size), 4096
+    room = torch.full((pad + need + pad,), 0x5A, dtype=torch.uint8, device="cuda")
+    outs = {k: torch.full((caps.size + 64,), 7, dtype=torch.int64, device="cuda") for k in ("hits", "depthsum")}
+    ws = room[pad:pad + need]
+    pc.belady(pc.to_dev_u32(nxt), pc.to_dev_u64(caps), out={k: v[:caps.size] for k, v in outs.items()}, ws=ws)
+    torch.cuda.synchronize()
+    code = pc.workspace_status(ws)
+    assert code == 5 if case == "one value" else code in (0, 5)
+    assert (room[:pad] == 0x5A).all() and (room[pad + need:] == 0x5A).all()
+    assert all((v[caps.size:] == 7).all() for v in outs.values())

@@ -167,3 +167,16 @@ def test_per_insert_walk_takes_what_the_greedy_takes(seed):
         mine, popped = per_insert(nb, ev, dm, d0, buf, pend)
         assert {rank[pend[j]] for j in mine} == {r for r in gone if order[r] not in buf}
         assert popped == sum(1 for r in gone if order[r] in buf)
+
+
+def test_copies_of_a_value_count_more_than_once():
+    # 36 accesses into free places, then 28 evictions, every insert the same
+    # value (a next[] that is not one-to-one): each copy finds an eviction left
+    # for itself, so more are gone than were evicted and the buffer's share is
+    # negative; the kernel must see that before it takes the share off its buffer
+    ev = sum(1 << j for j in range(36, 64))
+    gone, popped = per_insert(64, ev, 0, 0, [999], {j: 999 for j in range(64)})
+    assert len(gone) == 63 and popped == 28 - 63
+    # the same with different values
+    gone, popped = per_insert(64, ev, 0, 0, [999], {j: 998 - j for j in range(64)})
+    assert popped == 1 and len(gone) == 27
