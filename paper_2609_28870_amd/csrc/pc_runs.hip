@@ -245,7 +245,10 @@ __global__ __launch_bounds__(RUN_THREADS) void runs_compact_kernel(const uint32_
 
 // The first levels of the merge: each workgroup sorts BLOCK_RUNS consecutive
 // runs by p in LDS, bottom up, with the inclusive prefix sums of their lengths
-// and each run's sum over the earlier runs of the block with a smaller p.
+// and each run's sum over the earlier runs of the block with a smaller p.  The
+// p are distinct when prev is one-to-one; runs with equal p (any other prev)
+// keep their order, here and in the later merges, so that each run gets a place
+// of its own and no index is read from a place that was never written.
 constexpr int BLOCK_THREADS = 1024;
 constexpr int BLOCK_ITEMS = 2;
 constexpr int BLOCK_RUNS = BLOCK_THREADS * BLOCK_ITEMS;
@@ -277,10 +280,10 @@ __global__ __launch_bounds__(BLOCK_THREADS) void runs_block_kernel(
                 const int blk = i >> lvl, sb = (blk ^ 1) << lvl;
                 int lo = sb < m ? sb : m, hi = sb + (1 << lvl) < m ? sb + (1 << lvl) : m;
                 const int first = lo;
-                const uint32_t k = s_key[cur][i];
-                while (lo < hi) {   // first sibling key >= k (keys are distinct)
+                const uint32_t k = s_key[cur][i], from = k + (uint32_t)(blk & 1);
+                while (lo < hi) {   // the sibling's keys before k
                     const int mid = (lo + hi) >> 1;
-                    if (s_key[cur][mid] < k) lo = mid + 1;
+                    if (s_key[cur][mid] < from) lo = mid + 1;
                     else hi = mid;
                 }
                 const int rank = lo - first;
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(256) void runs_merge_kernel(const uint32_t *__restr
         const uint64_t blk = i >> lvl, g0 = (blk >> MERGE_BITS) << (lvl + MERGE_BITS);
         const int mine = (int)(blk & (MERGE_WAYS - 1));
         const uint32_t k = key[i];
-        // (positions fit 32 bits: r < 2^28)
+        // (positions fit 32 bits: r is at most n / 16 + 1024)
         uint32_t lo[MERGE_WAYS], hi[MERGE_WAYS];
 #pragma unroll
         for (int x = 0; x < MERGE_WAYS; ++x) {
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(256) void runs_merge_kernel(const uint32_t *__restr
             for (int x = 0; x < MERGE_WAYS; ++x) {
                 const uint32_t mid = (lo[x] + hi[x]) >> 1;
                 if (lo[x] < hi[x]) {
-                    if (v[x] < k) lo[x] = mid + 1;
+                    if (v[x] < k + (x < mine ? 1u : 0u)) lo[x] = mid + 1;
                     else hi[x] = mid;
                 }
             }

@@ -147,3 +147,35 @@ def test_many_runs_in_one_tile(burst, offset):
     info = exact(keys, offset)
     say(burst, info)
     assert not info["generic"] and info["runs"] >= burst
+
+
+@pytest.mark.parametrize("runs", [3, 100, 2047, 2049, 5000, 16385, 70000])
+def test_runs_that_share_their_previous_uses(runs):
+    """A prev that is not one-to-one: runs of 40 accesses, most of which start
+    at one of a few previous uses.  Each merge keeps the order of such runs, so
+    the count takes the earlier one as before, and every run has a place."""
+    rng = np.random.default_rng(runs)
+    first = 64 * rng.integers(1, 8, size=runs)                      # no run continues the one before it
+    some = rng.random(runs) < 0.1
+    first[some] = 640 + 64 * rng.integers(0, runs, size=int(some.sum()))
+    prev = np.concatenate([np.full(1000, NONE), (first[:, None] + np.arange(40)).reshape(-1)]).astype(np.uint32)
+    order = np.argsort(first, kind="stable")
+    at = np.empty(runs, np.int64)
+    at[order] = np.arange(runs)
+    tree = np.zeros(runs + 1, np.int64)
+    earlier = np.zeros(runs, np.int64)                              # earlier runs with p no larger
+    for r in range(runs):
+        k = int(at[r])
+        while k > 0:
+            earlier[r] += tree[k]
+            k -= k & -k
+        k = int(at[r]) + 1
+        while k <= runs:
+            tree[k] += 1
+            k += k & -k
+    want = np.concatenate([np.full(1000, NONE), np.repeat(1000 + 40 * earlier - first - 1, 40)]).astype(np.uint32)
+    up = pc.to_dev_u32(prev)
+    dist, ws = pc.stack_distance_runs(up, up)
+    info = pc.runs_info(ws)
+    assert info["runs"] == runs and not info["generic"], info
+    assert np.array_equal(pc.as_u32(dist), want)
