@@ -49,6 +49,11 @@
 // there, so a batch waits on no global memory (the next uses, depths and
 // masks come four batches at a time through LDS).  A refill syncs at once.
 //
+// The masks are made for a window of accesses at a time, or they would take
+// 8.1 bytes per access, many times the bitmaps of a few capacities.  A wave
+// leaves its state in memory at a window's end and takes it up again in the
+// next window's launch.
+//
 // Bound: the instructions of one wave, batch after batch, at the capacities
 // that evict most: 4.0e6 agent accesses at 69 capacities 0.139 s, 2.2 us a
 // batch of 64 (0.333 s with the joint ranking of all 128 candidates worked out
@@ -152,21 +157,23 @@ __device__ __forceinline__ uint32_t above_all(const uint32_t *buf, uint32_t len,
     return from >= len ? len : above_in(buf, len, x, from);
 }
 
-// What a batch's evictions need of next[] alone, once for all capacities: per
-// access the accesses of its batch whose next uses lie past the batch and
-// above its own (their number is its rank), and per batch the positions that
-// the batch links to inside itself.  One wave per batch.
+// What a batch's evictions need of next[] alone, once for all capacities, for
+// the accesses [from, to): per access the accesses of its batch whose next uses
+// lie past the batch and above its own (their number is its rank), and per
+// batch the positions that the batch links to inside itself.  One wave per
+// batch.
 __global__ __launch_bounds__(4 * WAVE) void belady_rank_kernel(const uint32_t *__restrict__ next, uint64_t n,
+                                                               uint64_t from, uint64_t to,
                                                                uint64_t *__restrict__ higher,
                                                                uint64_t *__restrict__ links,
                                                                int32_t *__restrict__ err) {
     __shared__ __align__(16) uint32_t s_val[4][WAVE];
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-    const uint64_t batches = (n + WAVE - 1) / WAVE;
+    const uint64_t batches = (to - from + WAVE - 1) / WAVE;
     for (uint64_t b0 = (uint64_t)blockIdx.x * 4; b0 < batches; b0 += (uint64_t)gridDim.x * 4) {
-        const uint64_t b = b0 + w, t = b * WAVE + lane;
+        const uint64_t b = b0 + w, at = b * WAVE + lane, t = from + at;
         const uint32_t x = checked_next(load_next(next, t, n), t, n, err);
-        const uint64_t we = (b + 1) * WAVE;
+        const uint64_t we = from + (b + 1) * WAVE;
         const uint32_t v = x != NONE && x >= we ? x : 0u;
         const uint64_t link = wave_or64(x != NONE && x < we ? 1ull << (x & (WAVE - 1)) : 0ull);
         __syncthreads();
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(4 * WAVE) void belady_rank_kernel(const uint32_t *_
             m[i / 8] |= (uint32_t)(a.x > v) << (4 * i % 32) | (uint32_t)(a.y > v) << (4 * i % 32 + 1) |
                         (uint32_t)(a.z > v) << (4 * i % 32 + 2) | (uint32_t)(a.w > v) << (4 * i % 32 + 3);
         }
-        if (t < n) higher[t] = (uint64_t)m[0] | (uint64_t)m[1] << 32;
+        if (t < to) higher[at] = (uint64_t)m[0] | (uint64_t)m[1] << 32;
         if (lane == 0 && b < batches) links[b] = link;
     }
 }
@@ -388,7 +395,22 @@ struct BelGroup {
     uint64_t link[BEL_GROUP];
 };
 
+// What a capacity's wave hands from one window to the next.
+struct BelSaved {
+    uint64_t ring[BEL_RING], fl_val[WAVE];
+    uint64_t theta, bm_hi, ex_lo, fl_lo, hits, dsum;
+    uint32_t buf[BEL_BUF];
+    uint32_t bufn, fl_n, dead, size;
+    uint32_t stopped;   // 0 once the window is through: if a check ended it, the later ones do nothing
+};
+
+// The accesses [from, to), `from` a multiple of BEL_WINDOW: 0, or the state
+// is resumed.  `higher` and `links` are indexed as if they held all accesses;
+// saved: nullptr when there is one window only.  The loop is short of scalar
+// registers, so nothing is added to it that can wait elsewhere.
+template <bool RESUME>
 __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__restrict__ depth, uint64_t n,
+                           uint64_t from, uint64_t to, BelSaved *saved,
                            uint64_t c64, uint64_t *__restrict__ l0, uint64_t *__restrict__ l1, uint64_t w0,
                            const uint64_t *__restrict__ higher, const uint64_t *__restrict__ links,
                            uint8_t *__restrict__ flags, uint64_t *hits_out, uint64_t *dsum_out, int32_t *err,
@@ -406,44 +428,73 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
     const uint32_t c = clamp32(c64 < n ? c64 : n);
     uint32_t dead = 0, size = 0;
     uint64_t hits = 0, dsum = 0;
+    if constexpr (RESUME) {
+        if (saved->stopped) return;
+        S.bufn = (uint32_t)__builtin_amdgcn_readfirstlane((int)saved->bufn);
+        S.theta = readlane64(saved->theta, 0);
+        S.bm_hi = readlane64(saved->bm_hi, 0);
+        S.ex_lo = readlane64(saved->ex_lo, 0);
+        S.fl_lo = readlane64(saved->fl_lo, 0);
+        S.fl_n = (uint32_t)__builtin_amdgcn_readfirstlane((int)saved->fl_n);
+        S.fl_val = saved->fl_val[lane];
+        dead = (uint32_t)__builtin_amdgcn_readfirstlane((int)saved->dead);
+        size = (uint32_t)__builtin_amdgcn_readfirstlane((int)saved->size);
+        hits = readlane64(saved->hits, 0);
+        dsum = readlane64(saved->dsum, 0);
+        for (uint64_t i = lane; i < BEL_RING; i += WAVE) s_ring[i] = saved->ring[i];
+        for (uint32_t i = lane; i < S.bufn; i += WAVE) s_a[i] = saved->buf[i];
+        __syncthreads();
+    }
+    // (a wave that an internal check stops leaves the mark)
+    if (saved && lane == 0) saved->stopped = 1;
+    // what only the end needs waits in LDS
+    __shared__ BelSaved *s_saved;
+    __shared__ uint64_t *s_out[2];
+    s_saved = saved;
+    s_out[0] = hits_out;
+    s_out[1] = dsum_out;
+    uint32_t n32 = (uint32_t)n;   // (in a vector register)
+    __asm__ volatile("" : "+v"(n32));
+    auto length = [&]() { return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)n32); };
     const int own = lane / WALK, own_at = own * WALK;   // the lane's group of the walk, its first access
     // A group's next uses, depths and masks lie in LDS, and the next group's
     // are on their way in registers: a batch that waited for a load of its own
     // would wait for the newest one too, and for its inserts into the bitmap.
-    const uint64_t batches = (n + WAVE - 1) / WAVE;
+    const uint64_t batches = (to + WAVE - 1) / WAVE;
     // each lane four consecutive accesses, one load per array
     BelQuad xa, da{0, 0, 0, 0}, ha0, ha1;
     uint64_t lk = 0;   // the links of the group's batches, one per lane
     auto load_group = [&](uint64_t b0) {
         const uint64_t t = b0 * WAVE + 4 * lane;
-        if ((b0 + BEL_GROUP) * WAVE <= n) {
+        if ((b0 + BEL_GROUP) * WAVE <= to) {
             xa = *reinterpret_cast<const BelQuad *>(next + t);
             if (depth) da = *reinterpret_cast<const BelQuad *>(depth + t);
             ha0 = reinterpret_cast<const BelQuad *>(higher + t)[0];
             ha1 = reinterpret_cast<const BelQuad *>(higher + t)[1];
         } else {
             auto one = [&](const uint32_t *p, uint64_t k, uint64_t m, uint32_t none) { return k < m ? p[k] : none; };
-            xa = BelQuad{one(next, t, n, NONE), one(next, t + 1, n, NONE), one(next, t + 2, n, NONE),
-                         one(next, t + 3, n, NONE)};
-            if (depth) da = BelQuad{one(depth, t, n, 0), one(depth, t + 1, n, 0), one(depth, t + 2, n, 0),
-                                    one(depth, t + 3, n, 0)};
+            xa = BelQuad{one(next, t, to, NONE), one(next, t + 1, to, NONE), one(next, t + 2, to, NONE),
+                         one(next, t + 3, to, NONE)};
+            if (depth) da = BelQuad{one(depth, t, to, 0), one(depth, t + 1, to, 0), one(depth, t + 2, to, 0),
+                                    one(depth, t + 3, to, 0)};
             const uint32_t *h = reinterpret_cast<const uint32_t *>(higher);
-            ha0 = BelQuad{one(h, 2 * t, 2 * n, 0), one(h, 2 * t + 1, 2 * n, 0), one(h, 2 * t + 2, 2 * n, 0),
-                          one(h, 2 * t + 3, 2 * n, 0)};
-            ha1 = BelQuad{one(h, 2 * t + 4, 2 * n, 0), one(h, 2 * t + 5, 2 * n, 0), one(h, 2 * t + 6, 2 * n, 0),
-                          one(h, 2 * t + 7, 2 * n, 0)};
+            const uint64_t u = 2 * t, m = 2 * to;
+            ha0 = BelQuad{one(h, u, m, 0), one(h, u + 1, m, 0), one(h, u + 2, m, 0),
+                          one(h, u + 3, m, 0)};
+            ha1 = BelQuad{one(h, u + 4, m, 0), one(h, u + 5, m, 0), one(h, u + 6, m, 0),
+                          one(h, u + 7, m, 0)};
         }
         if (lane < BEL_GROUP) lk = b0 + lane < batches ? links[b0 + lane] : 0ull;
     };
-    load_group(0);
-    for (uint64_t t0 = 0; t0 < n; t0 += WAVE) {
+    load_group(from / WAVE);
+    for (uint64_t t0 = from; t0 < to; t0 += WAVE) {
         const int in_group = (int)((t0 / WAVE) % BEL_GROUP);
         if (in_group == 0) {
             __syncthreads();
             const uint64_t t = t0 + 4 * lane;
             reinterpret_cast<uint4 *>(L.next)[lane] =
-                make_uint4(checked_next(xa.x, t, n, err), checked_next(xa.y, t + 1, n, err),
-                           checked_next(xa.z, t + 2, n, err), checked_next(xa.w, t + 3, n, err));
+                make_uint4(checked_next(xa.x, t, n32, err), checked_next(xa.y, t + 1, n32, err),
+                           checked_next(xa.z, t + 2, n32, err), checked_next(xa.w, t + 3, n32, err));
             reinterpret_cast<uint4 *>(L.depth)[lane] = make_uint4(da.x, da.y, da.z, da.w);
             reinterpret_cast<uint4 *>(L.higher)[2 * lane] = make_uint4(ha0.x, ha0.y, ha0.z, ha0.w);
             reinterpret_cast<uint4 *>(L.higher)[2 * lane + 1] = make_uint4(ha1.x, ha1.y, ha1.z, ha1.w);
@@ -455,9 +506,9 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
         const uint64_t hi_mask = L.higher[in_group][lane];
         const uint32_t rank = (uint32_t)__popcll(hi_mask);
         const uint64_t t = t0 + lane;
-        const bool valid = t < n;
+        const bool valid = t < to;
         const uint32_t xv = xq, dv = dq;
-        const int nb = n - t0 < (uint64_t)WAVE ? (int)(n - t0) : WAVE;
+        const int nb = to - t0 < (uint64_t)WAVE ? (int)(to - t0) : WAVE;
         const uint64_t vmask = nb == WAVE ? ~0ull : (1ull << nb) - 1;
         const uint64_t we = t0 + WAVE;
         const uint32_t we32 = clamp32(we), t32 = (uint32_t)t0;
@@ -493,7 +544,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
         uint64_t hm = (wbits | link) & vmask;
         const uint32_t misses = (uint32_t)__popcll(vmask & ~hm);
         const uint32_t E = size + misses > c ? size + misses - c : 0u;
-        if (E > dead && dead + S.bufn < (uint32_t)WAVE) refill(S, l0, l1, we, n, rend);
+        if (E > dead && dead + S.bufn < (uint32_t)WAVE) refill(S, l0, l1, we, length(), rend);
 
         bool to_buffer, to_bitmap;
         uint32_t popped = 0;
@@ -617,7 +668,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
                         S.bufn -= popped;
                         popped = 0;
                         above = NONE;
-                        refill(S, l0, l1, we, n, rend);
+                        refill(S, l0, l1, we, length(), rend);
                         top = buffer_top(S);
                         pb = S.bufn ? (uint32_t)__builtin_amdgcn_readlane((int)top, 0) : 0u;
                     }
@@ -715,14 +766,36 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
         // next batch's ring end
         if ((w + 1) % BEL_SYNC == 0) ring_sync(S, l0, l1, rend + 1, false);
     }
+    if (to < length()) {
+        saved = s_saved;
+        for (uint64_t i = lane; i < BEL_RING; i += WAVE) saved->ring[i] = s_ring[i];
+        for (uint32_t i = lane; i < S.bufn; i += WAVE) saved->buf[i] = S.buf[S.head + i];
+        saved->fl_val[lane] = S.fl_val;
+        if (lane == 0) {
+            saved->bufn = S.bufn;
+            saved->theta = S.theta;
+            saved->bm_hi = S.bm_hi;
+            saved->ex_lo = S.ex_lo;
+            saved->fl_lo = S.fl_lo;
+            saved->fl_n = S.fl_n;
+            saved->dead = dead;
+            saved->size = size;
+            saved->hits = hits;
+            saved->dsum = dsum;
+            saved->stopped = 0;
+        }
+        return;
+    }
     if (lane == 0) {
-        *hits_out = hits;
-        *dsum_out = dsum;
+        *s_out[0] = hits;
+        *s_out[1] = dsum;
     }
 }
 
+template <bool RESUME>
 __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict__ next,
                                                       const uint32_t *__restrict__ depth, uint64_t n,
+                                                      uint64_t from, uint64_t to, BelSaved *__restrict__ saved,
                                                       const uint64_t *__restrict__ caps, uint64_t *__restrict__ l0s,
                                                       uint64_t *__restrict__ l1s, uint64_t w0, uint64_t w1,
                                                       const uint64_t *__restrict__ higher,
@@ -740,6 +813,7 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
     const uint64_t c = caps[k];
     uint8_t *fl = flags ? flags + (uint64_t)k * n : nullptr;
     if (c == 0) {
+        if (from > 0) return;
         if (fl)
             for (uint64_t t = threadIdx.x; t < n; t += WAVE) fl[t] = 0;
         if (threadIdx.x == 0) {
@@ -748,8 +822,9 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
         }
         return;
     }
-    belady_one(next, depth, n, c, l0s + (uint64_t)k * w0, l1s + (uint64_t)k * w1, w0, higher, links,
-               fl, hits + k, dsum + k, err, s_a, s_b, s_new, s_mark, s_walk, s_ring, s_group);
+    belady_one<RESUME>(next, depth, n, RESUME ? from : 0, to, saved ? saved + k : nullptr, c, l0s + (uint64_t)k * w0,
+                       l1s + (uint64_t)k * w1, w0, higher, links, fl, hits + k, dsum + k, err, s_a, s_b, s_new,
+                       s_mark, s_walk, s_ring, s_group);
 }
 
 // bitmap words per capacity: one bit per position plus a word of slack, and
@@ -757,9 +832,15 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
 static uint64_t bel_w0(uint64_t n) { return (n + 2 * WAVE) / 64 + 1; }
 static uint64_t bel_w1(uint64_t n) { return bel_w0(n) / 64 + 2; }
 
+// Accesses per window: 136 MB of masks.  At a window's end all capacities wait
+// for the slowest: 2.8e7 accesses at 69 capacities 979 ms, in one window 973,
+// in windows of 2^22 992.
+constexpr uint64_t BEL_WINDOW = 1ull << 24;
+static_assert(BEL_WINDOW % (BEL_GROUP * WAVE) == 0 && BEL_WINDOW % (BEL_SYNC * WAVE) == 0, "windows are whole groups");
 struct BelWs {
     int32_t *hdr;
     uint64_t *l0, *l1, *links, *higher;
+    BelSaved *saved;
     size_t bytes;
 };
 static BelWs bel_ws(void *ws, uint64_t n, uint32_t n_caps) {
@@ -768,8 +849,10 @@ static BelWs bel_ws(void *ws, uint64_t n, uint32_t n_caps) {
     w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
     w.l0 = c.take<uint64_t>(n_caps * (bel_w0(n) + bel_w1(n)));
     w.l1 = w.l0 + n_caps * bel_w0(n);
-    w.links = c.take<uint64_t>((n + WAVE - 1) / WAVE);
-    w.higher = c.take<uint64_t>(n);
+    const uint64_t m = n < BEL_WINDOW ? n : BEL_WINDOW;
+    w.links = c.take<uint64_t>((m + WAVE - 1) / WAVE);
+    w.higher = c.take<uint64_t>(m);
+    w.saved = n > BEL_WINDOW ? c.take<BelSaved>(n_caps) : nullptr;
     w.bytes = c.off;
     return w;
 }
@@ -797,13 +880,20 @@ pc_status pc_belady(const uint32_t *next, const uint32_t *depth, uint64_t n, con
     f.add(w.l0, 0u, 2 * (size_t)n_caps * (w0 + w1));
     const pc_status st = pc::fill_all(f, s);
     if (st != PC_OK) return st;
-    if (n > 0) {
-        const uint64_t groups = (n + 4 * pc::WAVE - 1) / (4 * pc::WAVE), most = (uint64_t)pc::device_cus() * 16;
-        PC_LAUNCH(pc::K_BELADY_RANK, pc::belady_rank_kernel, dim3((unsigned)(groups < most ? groups : most)),
-                  dim3(4 * pc::WAVE), 0, s, next, n, w.higher, w.links, w.hdr);
-    }
-    PC_LAUNCH(pc::K_BELADY, pc::belady_kernel, dim3(n_caps), dim3(pc::WAVE), 0, s, next, depth, n, caps, w.l0, w.l1, w0,
-              w1, w.higher, w.links, hits, depthsum, hit_flags, w.hdr);
+    uint64_t from = 0;
+    do {
+        const uint64_t to = n - from < pc::BEL_WINDOW ? n : from + pc::BEL_WINDOW;
+        if (to > from) {
+            const uint64_t per = 4 * pc::WAVE, groups = (to - from + per - 1) / per;
+            const uint64_t most = (uint64_t)pc::device_cus() * 16;
+            PC_LAUNCH(pc::K_BELADY_RANK, pc::belady_rank_kernel, dim3((unsigned)(groups < most ? groups : most)),
+                      dim3(4 * pc::WAVE), 0, s, next, n, from, to, w.higher, w.links, w.hdr);
+        }
+        const auto kernel = from ? pc::belady_kernel<true> : pc::belady_kernel<false>;
+        PC_LAUNCH(pc::K_BELADY, kernel, dim3(n_caps), dim3(pc::WAVE), 0, s, next, depth, n, from, to, w.saved, caps,
+                  w.l0, w.l1, w0, w1, w.higher - from, w.links - from / pc::WAVE, hits, depthsum, hit_flags, w.hdr);
+        from = to;
+    } while (from < n);
     return PC_OK;
 }
 

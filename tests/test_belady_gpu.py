@@ -84,6 +84,38 @@ def test_stream_lengths_around_batches_and_groups(n, distinct):
                          depth)
 
 
+WINDOW = 1 << 24   # accesses whose masks the workspace holds at a time
+
+
+@pytest.mark.parametrize("n", [WINDOW, WINDOW + 1, 2 * WINDOW + 12345])
+def test_streams_longer_than_a_window_of_masks(n):
+    # each capacity's wave stops at a window's end and goes on in the next
+    # launch: hits, depths and flags on both sides, nothing past the workspace
+    rng = np.random.default_rng(n)
+    keys = rng.integers(0, 30000, size=n).astype(np.uint64)
+    keys[WINDOW - 2000:WINDOW + 2000] %= 700       # reuses on both sides of the first edge
+    cold = rng.random(n) < 0.02
+    keys[cold] = 10 ** 6 + np.arange(int(cold.sum()))
+    depth = rng.integers(0, 5000, size=n).astype(np.uint32)
+    caps = [0, 1, 64, 500, 9000, 29000, 10 ** 7]
+    ids = oracle.key_ids(keys)
+    _, nxt = oracle.prev_next(keys, ids)
+    want = oracle.belady(keys, caps, ids, nxt, flags=True, threads=8)
+    need, pad = pc.lib().pc_belady_ws(n, len(caps)), 4096
+    room = torch.full((pad + need + pad,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws = room[pad:pad + need]
+    out, _ = pc.belady(pc.to_dev_u32(nxt), pc.to_dev_u64(np.asarray(caps, np.uint64)), pc.to_dev_u32(depth),
+                       flags=True, ws=ws)
+    torch.cuda.synchronize()
+    assert pc.workspace_status(ws) == 0
+    flags = out["flags"].cpu().numpy()
+    for k, (h, fl) in enumerate(want):
+        assert int(pc.as_u64(out["hits"])[k]) == h, caps[k]
+        assert np.array_equal(flags[k], fl), caps[k]
+        assert int(pc.as_u64(out["depthsum"])[k]) == int(depth[fl.astype(bool)].astype(np.uint64).sum()), caps[k]
+    assert (room[:pad] == 0x5A).all() and (room[pad + need:] == 0x5A).all()
+
+
 def test_looping_scan_and_degenerate_streams():
     # a cyclic scan one block larger than the cache: MIN keeps c - 1 of the
     # loop's blocks per round
