@@ -124,7 +124,6 @@ constexpr int HASH_RING = 4;                                        // token chu
 // 2.10 ms, with three 2.35; on 2.8e7, where the longest chain counts, 0.66 and
 // 0.83 ms).
 constexpr int HASH_WG_PER_CU = 2;
-static_assert(HASH_SWEEPS % HASH_RING == 0, "a round's chunks fill the ring a whole number of times");
 
 // One row (request) of one round: its first token, the position of its first
 // key, the number of blocks (0: none) and the first one's depth.
@@ -299,42 +298,42 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         // lane fetches its row's values by ds_bpermute)
         constexpr bool SHORT = SPAN < WAVE;
         constexpr int H = SHORT ? 1 : SPAN / WAVE, RPS = SHORT ? WAVE / SPAN : 1;
+        constexpr int SWEEPS = ROWS * SPAN / (DIGEST_WAVES * WAVE);   // of 16-token blocks
+        static_assert(SWEEPS % HASH_RING == 0, "a round's chunks fill the ring a whole number of times");
         static_assert(DIGEST_WAVES % H == 0, "a wave's sweeps start at the same block of their rows");
         // sweep 0's (first) row, and every sweep's first block
         const int row0 = (w - 1) / H * RPS, first = (w - 1) % H * WAVE;
         RoundRow r2{}, r1{}, r0{}, rs{};   // rounds p + 2, p + 1, p, p - 1
         auto row_of = [&](int q) { return row0 + DIGEST_WAVES / H * RPS * q; };
-        // blocks of sweep q (from 64 down; none below 1)
-        auto count_of = [&](const RoundRow &r, int q) {
-            return __builtin_amdgcn_readlane((int)r.m, row_of(q)) - first;
-        };
+        // blocks of the sweep at `row` (from 64 down; none below 1)
+        auto count_of = [&](const RoundRow &r, int row) { return __builtin_amdgcn_readlane((int)r.m, row) - first; };
         // SHORT: value x of the row that this lane's block is in
-        auto of_row = [&](uint32_t x, int q) {
-            return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (row_of(q) + lane / SPAN), (int)x);
+        auto of_row = [&](uint32_t x, int row) {
+            return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (row + lane / SPAN), (int)x);
         };
         // Every lane loads, idle ones the sweep's first block or, without one,
         // a few unused header words: with a branch around a load the wait for
         // an older one would count as a wait for all.
-        auto fetch = [&](TokChunk &c, const RoundRow &r, int q, int g) {
+        auto fetch = [&](TokChunk &c, const RoundRow &r, int row, bool any, int g) {
             if constexpr (SHORT) {
                 const uint32_t sub = lane % SPAN;
-                const bool mine = sub < of_row(r.m, q);
-                const uint64_t tok = (uint64_t)of_row((uint32_t)r.tok, q) |
-                                     (uint64_t)of_row((uint32_t)(r.tok >> 32), q) << 32;
+                const bool mine = any && sub < of_row(r.m, row);
+                const uint64_t tok = (uint64_t)of_row((uint32_t)r.tok, row) |
+                                     (uint64_t)of_row((uint32_t)(r.tok >> 32), row) << 32;
                 const int32_t *src = mine ? tokens + tok + sub * B + 16 * (uint32_t)g : idle;
                 if (g < G - 1) load16(src, c);
                 else load_last(src, last, c);
                 return;
             }
-            const int cnt = count_of(r, q);
-            const uint64_t tok = readlane64(r.tok, row_of(q)) + (uint64_t)(uint32_t)first * B + 16 * (uint32_t)g;
+            const int cnt = any ? count_of(r, row) : 0;
+            const uint64_t tok = readlane64(r.tok, row) + (uint64_t)(uint32_t)first * B + 16 * (uint32_t)g;
             const char *src = cnt > 0 ? reinterpret_cast<const char *>(tokens + tok)
                                       : reinterpret_cast<const char *>(idle);
             const uint32_t off = lane < cnt ? (uint32_t)lane * B * 4 : 0u;
             if (G16 == 1 || g < G - 1) load16(reinterpret_cast<const int32_t *>(src + off), c);
             else load_last(reinterpret_cast<const int32_t *>(src + off), last, c);
         };
-        // sweep q's keys of round p - 1 leave the tile, and the digests of
+        // the sweep's keys of round p - 1 leave the tile, and the digests of
         // round p + 1 take their place
         auto put = [&](uint64_t k, uint64_t at, uint32_t b) {
             keys[at] = k;
@@ -345,20 +344,19 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
                 for (int x = 0; x < 4; ++x) atomicAdd(&L.hist[256 * x + ((lo >> (8 * x)) & 0xFF)], 1u);
             }
         };
-        auto exchange = [&](uint64_t *tile, int q, int cnt, uint64_t d) {
+        auto exchange = [&](uint64_t *tile, int row, int cnt, uint64_t d) {
             if constexpr (SHORT) {
-                const uint32_t sub = lane % SPAN, out = of_row(rs.m, q), pos = of_row(rs.pos, q), b = of_row(rs.b, q);
-                const uint32_t in = of_row(r1.m, q);
-                uint64_t *at = tile + (row_of(q) + lane / SPAN) * ROW + sub;
+                const uint32_t sub = lane % SPAN, out = of_row(rs.m, row), pos = of_row(rs.pos, row);
+                const uint32_t b = of_row(rs.b, row), in = of_row(r1.m, row);
+                uint64_t *at = tile + (row + lane / SPAN) * ROW + sub;
                 if (sub < out) put(*at, deepest_first ? pos - sub : pos + sub, b + sub);
                 if (sub < in) *at = d;
                 return;
             }
-            const int row = row_of(q);
             uint64_t *at = tile + row * ROW + lane;
             // (readlane before the branch: inside it a register may hold the
             // active lanes' values only)
-            const int out = count_of(rs, q);
+            const int out = count_of(rs, row);
             const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)rs.pos, row);
             const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)rs.b, row) + (uint32_t)first;
             const uint64_t o = deepest_first ? (uint64_t)pos - (uint32_t)first : (uint64_t)pos + (uint32_t)first;
@@ -368,10 +366,35 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
             }
             if (lane < cnt) *at = d;
         };
+        // this wave's sweeps that have blocks in a round, as a mask of their
+        // (first) rows
+        uint64_t mine = 0;
+        for (int q = 0; q < sweeps; ++q) mine |= 1ull << row_of(q);
+        auto sweeps_in = [&](const RoundRow &r) {
+            uint64_t m = ballot(r.m > (uint32_t)first);
+            if constexpr (SHORT)
+                for (int x = 1; x < RPS; x *= 2) m |= m >> x;
+            return m & mine;
+        };
+        // the chunks to fetch, a sweep after the other: the sweeps left and the
+        // next one's next chunk (none left: an idle fetch)
+        uint64_t left = 0;
+        int chunk = 0;
+        auto fetch_next = [&](TokChunk &c, const RoundRow &r) {
+            fetch(c, r, left ? __builtin_ctzll(left) : 0, left != 0, chunk);
+            if (left && ++chunk == G) {
+                chunk = 0;
+                left &= left - 1;
+            }
+        };
         __syncthreads();   // phase -3: round 0 is planned
         if (lane < ROWS) r1 = L.rows[0][lane];
+        left = sweeps_in(r1);
 #pragma unroll
-        for (int k = 0; k < HASH_RING; ++k) fetch(ring[k], r1, k / G, k % G);
+        for (int k = 0; k < HASH_RING; ++k) {
+            if constexpr (G16 == 1) fetch(ring[k], r1, row_of(k), true, 0);
+            else fetch_next(ring[k], r1);
+        }
         __syncthreads();   // phase -2
         for (int p = -1;; ++p) {
             // an opaque copy of the lane index: what is derived from it is worked
@@ -381,45 +404,54 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
             uint64_t *tile = L.tile[(p + 1) & 1] + first;
             if constexpr (G16 == 1) {
 #pragma unroll
-                for (int q = 0; q < HASH_SWEEPS; ++q) {
-                    const int cnt = count_of(r1, q);
+                for (int q = 0; q < SWEEPS; ++q) {
+                    const int row = row_of(q);
+                    const int cnt = SHORT ? __popcll(ballot((uint32_t)(lane % SPAN) < of_row(r1.m, row))) : count_of(r1, row);
                     uint64_t d = 0;
                     if (cnt > 0) d = fold_end(fold16(0, ring[q % HASH_RING]));
-                    exchange(tile, q, cnt, d);
-                    if (q + HASH_RING < HASH_SWEEPS) fetch(ring[q % HASH_RING], r1, q + HASH_RING, 0);
-                    else fetch(ring[q % HASH_RING], r2, q + HASH_RING - HASH_SWEEPS, 0);
+                    exchange(tile, row, cnt, d);
+                    if (q + HASH_RING < SWEEPS) fetch(ring[q % HASH_RING], r1, row_of(q + HASH_RING), true, 0);
+                    else fetch(ring[q % HASH_RING], r2, row_of(q + HASH_RING - SWEEPS), true, 0);
                 }
             } else {
-                // chunk (q, g) is folded, chunk (fq, fg), four ahead, fetched;
-                // past this round's chunks, the next round's first ones
-                int q = 0, g = 0, fq = HASH_RING / G, fg = HASH_RING % G;
+                // Sweeps without blocks are passed over, so that a round costs
+                // what it holds: the ones that only have keys to store first.
+                uint64_t now = sweeps_in(r1);
+                for (uint64_t out = sweeps_in(rs) & ~now; out; out &= out - 1) exchange(tile, __builtin_ctzll(out), 0, 0);
+                // A chunk is folded, the one four ahead fetched; past this round's
+                // chunks (rounded up to fours, at least four), the next round's
+                // first ones.
+                int quads = (__popcll(now) * G + HASH_RING - 1) / HASH_RING, g = 0;
+                quads = quads ? quads : 1;
                 uint64_t t = 0;
-                while (q < sweeps) {
+                for (; quads; --quads) {
+                    const bool here = quads > 1;
+                    if (!here) {
+                        left = sweeps_in(r2);
+                        chunk = 0;
+                    }
 #pragma unroll
                     for (int k = 0; k < HASH_RING; ++k) {
-                        int cnt;
-                        if constexpr (SHORT) cnt = __popcll(ballot((uint32_t)(lane % SPAN) < of_row(r1.m, q)));
-                        else cnt = count_of(r1, q);
-                        if (cnt > 0) {
+                        if (now) {
                             if (g < G - 1) t = fold16(t, ring[k]);
                             else t = fold_last(t, ring[k], last);
+                            if (++g == G) {
+                                const int row = __builtin_ctzll(now);
+                                exchange(tile, row, SHORT ? WAVE : count_of(r1, row), fold_end(t));
+                                t = 0;
+                                g = 0;
+                                now &= now - 1;
+                            }
                         }
-                        if (g == G - 1) {
-                            exchange(tile, q, cnt, fold_end(t));
-                            t = 0;
-                        }
-                        if (++g == G) { g = 0; ++q; }
                         // two at a time: mostly the halves of the same lines,
                         // which do not stay in the caches until the next fetch
                         if (k % 2)
 #pragma unroll
                             for (int x = k - 1; x <= k; ++x) {
-                                const bool here = fq < sweeps;
                                 RoundRow from;
                                 from.tok = here ? r1.tok : r2.tok;
                                 from.m = here ? r1.m : r2.m;
-                                fetch(ring[x], from, here ? fq : fq - sweeps, fg);
-                                if (++fg == G) { fg = 0; ++fq; }
+                                fetch_next(ring[x], from);
                             }
                     }
                 }
@@ -567,6 +599,31 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     const int chunks = ((int)block_size + 15) / 16;
     int sweeps = 1;
     while (sweeps < pc::HASH_SWEEPS && (sweeps * chunks < 16 || sweeps * chunks % pc::HASH_RING)) sweeps *= 2;
+    const uint64_t cus = (uint64_t)pc::device_cus(), mean = n_blocks / n_seqs;
+    const uint64_t need = (n_seqs + 2 * cus - 1) / (2 * cus);
+    int per_cu = pc::HASH_WG_PER_CU, span = 0;
+    // Many short requests: a round of 64 blocks of one request would leave most
+    // of it empty, so a sweep takes blocks of several requests.  The few long
+    // ones that may be among them pay for the shorter rounds, hence not for
+    // fewer requests (us with spans of 16 / 32 / 64 and, in brackets, of a wave
+    // per 64 requests that walks them 32 blocks at a time):
+    //   16 tokens, 1.0e6 requests of 1..8 blocks    208 239 419 (388)
+    //              1.0e6 of 1..32                   407 267 479 (447)
+    //              1.0e5 of 13, log-normal          244 237 200 (451)
+    //   32 tokens, 1.0e6 of 1..8                    308 541 974 (580)
+    //              1.0e4 of 1..32                    26  25  39  (45)
+    //   64 tokens, 5.0e5 of 1..8                    274 496 898 (491)
+    //              5.0e5 of 1..32                   651 706 1010 (621)
+    //              1.0e4 of 26, log-normal          380 209 182 (366)
+    if (chunks < 8) {
+        const bool few_tokens = block_size < 16, one = block_size == 16;
+        const uint32_t many = one ? 1u << 19 : chunks == 2 || chunks == 3 ? 1u << 13 : 1u << 16;
+        if (mean < 12 && n_seqs >= 1u << 19 && chunks > 1) span = 16;
+        else if (mean < (few_tokens ? 128 : 48) && n_seqs >= many) span = 32;
+        else if (mean < 24 && n_seqs >= 1u << 11 && !one) span = 64;
+    }
+    const uint64_t sweep = pc::DIGEST_WAVES * pc::WAVE;   // blocks of one sweep of every digest wave
+    while (span && sweeps * sweep / span > pc::WAVE) sweeps /= 2;   // a lane of the chain wave per row
     // Rows in work at once (256 CUs x workgroups per CU x entries / span): the
     // fewer, the closer each request runs to its chain's own pace; the more,
     // the better the memory is used.  Best is about a quarter of the requests,
@@ -585,10 +642,7 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     // 2.16 2.26; 1.7e6 of 256 in 18,389 0.44 0.32 0.38 0.41; with smaller
     // blocks the shorter rounds cost more: 5.0e7 of 64 in 156,000 2.77 against
     // 2.01).
-    const uint64_t entries = (uint64_t)sweeps * pc::DIGEST_WAVES * pc::WAVE;
-    const uint64_t cus = (uint64_t)pc::device_cus(), mean = n_blocks / n_seqs;
-    const uint64_t need = (n_seqs + 2 * cus - 1) / (2 * cus);
-    int per_cu = pc::HASH_WG_PER_CU, span = 0;
+    const uint64_t entries = sweeps * sweep;
     for (int x = chunks < 8 ? 64 : 16; x <= 128 && !span; x *= 2)
         if (entries / x <= pc::WAVE && n_seqs >= 4 * per_cu * cus * (entries / x)) span = x;
     if (!span && sweeps == pc::HASH_SWEEPS) {
@@ -598,8 +652,17 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     } else if (!span) {
         span = need * 256 <= entries ? 256 : need * 32 <= entries ? 128 : 64;
     }
-    // (8192 requests of 8 blocks 0.078 ms, with 64 0.094)
-    if (chunks >= 8 && span == 64 && mean < 32 && n_seqs >= 8 * cus * (entries / 128)) span = 32;
+    if (chunks >= 8 && mean < 48) {
+        // (8192 requests of 8 blocks of 128 tokens 0.078 ms, with 64 0.094)
+        if (span == 64 && mean < 32 && n_seqs >= 8 * cus * (entries / 128)) span = 32;
+        // with more than a few blocks to a request they differ in length, and the
+        // long ones pay (1.0e5 of 13 blocks of 256 tokens, log-normal, us with 16
+        // / 32 / 64: 1908 1071 740; of 27 3216 1811 1073; 1..32 530 524 737)
+        if (span == 16 && mean >= 12) span = 32;
+        if (span == 32 && mean >= 24 && chunks >= 16) span = 64;
+        // (1.0e4 requests of 1..32 blocks of 128 tokens 66 us, with 128 81)
+        if (span == 128 && mean < 24 && n_seqs >= 1u << 13 && chunks < 16) span = 64;
+    }
     const uint64_t wgs = cus * per_cu, most = ((uint64_t)n_seqs + wgs - 1) / wgs;
     const int rows = (int)(entries / span);
     const int lanes = most < (uint64_t)rows ? (int)most : rows;
@@ -638,7 +701,8 @@ pc_status pc_hash_blocks(const int32_t *tokens, uint64_t n_tokens, const uint64_
     if (block_size == 16) {
         if (span == 256) PC_HASH(256, 1);
         else if (span == 128) PC_HASH(128, 1);
-        else PC_HASH(64, 1);
+        else if (span == 64) PC_HASH(64, 1);
+        else PC_HASH(32, 1);
     } else {
         if (span == 256) PC_HASH(256, 0);
         else if (span == 128) PC_HASH(128, 0);

@@ -78,3 +78,16 @@ def test_a_bad_request_is_skipped_and_reported():
     assert pc.workspace_status(ws) == 2      # one past the tokens, one past the blocks
     want, _ = oracle.hash_requests(np.arange(4096, dtype=np.int32), start[:1], length[:1], 16)
     assert np.array_equal(pc.as_u64(keys)[:4], want) and (pc.as_u64(keys)[4:] == 7).all()
+
+
+@pytest.mark.parametrize("n_seqs,B,most", [(1 << 19, 16, 9), (1 << 19, 16, 60), ((1 << 19) - 1, 16, 9), (1 << 19, 24, 9),
+                                           (1 << 19, 24, 40), (1 << 16, 10, 200), (1 << 13, 32, 60), ((1 << 13) - 1, 32, 40),
+                                           (1 << 11, 64, 40), ((1 << 11) - 1, 64, 40), (1 << 16, 64, 60),
+                                           (1 << 16, 128, 20), (1 << 13, 128, 40), (1 << 15, 256, 26), (1 << 15, 256, 52)])
+def test_short_requests_share_the_sweeps(n_seqs, B, most):
+    # on both sides of each rule on the number and the mean length of short
+    # requests; a few long ones among them leave most sweeps of a round empty
+    g = np.random.default_rng(n_seqs + B + most)
+    blocks = g.integers(0, most + 1, size=n_seqs)
+    blocks[g.integers(0, n_seqs, size=4)] = [700, 257, 64, 65]
+    check(blocks, B, most, deepest=B % 3 == 0, parent=B != 24, pad=1)
