@@ -1052,8 +1052,11 @@ static pc_status stack_distance_steps(const uint32_t *prev, const uint32_t *next
 // what they cost with four (3.0e6 random accesses 0.37 ms, 0.39 as launches,
 // 1.14 with four).  Larger calls keep the launches: one workgroup per CU is
 // too slow for the tiles (3.0e7: 1.42 against 0.89 ms), and 70 us of gated
-// launches are little beside the rest of such a step.
+// launches are little beside the rest of such a step.  At least 32 workgroups,
+// for the carries have 256 chunks however few the tiles are (3000 accesses 70
+// us; two workgroups 184, 16 76, 256 104; as launches 89).
 constexpr uint64_t SD_PERSISTENT_MAX = 1ull << 22;
+constexpr uint64_t SD_WORKGROUPS_MIN = 32;
 struct SdJob {
     const uint32_t *prev, *next;
     uint32_t *dist;
@@ -1167,7 +1170,8 @@ pc_status stack_distance_rare(const uint32_t *prev, const uint32_t *next, uint64
     for (int i = 0; i < j.p.passes; ++i) j.group[i] = seg_group(j.p.grid[i]);
     j.ctl = ctl;
     j.status = status;
-    const uint64_t tiles = (n + DOM_TILE - 1) / DOM_TILE;
+    uint64_t tiles = (n + DOM_TILE - 1) / DOM_TILE;
+    if (tiles < SD_WORKGROUPS_MIN) tiles = SD_WORKGROUPS_MIN;
     PC_LAUNCH(K_SD_PASS, sd_persistent_kernel, dim3(capped(tiles, 1)), dim3(DOM_THREADS), 0, s, j, gate);
     return PC_OK;
 }

@@ -119,6 +119,23 @@ def test_the_generic_path_behind_the_chained_one(n, low_shared):
         assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
 
 
+@pytest.mark.parametrize("n", [2047, 2049, 3000, 20_000, 65_535, 65_537, 262_145])
+@pytest.mark.parametrize("low_shared", [False, True])
+def test_one_launch_paths_with_more_workgroups_than_tiles(n, low_shared):
+    # up to 32 workgroups where the sort and the dominance count have a few
+    # tiles: some get none of a phase's chunks
+    keys = device_keys(n, max(2, n // 4), low_shared)
+    reqs = n // 50
+    off = torch.arange(reqs + 1, device="cuda") * n // reqs
+    prev, nxt, ws = pc.prev_next_chained(keys, off)
+    p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
+    assert pc.chained_info(ws)["generic"] and pc.workspace_status(ws) == 0
+    assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+    dist, ws = pc.stack_distance_runs(prev, nxt)
+    assert pc.workspace_status(ws) == 0
+    assert np.array_equal(pc.as_u32(dist), oracle.stack_distance_bit(p))
+
+
 @pytest.mark.parametrize("edges", ["classes", "one octave", "one edge", "top"])
 @pytest.mark.parametrize("n,shift", [(1, 0), (15, 1), (1 << 16, 3), ((1 << 20) + 1, 0), ((1 << 20) + 7, 2), (4_300_003, 1),
                                      (9_000_001, 0)])
