@@ -72,6 +72,20 @@ def chain_bytes(name, n, n_slots, m, n_req):
             }.get(name)
 
 
+def working_launches(calls, highs, runs):
+    """Launches per step that move data, where a path not taken is gated off
+    on the device and its launches return at once: `calls` prev/next calls, of
+    which `highs` sorted by the high key bits too, and the path that the stack
+    distance took (pc.runs_info; None: not over runs)."""
+    w = {"sort_onesweep_pass": 4 * calls, "link_partition": calls, "sort_digit_hist": calls, "sort_high_bits": highs}
+    if runs:
+        off = ("runs_compact", "runs_merge", "runs_fill") if runs["generic"] else (
+            "sd_cold_count", "sd_scan", "sd_tile_map", "sd_count", "sd_seg_scan", "sd_dominance_pass",
+            "sd_local_finish", "sd_one_launch")
+        w.update({name: 0 for name in off})
+    return w
+
+
 def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
@@ -453,8 +467,8 @@ def main():
         calls = 1
         highs = int(pc.high_key_passes_ran(pipe.ws_pn))
         n_slots = pn_elems = n_blocks
-    work_launches = {"sort_onesweep_pass": 4 * calls, "link_partition": calls, "sort_digit_hist": calls,
-                     "sort_high_bits": highs}
+    runs = pc.runs_info(pipe.ws_sd) if pipe.chained and not args.profile and not session_mode else None
+    work_launches = working_launches(calls, highs, runs)
     # bins: dist in, depth in unless it comes from the request layout, next in
     # when the next-use histogram is taken
     layout_depth = getattr(pipe, "layout_depth", False)
@@ -468,7 +482,7 @@ def main():
         entry = {"launches_per_step": launches // args.steps, "working_launches_per_step": wl,
                  "ms_per_step": round(per_step, 4)}
         cb_bytes = chain_bytes(name, n_blocks, n_slots, chain["unresolved"], trace.n_requests) if chain else None
-        if name in ALGO_BYTES or cb_bytes is not None:
+        if wl and (name in ALGO_BYTES or cb_bytes is not None):
             if cb_bytes is not None:
                 per_launch = cb_bytes
             elif name in GENERIC_PN:
@@ -582,8 +596,7 @@ def main():
         "stages": stages,
         "high_key_sort_passes": highs,
         "chained_prev_next": chain,
-        "stack_distance_runs": (pc.runs_info(pipe.ws_sd) if pipe.chained and not args.profile
-                                and not session_mode else None),
+        "stack_distance_runs": runs,
     }
     if args.profile:
         out["metric"] = "KV-block accesses/sec for hash+prev/next+workload characterisation; achieved HBM GB/s"

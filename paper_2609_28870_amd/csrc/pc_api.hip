@@ -25,6 +25,7 @@ static const char *kernel_name(KernelId k) {
     case K_SD_SEG: return "sd_seg_scan";
     case K_SD_PASS: return "sd_dominance_pass";
     case K_SD_LOCAL: return "sd_local_finish";
+    case K_SD_ALL: return "sd_one_launch";
     case K_MRC_HIST: return "mrc_hist";
     case K_REQ_ORDER: return "request_order";
     case K_REQ_DIST: return "request_distance";

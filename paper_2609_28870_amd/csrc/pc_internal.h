@@ -43,7 +43,7 @@ enum KernelId {
     K_HASH,
     K_HASH_ORDER,
     K_SORT_HIST,
-    K_SORT_HIGH,
+    K_SORT_HIGH,   // the persistent launch: the high key bits, or the whole of a path seldom taken
     K_SORT_PASS,
     K_LINK,
     K_PERM,
@@ -55,6 +55,7 @@ enum KernelId {
     K_SD_SEG,
     K_SD_PASS,
     K_SD_LOCAL,
+    K_SD_ALL,      // the dominance count as one persistent launch
     K_MRC_HIST,
     K_REQ_ORDER,
     K_REQ_DIST,

@@ -1172,7 +1172,7 @@ pc_status stack_distance_rare(const uint32_t *prev, const uint32_t *next, uint64
     j.status = status;
     uint64_t tiles = (n + DOM_TILE - 1) / DOM_TILE;
     if (tiles < SD_WORKGROUPS_MIN) tiles = SD_WORKGROUPS_MIN;
-    PC_LAUNCH(K_SD_PASS, sd_persistent_kernel, dim3(capped(tiles, 1)), dim3(DOM_THREADS), 0, s, j, gate);
+    PC_LAUNCH(K_SD_ALL, sd_persistent_kernel, dim3(capped(tiles, 1)), dim3(DOM_THREADS), 0, s, j, gate);
     return PC_OK;
 }
 

@@ -37,7 +37,7 @@ IDS = {"pc::hash_kernel": "hash_blocks", "pc::hash_classes_kernel": "hash_order"
        "pc::perm_partition_kernel": "perm_partition", "pc::perm_local_kernel": "perm_local",
        "pc::sort_init_kernel": "fill_u32", "pc::rare_gate_kernel": "fill_u32", "pc::fill_u32_kernel": "fill_u32",
        "pc::fill_all_kernel": "fill_u32",
-       "pc::sd_cold_count_kernel": "sd_cold_count", "pc::sd_persistent_kernel": "sd_scan",
+       "pc::sd_cold_count_kernel": "sd_cold_count", "pc::sd_persistent_kernel": "sd_one_launch",
        "pc::sd_scan_reduce_kernel": "sd_scan", "pc::sd_scan_apply_kernel": "sd_scan",
        "pc::sd_tile_map_kernel": "sd_tile_map", "pc::sd_count_kernel": "sd_count",
        "pc::sd_seg_reduce_kernel": "sd_seg_scan", "pc::sd_seg_carry_kernel": "sd_seg_scan",

@@ -30,6 +30,15 @@ def test_every_timed_kernel_has_algorithmic_bytes():
         assert bench.chain_bytes(name, 1 << 20, 1 << 14, 1 << 17, 1000) > 0, name
 
 
+def test_launches_of_the_path_not_taken_move_no_data():
+    over_runs = bench.working_launches(2, 0, {"generic": False})
+    assert over_runs["sd_dominance_pass"] == over_runs["sd_local_finish"] == over_runs["sd_one_launch"] == 0
+    assert "runs_fill" not in over_runs and over_runs["sort_onesweep_pass"] == 8
+    fell_back = bench.working_launches(2, 0, {"generic": True})
+    assert fell_back["runs_fill"] == 0 and "sd_dominance_pass" not in fell_back
+    assert "sd_dominance_pass" not in bench.working_launches(1, 1, None)
+
+
 @pytest.mark.parametrize("key", sorted(bench.PROFILES, key=str))
 def test_committed_profiles_parse(key):
     path = bench.profile_for(*key)
