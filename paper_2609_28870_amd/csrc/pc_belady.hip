@@ -106,10 +106,6 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t x) {
     return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, WAVE - 1) |
            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, WAVE - 1) << 32);
 }
-// inclusive prefix OR of one uint64 per lane
-__device__ __forceinline__ uint64_t wave_incl_or64(uint64_t x) {
-    return (uint64_t)wave_incl_or((uint32_t)x) | ((uint64_t)wave_incl_or((uint32_t)(x >> 32)) << 32);
-}
 // sum of one uint32 per lane, exact (as two 16-bit halves)
 __device__ __forceinline__ uint64_t wave_sum64(uint32_t x) {
     const uint32_t lo = wave_incl_scan(x & 0xFFFFu), hi = wave_incl_scan(x >> 16);
@@ -583,7 +579,7 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             // (wave_shr:1, 0 into lane 0)
             const uint32_t un_prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)un, 0x138, 0xf, 0xf, false);
             const uint64_t real = ballot(un > un_prev);
-            const uint32_t E = (uint32_t)__popcll(real);
+            const uint32_t n_real = (uint32_t)__popcll(real);
             // (2) Which candidates the real evictions take.  Each takes the
             // largest one present; the buffer's are present from the start, a
             // pending one after its own access.  For a value x let R(x) be the
@@ -591,8 +587,9 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             // buffer candidates above x, and r_i the count after the i-th
             // eviction, r_i = min(r_{i-1} + 1, A(x) + P_i(x)) where P_i(x)
             // counts the pending candidates above x inserted before it, hence
-            // R(x) = min(E, A(x) + E + m(x)) with m(x) the lowest sum of the
-            // walk "-1 per eviction, then +1 per such insert", access by access.
+            // R(x) = min(n, A(x) + n + m(x)) with n of them in all (n_real) and m(x)
+            // the lowest sum of the walk "-1 per eviction, then +1 per such insert",
+            // access by access.
             // x itself is taken iff counting it too makes R larger: iff the walk
             // gets, after x's own access, below both -A(x) and every sum before.
             // Each lane walks for its own value, six accesses per table entry.
@@ -622,13 +619,13 @@ __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__
             const uint64_t lt = (1ull << lane) - 1;
             const int sum = (int)__popcll(high & lt) - (int)__popcll(real & le);
             const bool ok = ballot(((real >> lane) & 1) && sum < -(int)nbt) == 0;
-            const uint32_t d = dead + (uint32_t)__popcll(dm) - ((uint32_t)__popcll(ev) - E);
+            const uint32_t d = dead + (uint32_t)__popcll(dm) - ((uint32_t)__popcll(ev) - n_real);
             uint64_t gone = 0;   // lane mask
             if (ok) {
                 dead = d;
                 size = c;   // evictions happened, so the cache is full
                 gone = gone_if;
-                popped = E - (uint32_t)__popcll(gone);
+                popped = n_real - (uint32_t)__popcll(gone);
                 // With next[] one-to-one the buffer gives the rest of the
                 // evictions; copies of a value each count as taken, so that
                 // more may be gone than were evicted.

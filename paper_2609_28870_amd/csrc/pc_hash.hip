@@ -14,8 +14,11 @@
 // request: while the chain wave walks round p, the digest waves load and fold
 // the tokens of round p + 1 and write the keys of round p - 1 out, so a
 // request advances at the chain's own pace and neither memory latency nor
-// the digests are added to it.  Rounds pass through a ring of three LDS
-// tiles (digests, turned into keys in place), and one barrier ends a phase.
+// the digests are added to it.  Rounds pass through two LDS tiles in turn
+// (digests, turned into keys in place), and one barrier ends a phase.  Round
+// p + 1 goes to the tile that round p - 1 leaves in the same phase: a digest
+// lane takes a key out of its place before it puts the digest there (exchange),
+// and a place belongs to the same lane in every round.
 // The chain wave also plans the rounds: it takes requests from a global
 // counter, last to first (contexts grow turn by turn, so the longest chains
 // come early; where it pays the requests are sorted by length first), two

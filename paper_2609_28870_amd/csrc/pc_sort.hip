@@ -341,11 +341,12 @@ constexpr int PERM_LOCAL_BITS = 14;
 constexpr uint64_t LINK_CHUNK_MAX = 1ull << 16;   // elements per workgroup, link
 
 // Work per workgroup: a later pass takes one tile (it reserves per tile), the
-// link, which reserves per chunk, chunks of up to 2^16 elements: with small
-// chunks the runs that its workgroups in flight append to lie close together,
-// and the link, which waits on more loads per element than the plain partition,
-// gains from eight workgroups per CU (3.4e7 elements 337 us, with two 409).  The
-// same on the host (grids) and the device (a count the GPU wrote).
+// link, which reserves per chunk, chunks of up to 2^16 elements, eight per CU
+// where n allows: four of its workgroups are on a CU at a time, so each place
+// takes two chunks or more and ends with the others, and the runs that the
+// workgroups in flight append to lie closer together (3.4e7 elements 337 us,
+// with two chunks per CU 409).  The same on the host (grids) and the device (a
+// count the GPU wrote).
 constexpr int LINK_CHUNKS_PER_CU = 8;
 __host__ __device__ inline uint64_t chunk_elems(uint64_t n, uint64_t chunks, uint64_t cap, uint64_t tile) {
     uint64_t c = (n + chunks - 1) / chunks;
@@ -866,7 +867,7 @@ static PermPlan plan_perm(uint64_t n) {
     // later pass as two chunks per CU; it takes 188 now).
     const int total = nbits - PERM_LOCAL_BITS;
     int width = 8;
-    if (total > 8 && total <= 17 && (total + 1) / 2 < 8) width = (total + 1) / 2;
+    if (total > 8 && total < 15) width = (total + 1) / 2;
     while (cur > PERM_LOCAL_BITS && k < 4) {
         int next_s = cur - width > PERM_LOCAL_BITS ? cur - width : PERM_LOCAL_BITS;
         shifts[k++] = next_s;
