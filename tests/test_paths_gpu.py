@@ -172,3 +172,68 @@ def test_bins_of_values_around_the_edges(n, shift, edges):
     assert [int(x) for x in got["count"]] == count and [int(x) for x in got["depthsum"]] == depthsum
     assert [int(x) for x in got["cost"]] == [3 * a + 2 * b for a, b in zip(count, depthsum)]
     assert [int(x) for x in got["nextuse"]] == hist(gap)
+
+
+def periodic(n, period, key_of, step=1 << 26):
+    """keys[t] = key_of(t mod period), and a check of prev / next against t - period / t + period."""
+    keys = torch.empty(n, dtype=torch.int64, device="cuda")
+    for a in range(0, n, step):
+        keys[a:a + step] = key_of(torch.arange(a, min(a + step, n), device="cuda") % period)
+
+    def check(prev, nxt):
+        for a in range(0, n, step):
+            t = torch.arange(a, min(a + step, n), device="cuda")
+            back, ahead = t - period, t + period
+            back[back < 0] = pc.NONE
+            ahead[ahead >= n] = pc.NONE
+            assert torch.equal(prev[a:a + step].to(torch.int64) & 0xFFFFFFFF, back), a
+            assert torch.equal(nxt[a:a + step].to(torch.int64) & 0xFFFFFFFF, ahead), a
+    return keys, check
+
+
+@pytest.mark.parametrize("n", [1 << 26, (1 << 26) + 8193])
+def test_high_key_bits_inside_the_one_launch_path(n):
+    # from 2^26 keys on the generic path behind the chained one is one launch
+    # again, here with its passes over the high key bits
+    keys, check = periodic(n, (1 << 24) + 5, lambda i: (i << 32) | (i % 4099))
+    reqs = n // 70
+    off = torch.arange(reqs + 1, device="cuda") * n // reqs
+    prev, nxt, ws = pc.prev_next_chained(keys, off)
+    info = pc.chained_info(ws)
+    assert pc.workspace_status(ws) == 0 and info["generic"] and info["high_anchor"], info
+    check(prev, nxt)
+
+
+def test_persistent_launches_on_two_streams_at_once():
+    # their phases wait for chunks, which only running workgroups hold
+    n, sides = 300_007, []
+    off = torch.arange(n // 50 + 1, device="cuda") * n // (n // 50)
+    for seed in (1, 2):
+        keys = device_keys(n, n // 4, low_shared=seed == 2, seed=seed)
+        p, q = oracle.prev_next(keys.cpu().numpy().view(np.uint64))
+        outs = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3)]
+        sides.append((keys, p, q, oracle.stack_distance_bit(p), outs,
+                      pc.workspace(pc.lib().pc_prev_next_chained_ws(n, off.numel() - 1)),
+                      pc.workspace(pc.lib().pc_stack_distance_runs_ws(n)), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for keys, _, _, _, (prev, nxt, dist), ws_pn, ws_sd, stream in sides:
+            with torch.cuda.stream(stream):
+                pc.prev_next_chained(keys, off, prev, nxt, ws_pn)
+                pc.stack_distance_runs(prev, nxt, dist, ws_sd)
+    torch.cuda.synchronize()
+    for _, p, q, d, (prev, nxt, dist), ws_pn, ws_sd, _ in sides:
+        assert pc.workspace_status(ws_pn) == 0 and pc.workspace_status(ws_sd) == 0
+        assert pc.chained_info(ws_pn)["generic"] and pc.runs_info(ws_sd)["generic"]
+        assert np.array_equal(pc.as_u32(prev), p) and np.array_equal(pc.as_u32(nxt), q)
+        assert np.array_equal(pc.as_u32(dist), d)
+
+
+def test_prev_next_above_2e31_keys():
+    # 18 bits above the last step's ranges: a link and two later partition passes
+    n = (1 << 31) + 12_345
+    keys, check = periodic(n, 700_000_001, lambda i: i * (MIX - (1 << 64)))
+    prev, nxt, ws = pc.prev_next_use(keys)
+    assert pc.workspace_status(ws) == 0 and not pc.high_key_passes_ran(ws)
+    del keys
+    check(prev, nxt)
