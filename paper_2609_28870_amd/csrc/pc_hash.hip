@@ -372,7 +372,7 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         // this wave's sweeps that have blocks in a round, as a mask of their
         // (first) rows
         uint64_t mine = 0;
-        for (int q = 0; q < sweeps; ++q) mine |= 1ull << row_of(q);
+        for (int q = 0; G16 != 1 && q < sweeps; ++q) mine |= 1ull << row_of(q);
         auto sweeps_in = [&](const RoundRow &r) {
             uint64_t m = ballot(r.m > (uint32_t)first);
             if constexpr (SHORT)
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(HASH_THREADS, 4) void hash_kernel(
         };
         __syncthreads();   // phase -3: round 0 is planned
         if (lane < ROWS) r1 = L.rows[0][lane];
-        left = sweeps_in(r1);
+        if (G16 != 1) left = sweeps_in(r1);
 #pragma unroll
         for (int k = 0; k < HASH_RING; ++k) {
             if constexpr (G16 == 1) fetch(ring[k], r1, row_of(k), true, 0);
