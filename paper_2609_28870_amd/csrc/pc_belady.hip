@@ -49,10 +49,10 @@
 // there, so a batch waits on no global memory (the next uses, depths and
 // masks come four batches at a time through LDS).  A refill syncs at once.
 //
-// The masks are made for a window of accesses at a time, or they would take
+// The masks are made for a stretch of accesses at a time, or they would take
 // 8.1 bytes per access, many times the bitmaps of a few capacities.  A wave
-// leaves its state in memory at a window's end and takes it up again in the
-// next window's launch.
+// leaves its state in memory at a stretch's end and takes it up again in the
+// next one's launch.
 //
 // Bound: the instructions of one wave, batch after batch, at the capacities
 // that evict most: 4.0e6 agent accesses at 69 capacities 0.139 s, 2.2 us a
@@ -391,18 +391,18 @@ struct BelGroup {
     uint64_t link[BEL_GROUP];
 };
 
-// What a capacity's wave hands from one window to the next.
+// What a capacity's wave hands from one stretch to the next.
 struct BelSaved {
     uint64_t ring[BEL_RING], fl_val[WAVE];
     uint64_t theta, bm_hi, ex_lo, fl_lo, hits, dsum;
     uint32_t buf[BEL_BUF];
     uint32_t bufn, fl_n, dead, size;
-    uint32_t stopped;   // 0 once the window is through: if a check ended it, the later ones do nothing
+    uint32_t stopped;   // 0 once the stretch is through: if a check ended it, the later ones do nothing
 };
 
-// The accesses [from, to), `from` a multiple of BEL_WINDOW: 0, or the state
+// The accesses [from, to), `from` a multiple of BEL_STRETCH: 0, or the state
 // is resumed.  `higher` and `links` are indexed as if they held all accesses;
-// saved: nullptr when there is one window only.  The loop is short of scalar
+// saved: nullptr when there is one stretch only.  The loop is short of scalar
 // registers, so nothing is added to it that can wait elsewhere.
 template <bool RESUME>
 __device__ void belady_one(const uint32_t *__restrict__ next, const uint32_t *__restrict__ depth, uint64_t n,
@@ -829,11 +829,11 @@ __global__ __launch_bounds__(WAVE) void belady_kernel(const uint32_t *__restrict
 static uint64_t bel_w0(uint64_t n) { return (n + 2 * WAVE) / 64 + 1; }
 static uint64_t bel_w1(uint64_t n) { return bel_w0(n) / 64 + 2; }
 
-// Accesses per window: 136 MB of masks.  At a window's end all capacities wait
-// for the slowest: 2.8e7 accesses at 69 capacities 979 ms, in one window 973,
-// in windows of 2^22 992.
-constexpr uint64_t BEL_WINDOW = 1ull << 24;
-static_assert(BEL_WINDOW % (BEL_GROUP * WAVE) == 0 && BEL_WINDOW % (BEL_SYNC * WAVE) == 0, "windows are whole groups");
+// Accesses per stretch: 136 MB of masks.  At its end all capacities wait for the
+// slowest: 2.8e7 accesses at 69 capacities 979 ms, in one stretch 973, in
+// stretches of 2^22 992.
+constexpr uint64_t BEL_STRETCH = 1ull << 24;
+static_assert(BEL_STRETCH % (BEL_GROUP * WAVE) == 0 && BEL_STRETCH % (BEL_SYNC * WAVE) == 0, "stretches are whole groups");
 struct BelWs {
     int32_t *hdr;
     uint64_t *l0, *l1, *links, *higher;
@@ -846,10 +846,10 @@ static BelWs bel_ws(void *ws, uint64_t n, uint32_t n_caps) {
     w.hdr = c.take<int32_t>(WS_HEADER / sizeof(int32_t));
     w.l0 = c.take<uint64_t>(n_caps * (bel_w0(n) + bel_w1(n)));
     w.l1 = w.l0 + n_caps * bel_w0(n);
-    const uint64_t m = n < BEL_WINDOW ? n : BEL_WINDOW;
+    const uint64_t m = n < BEL_STRETCH ? n : BEL_STRETCH;
     w.links = c.take<uint64_t>((m + WAVE - 1) / WAVE);
     w.higher = c.take<uint64_t>(m);
-    w.saved = n > BEL_WINDOW ? c.take<BelSaved>(n_caps) : nullptr;
+    w.saved = n > BEL_STRETCH ? c.take<BelSaved>(n_caps) : nullptr;
     w.bytes = c.off;
     return w;
 }
@@ -879,7 +879,7 @@ pc_status pc_belady(const uint32_t *next, const uint32_t *depth, uint64_t n, con
     if (st != PC_OK) return st;
     uint64_t from = 0;
     do {
-        const uint64_t to = n - from < pc::BEL_WINDOW ? n : from + pc::BEL_WINDOW;
+        const uint64_t to = n - from < pc::BEL_STRETCH ? n : from + pc::BEL_STRETCH;
         if (to > from) {
             const uint64_t per = 4 * pc::WAVE, groups = (to - from + per - 1) / per;
             const uint64_t most = (uint64_t)pc::device_cus() * 16;

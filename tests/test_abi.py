@@ -50,7 +50,7 @@ def test_workspace_queries_grow_with_n(L):
 @pytest.mark.parametrize("k", [1, 8, 69, 1000])
 def test_belady_workspace_is_its_bitmaps(L, n, k):
     # an eighth of a byte per access and capacity, a 64th of that for the
-    # summary, 4 KB a capacity, and the masks of a window of 2^24 accesses at
+    # summary, 4 KB a capacity, and the masks of 2^24 accesses at
     # most (8.1 bytes each)
     bitmaps = k * (n / 8 * (1 + 1 / 64) + 64)
     assert L.pc_belady_ws(n, k) <= 2048 + bitmaps + 4096 * k + 8.2 * min(n, 2 ** 24)

@@ -84,16 +84,16 @@ def test_stream_lengths_around_batches_and_groups(n, distinct):
                          depth)
 
 
-WINDOW = 1 << 24   # accesses whose masks the workspace holds at a time
+STRETCH = 1 << 24   # accesses whose masks the workspace holds at a time
 
 
-@pytest.mark.parametrize("n", [WINDOW, WINDOW + 1, 2 * WINDOW + 12345])
-def test_streams_longer_than_a_window_of_masks(n):
-    # each capacity's wave stops at a window's end and goes on in the next
+@pytest.mark.parametrize("n", [STRETCH, STRETCH + 1, 2 * STRETCH + 12345])
+def test_streams_longer_than_a_stretch_of_masks(n):
+    # each capacity's wave stops at a stretch's end and goes on in the next
     # launch: hits, depths and flags on both sides, nothing past the workspace
     rng = np.random.default_rng(n)
     keys = rng.integers(0, 30000, size=n).astype(np.uint64)
-    keys[WINDOW - 2000:WINDOW + 2000] %= 700       # reuses on both sides of the first edge
+    keys[STRETCH - 2000:STRETCH + 2000] %= 700       # reuses on both sides of the first edge
     cold = rng.random(n) < 0.02
     keys[cold] = 10 ** 6 + np.arange(int(cold.sum()))
     depth = rng.integers(0, 5000, size=n).astype(np.uint32)
